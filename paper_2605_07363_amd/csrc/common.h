@@ -133,6 +133,24 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return x + (lane >= 16 ? t0 : 0) + (lane >= 32 ? t1 : 0) + (lane >= 48 ? t2 : 0);
 }
 
+// Largest value of the wavefront's 64 lanes (all active) in every lane; lanes shifted in from outside
+// a row of 16 count as -inf.
+__device__ __forceinline__ float wave_max_f32(float v) {
+  const int none = (int)0xFF800000u;
+#define MISA_DPP_MAX(ctrl) \
+  v = fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(none, __float_as_int(v), ctrl, 0xf, 0xf, false)))
+  MISA_DPP_MAX(0x111);  // row_shr:1
+  MISA_DPP_MAX(0x112);  // row_shr:2
+  MISA_DPP_MAX(0x114);  // row_shr:4
+  MISA_DPP_MAX(0x118);  // row_shr:8: lane 15 of a row holds the row's maximum
+#undef MISA_DPP_MAX
+  const float a = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
+  const float b = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 31));
+  const float c = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 47));
+  const float d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+  return fmaxf(fmaxf(a, b), fmaxf(c, d));
+}
+
 // Given the totals of the block's wavefronts in wave_total[0 .. nw-1] (nw <= 16), returns the
 // sum of the totals of the wavefronts before this one and, in *total, the sum of all: the
 // first 16 lanes of every wavefront read one total each and scan them.
@@ -156,4 +174,17 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* scratch, int* to
   return waves_before(scratch, nw, total) + inc - v;
 }
 
+// Buffer descriptors (raw, unstrided): accesses at byte offsets >= num_bytes read zeros and
+// drop stores.  Addresses are descriptor base + per-lane byte offset + wave-uniform byte offset.
+using BufferRsrc = __amdgpu_buffer_rsrc_t;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+// base and num_bytes must be the same in every lane: they are moved to scalar registers here,
+// so that the compiler keeps the descriptor there instead of looping over "distinct" lanes.
+__device__ __forceinline__ BufferRsrc make_rsrc(const void* base, uint32_t num_bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+  void* uniform = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(uniform, 0, (int)__builtin_amdgcn_readfirstlane(num_bytes), 0x00020000);
+}
 }  // namespace misa

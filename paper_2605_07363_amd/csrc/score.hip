@@ -117,19 +117,6 @@ union Frag8 {   // 32 fp8 codes: one operand of the fp8 matrix instruction
   uint4 u[2];
 };
 
-// Buffer descriptors (raw, unstrided): accesses at byte offsets >= num_bytes read zeros and
-// drop stores.  Addresses are descriptor base + per-lane byte offset + wave-uniform byte offset.
-using BufferRsrc = __amdgpu_buffer_rsrc_t;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-// base and num_bytes must be the same in every lane: they are moved to scalar registers here,
-// so that the compiler keeps the descriptor there instead of looping over "distinct" lanes.
-__device__ __forceinline__ BufferRsrc make_rsrc(const void* base, uint32_t num_bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  void* uniform = reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
-  return __builtin_amdgcn_make_buffer_rsrc(uniform, 0, (int)__builtin_amdgcn_readfirstlane(num_bytes), 0x00020000);
-}
 __device__ __forceinline__ uint4 buffer_load16(BufferRsrc r, uint32_t lane_off, uint32_t wave_off = 0) {
   const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)wave_off, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);

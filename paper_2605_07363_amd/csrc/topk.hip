@@ -6,333 +6,573 @@
 // the result is expanded from the bitmap in index order with one block-wide
 // prefix sum, so the output is ascending and bit-reproducible without a sort.
 //
-// Common case: after the first digit, the elements that share the threshold
-// digit ("boundary" elements) are few.  They are compacted into a small list
-// and every later digit, and the tie rule (equal values: lower index first),
-// is resolved on that list in LDS, so the row itself is read only twice.
-// If the boundary bin is larger than the list (heavily repeated values), the
-// kernel falls back to two more digit passes over the row and a bitmap of the
-// elements equal to the threshold value.
-//
-// Few long rows (decode): one workgroup per row would leave most of the chip
-// idle.  There topk_prefilter_kernel runs first, up to 16 workgroups per row:
-// each derives the same score threshold from a small sample of the row (so
-// that a few thousand elements pass, at least k of them but for a negligible
-// chance) and hands the elements of its key range that pass to topk_kernel<true>,
-// which selects exactly among them.  A row whose hand-over is not usable (fewer
-// than k passed, too many for the list, or too many tied around the k-th) is
-// redone by the same workgroup with the two passes over the row, so the result
-// never depends on the sample.
+// Usual case (sampled path): the row is read once.  A sample of the row brackets the k-th largest
+// value between two thresholds; while the row streams through registers everything above the
+// upper one goes to the bitmap straight from ballots, and only the few elements between the two
+// are listed and selected from exactly.  The counts found on the way prove the bracket right or
+// wrong, so the result never depends on the sample: a row whose bracket fails (or whose values
+// repeat so much that the list overflows) is redone by the radix select on the row itself, which
+// reads it twice (or four times if the values around the k-th are heavily repeated).
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+#include <utility>
+
 #include "kernels.h"
 #include "radix.h"
 
 namespace misa {
 
-constexpr int kCap = 7000;          // boundary list capacity (entries); sized so two workgroups share a CU
 constexpr int kFew = 64;             // entries around the k-th largest that are ranked directly
-constexpr int kMaxRanges = 16;      // key ranges (workgroups) per row in the prefilter
-constexpr int kMinRange = 8192;     // shortest key range
-constexpr int kSampleLines = 256;   // sampled 16-element lines per row (at most)
-constexpr int kSegInts = 64 + 2 * kCap;  // per (row, range): header (count; threshold and upper key at 8, 9), then (index, key) pairs
+constexpr int kListTarget = 6000;    // boundary list entries of the two-pass path, where LDS is cheap
+
+// How a block of NT threads takes a row.  A short row of at most 16 (256 threads) or 8 elements per
+// thread stays in registers and is its own sample.  Otherwise the row is streamed and at most eight
+// elements per thread are sampled.
+constexpr int kHeldLong = 8;
+__host__ __device__ constexpr int held_short(int nt) { return nt == 256 ? 16 : 8; }
 
 // Visits elements lo..hi-1 of a row with all threads of the block.  Eight
 // coalesced loads per thread are in flight before the first one is used.  f is
 // called by every thread of every wavefront in each round (in == false past
 // the end), so it may contain wavefront-wide operations.
-template <typename F>
+template <int NT, typename F>
 __device__ __forceinline__ void scan_row(const float* __restrict__ s, int lo, int hi, F f) {
   constexpr int U = 8;
-  for (int base = lo; base < hi; base += kTopkThreads * U) {
+  for (int base = lo; base < hi; base += NT * U) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = base + u * kTopkThreads + (int)threadIdx.x;
+      const int i = base + u * NT + (int)threadIdx.x;
       v[u] = i < hi ? s[i] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = base + u * kTopkThreads + (int)threadIdx.x;
+      const int i = base + u * NT + (int)threadIdx.x;
       f(i, v[u], i < hi);
     }
   }
 }
 
-// Length of the key ranges the prefilter cuts a row of L elements into (at most kMaxRanges).
-__host__ __device__ inline int range_len(int L) {
-  const int per = (L + kMaxRanges - 1) / kMaxRanges;
-  const int r = (per + 1023) & ~1023;
-  return r < kMinRange ? kMinRange : r;
+// Sampled 16-element lines of a long row of n elements: about 4096 elements, 8192 for large k and very
+// long rows (they narrow the bracket, whose width in elements grows with sqrt(k n / samples)).
+__host__ __device__ inline int sample_lines(int n, int k, int nt) {
+  return nt == kTopkThreads && (n <= 8192 || k > 4096 || n > 131072) ? 512 : 256;
 }
 
-// ---------------------------------------------------------------- sampled prefilter
-// Workgroup (range, t, seq).  Sample: the row's n visible elements form lines of 16; of every
-// `ls` consecutive lines one (picked by a multiplicative hash) is read, at most kSampleLines
-// lines.  With m samples, the sample element of rank r = k m/n + 6 sqrt(k m/n) + 8 gives the
-// threshold: the number of row elements above it is >= k unless the sample is more than six
-// standard deviations off.  Only the two upper digits of that element's key are resolved (22
-// bits), so a few more elements pass.  Every workgroup of a row computes the same threshold.
-__global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p,
-                                                                      const float* __restrict__ S,
-                                                                      int k, int rlen,
-                                                                      int* __restrict__ pre) {
-  __shared__ int hist[kBins];
-  __shared__ int hist2[kBins];
-  __shared__ int scan_scratch[32];
-  __shared__ int thr[3];
-  __shared__ int thr_up[3];
-  __shared__ int cnt;
-  constexpr int SPT = kSampleLines * 16 / kTopkThreads;  // samples per thread
-  constexpr int U = 8;
-  const int range = blockIdx.x, t = blockIdx.y, seq = blockIdx.z, tid = threadIdx.x;
-  const size_t row = (size_t)seq * p.n_q + t;
-  const int n = visible(p, seq, t);
-  const int lo = range * rlen, hi = min(lo + rlen, n);
-  const int k_eff = min(k, n);
-  if (lo >= hi || k_eff == n) return;   // nothing here / every element is selected anyway
-  const float* s = S + row * p.L;
-  int* seg = pre + (row * gridDim.x + range) * kSegInts;
+// LDS words of the bitmap of a row, which a histogram has to fit as well.
+__host__ __device__ inline int sel_words(int row_len) { return max((row_len + 31) / 32, kBins); }
 
-  // samples and the first round of the range are loaded together
-  const int lines = (n + 15) >> 4;
-  const int ls = (lines + kSampleLines - 1) / kSampleLines;
+// ---------------------------------------------------------------- sampled path
+//
+//   sample   16-element lines, one of every `ls` at a hashed place (the short rows of the smaller
+//            blocks are their own sample and stay in registers).  The k-th largest of the row lies
+//            between the sample elements of rank r_hi and r_lo = k m/n -+ (6 sqrt(k m/n) + 8): the
+//            number of the top k in the sample has mean k m/n and no larger variance.  Both are
+//            found by a histogram that is linear between the smallest and the largest sample, again
+//            on the bins around them where outliers left these too coarse, and rounded outwards to
+//            the values lo and hi of the bracket.
+//   stream   Elements >= lo (and NaN) go to the list, at places counted from the ballots of the
+//            compares; a wavefront claims the places of eight ballots with one atomic: five vector
+//            instructions per 64 elements.  (At the 6 TB/s of the memory a CU has time for that many
+//            and no more; with the bitmap marked here from a second compare, and a list of only the
+//            elements in between, the same rows took 1.3 times as long.)  A register is requested
+//            again as soon as its elements have been looked at.
+//            A list segment per wavefront instead of the claims overflows where the large values lie
+//            in stretches.
+//   select   Entries >= hi are sure and only counted; need = k - sure of the others are found by a
+//            histogram that is linear over [lo, hi), and a second one inside a crowded bin; the few
+//            entries in the bin of the need-th are ranked against each other, or, if there are many
+//            (repeated values), resolved by the digits of key and index.
+//
+// The row is left to the two-pass path if sure > k, or fewer than k or more than the list holds pass, or
+// a NaN turns up.  Candidate rows never select -inf: it lies below the bracket.
+// The histograms share their LDS with the bitmap, which is cleared once the last of them has been read.
+//
+// Measured: 4096 rows of 65536, k = 2048: 212 us = 5.1 TB/s (two passes over each row: 402 us; sample and
+// stream alone, nothing selected: 190 us); 64 rows of 32768: 13.8 us (17.3 us in two launches).  Few rows
+// are a chain of barrier-separated phases of one workgroup.
+struct Bracket {
+  float lo, hi;
+  float edge;   // upper end of the histogram: hi where it is finite
+};
+
+// What the phases of a block share.
+template <int NT>
+struct TopkLds {
+  int scan_scratch[32];
+  int thr[3], thr_up[3];
+  int list_fill, few_len, nan_seen;
+  int wave_sure[NT / 64];
+  float wave_min[NT / 64], wave_max[NT / 64];
+  uint32_t fkey[kFew];
+  int fidx[kFew];
+  int frank[kFew];   // entries of the few that rank before an entry
+};
+
+// values at or above `from`, in bins of 1 / scale; all others in bin 0, values past the end in the last
+__device__ __forceinline__ int linear_bin(float v, float from, float scale) {
+  return (int)__builtin_amdgcn_fmed3f((v - from) * scale, 0.f, (float)(kBins - 1));
+}
+
+// The bracket of a row's k-th largest of n > k elements; false if the sample gives none (block-uniform).
+// `held` receives the thread's sample, `have` says which of it are elements; `also` is called once the
+// sample's loads have been issued.  Leaves hist cleared.
+template <int NT, bool SHORT, int HELD, typename F>
+__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int k, float (&held)[HELD],
+                                               uint32_t& have, int* hist, TopkLds<NT>& L, Bracket& br, F also) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  have = 0;
+  const int lines = (n + 15) >> 4, max_lines = SHORT ? lines : sample_lines(n, k, NT);
+  const int ls = (lines + max_lines - 1) / max_lines;
   const int groups = lines / ls;       // >= 1
-  uint32_t skey[SPT];
-  bool sin[SPT];
-  float sv[SPT], cv[U];
+  // (16-bit hash and ls <= 128: 24-bit products)
+  auto line_of = [&](uint32_t g) { return (int)(__umul24(g, ls) + (__umul24((g * 2654435761u) >> 16, ls) >> 16)); };
 #pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    const int smp = tid + u * kTopkThreads, g = smp >> 4;
-    const int line = g * ls + (int)((((uint32_t)g * 2654435761u) >> 16) % (uint32_t)ls);
-    const int i = line * 16 + (smp & 15);
-    sin[u] = g < groups && i < n;
-    sv[u] = sin[u] ? s[i] : 0.f;
+  for (int u = 0; u < HELD; ++u) {
+    const int smp = tid + u * NT, g = smp >> 4;
+    const int i = SHORT ? smp : line_of(g) * 16 + (smp & 15);
+    const bool in = (SHORT || g < groups) && i < n;
+    have |= in ? 1u << u : 0u;
+    held[u] = s[in ? i : 0];
   }
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = lo + u * kTopkThreads + tid;
-    cv[u] = i < hi ? s[i] : 0.f;
-  }
-  if (tid == 0) cnt = 0;
-  for (int i = tid; i < kBins; i += kTopkThreads) hist2[i] = 0;
-  zero_hist(hist);
-#pragma unroll
-  for (int u = 0; u < SPT; ++u) {
-    skey[u] = order_key(sv[u]);
-    if (sin[u]) atomicAdd(&hist[skey[u] >> 21], 1);
-  }
+  also();
+  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+  if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
+  if (tid < kFew) L.frank[tid] = 0;
   // number of samples: 16 per sampled line, less what the row's last line lacks if it is one
   int m = 16 * groups;
   {
     const int last = lines - 1, g = last / ls;
-    if (g < groups && g * ls + (int)((((uint32_t)g * 2654435761u) >> 16) % (uint32_t)ls) == last)
-      m -= 16 * lines - n;
+    if (g < groups && line_of(g) == last) m -= 16 * lines - n;
   }
-  __syncthreads();
-  const float kf = (float)k_eff * (float)m / (float)n;
-  const int r = (int)ceilf(kf + 6.f * sqrtf(kf) + 8.f);
-  uint32_t tau = 0;                    // r > m: everything passes
-  uint32_t upper = 0xFFFFFFFFu;        // top of the digit that holds the sample element of rank r/4
-  if (r <= m) {
-    find_threshold_bin(hist, r, scan_scratch, thr, max(r / 4, 1), thr_up);
-    const uint32_t d1 = thr[0];
-    const int need = thr[1];
-    upper = ((uint32_t)thr_up[0] << 21) | 0x1FFFFFu;
+  int r_lo = k, r_hi = k;
+  if (ls > 1) {
+    const float kf = (float)k * (float)m / (float)n, margin = 6.f * sqrtf(kf) + 8.f;
+    r_lo = (int)ceilf(kf + margin);
+    r_hi = (int)floorf(kf - margin);
+  }
+  if (r_lo > m) return false;           // (block-uniform, as every early return here)
+  float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
-    for (int u = 0; u < SPT; ++u)
-      if (sin[u] && (skey[u] >> 21) == d1) atomicAdd(&hist2[(skey[u] >> 10) & 0x7FF], 1);
+  for (int u = 0; u < HELD; ++u)
+    if (((have >> u) & 1) && fabsf(held[u]) < INFINITY) { lo = fminf(lo, held[u]); hi = fmaxf(hi, held[u]); }
+  lo = -wave_max_f32(-lo);
+  hi = wave_max_f32(hi);
+  if (lane == 0) { L.wave_min[wave] = lo; L.wave_max[wave] = hi; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
+  for (int pass = 0;; ++pass) {
+    const float width = (hi - lo) * (1.f / kBins), per = (float)kBins / (hi - lo);
+    if (!(width > 0.f) || !(per < 3e38f) || !(per > 0.f)) return false;
+#pragma unroll
+    for (int u = 0; u < HELD; ++u)
+      if ((have >> u) & 1) atomicAdd(&hist[linear_bin(held[u], lo, per)], 1);
     __syncthreads();
-    find_threshold_bin(hist2, need, scan_scratch, thr);
-    tau = (d1 << 21) | ((uint32_t)thr[0] << 10);
+    find_threshold_bin_n<NT>(hist, r_lo, L.scan_scratch, L.thr, max(r_hi, 1), L.thr_up);
+    const int b_lo = L.thr[0], b_hi = L.thr_up[0];
+    const int crowd = max(L.thr[2], L.thr_up[2]);
+    br.lo = lo + ((float)b_lo - 0.02f) * width;
+    br.edge = lo + ((float)b_hi + 1.02f) * width;
+    br.hi = r_hi >= 1 ? br.edge : INFINITY;
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0;   // (read by everybody: find_threshold_bin ends with a barrier)
+    __syncthreads();
+    if (crowd <= 64 || pass == 2) return true;
+    lo = br.lo;
+    hi = br.edge;
   }
-
-  // elements of the range at or above the threshold -> the segment; the count goes on past
-  // the capacity so that the reader sees the overflow
-  int2* ent = reinterpret_cast<int2*>(seg + 64);
-  for (int base = lo; base < hi; base += kTopkThreads * U) {
-    if (base > lo) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = base + u * kTopkThreads + tid;
-        cv[u] = i < hi ? s[i] : 0.f;
-      }
-    }
-    // one counter update per wavefront and round: the slots of its passing elements follow
-    // each other in (u, lane) order
-    uint32_t key[U];
-    unsigned long long mask[U];
-    int total = 0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      key[u] = order_key(cv[u]);
-      mask[u] = __ballot(base + u * kTopkThreads + tid < hi && key[u] >= tau);
-      total += __popcll(mask[u]);
-    }
-    if (total) {   // wavefront-uniform
-      const int lane = tid & 63;
-      int slot = 0;
-      if (lane == 0) slot = atomicAdd(&cnt, total);
-      slot = __builtin_amdgcn_readfirstlane(slot);
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if ((mask[u] >> lane) & 1) {
-          const int c = slot + __popcll(mask[u] & ((1ull << lane) - 1ull));
-          if (c < kCap) ent[c] = make_int2(base + u * kTopkThreads + tid, (int)key[u]);
-        }
-        slot += __popcll(mask[u]);
-      }
-    }
-  }
-  __syncthreads();
-  if (tid == 0) { seg[0] = cnt; seg[8] = (int)tau; seg[9] = (int)upper; }
 }
 
-// ---------------------------------------------------------------- per-row kernel
-// Candidate mode (CAND): the elements at or above the sampled threshold were left in `pre` by
-// topk_prefilter_kernel, in ranges of rlen elements.  They become the list.  One digit is
-// taken of key - threshold, scaled so that the interval [threshold, upper key] of the
-// hand-over fills the 2047 lower values of the digit (larger keys share digit 2047); entries
-// above the digit of the k-th largest are selected, the few entries in it are ranked against
-// each other.  Returns false, with nothing selected, if the hand-over is unusable (fewer than
-// k entries, more than the list holds) or more than 64 entries share that digit.
-__device__ __forceinline__ bool topk_from_candidates(const int* __restrict__ segs, int ranges, int k,
-                                                     uint32_t* sel, uint32_t* lkey, int* lidx,
-                                                     int* hist, int* scan_scratch, int* thr,
-                                                     int* list_len) {
-  __shared__ int seg_base[kMaxRanges + 1];
-  __shared__ int seg_cnt[kMaxRanges];
-  __shared__ int seg_max;
-  __shared__ uint32_t bkey[64];
-  __shared__ int bidx[64];
-  __shared__ uint32_t key_lo, key_span;
-  __shared__ int cand_ok;
-  const int tid = threadIdx.x;
-  if (tid < 64) {   // lane c looks after range c
-    const bool live = tid < ranges;
-    const int cnt = live ? segs[(size_t)tid * kSegInts] : 0;
-    const uint32_t lo_key = (uint32_t)segs[8], up_key = (uint32_t)segs[9];
-    const bool bad = live && (cnt < 0 || cnt > kCap);
-    const int inc = wave_inclusive_scan(bad ? 0 : cnt);
-    int mx = cnt;
+// The elements of a stretch of the row that reach `lo` go to the list (`cap` entries and 64 of slack,
+// its fill in *fill, which counts on past cap); indices are counted from `first`.  The eight values of a
+// lane: the compares, one claim of list places for all that pass, the places, the stores.
+template <typename INDEX>
+__device__ __forceinline__ void list_append(const float (&x)[8], float lo, uint2* list, int cap, int* fill, INDEX index) {
+  unsigned long long pass[8];
+  int total = 0;
 #pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) mx = max(mx, __shfl_xor(mx, o));   // kMaxRanges = 16 lanes matter
-    const int tot = __builtin_amdgcn_readlane(inc, 63);
-    const bool any_bad = __ballot(bad) != 0;
-    if (live) { seg_cnt[tid] = cnt; seg_base[tid] = inc - cnt; }
-    if (tid == 0) {
-      seg_base[ranges] = tot;
-      seg_max = mx;
-      key_lo = lo_key;
-      key_span = up_key > lo_key ? up_key - lo_key : 1u;
-      cand_ok = !any_bad && tot <= kCap && tot >= k;
+  for (int c = 0; c < 8; ++c) {
+    pass[c] = __builtin_amdgcn_ballot_w64(!(x[c] < lo));
+    total += __popcll(pass[c]);
+  }
+  int base = 0;
+  if ((threadIdx.x & 63) == 0) base = atomicAdd(fill, total);
+  base = __builtin_amdgcn_readfirstlane(base);
+  uint32_t* at[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const uint32_t below = __builtin_amdgcn_mbcnt_hi((uint32_t)(pass[c] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pass[c], 0));
+    at[c] = reinterpret_cast<uint32_t*>(list + min(base, cap)) + 2 * below;
+    base += __popcll(pass[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    if (__builtin_amdgcn_inverse_ballot_w64(pass[c])) {
+      at[c][0] = __float_as_uint(x[c]);
+      at[c][1] = (uint32_t)index(c);
     }
   }
-  __syncthreads();
-  if (!cand_ok) return false;
+}
 
-  const int len = seg_base[ranges];
-  const uint32_t klo = key_lo, span = key_span;
-  const int sh = __clz(span);
-  auto digit = [&](uint32_t key) {
-    const uint32_t x = key - klo;
-    return x > span ? (uint32_t)(kBins - 1) : (x << sh) >> 21;
-  };
-  // one entry of every range per thread and round.  The loads are unconditional (clamped to
-  // the range's last entry and the row's last range), so all of a round are in flight together.
-  int cnt_c[kMaxRanges], base_c[kMaxRanges];
-#pragma unroll
-  for (int c = 0; c < kMaxRanges; ++c) {
-    cnt_c[c] = c < ranges ? seg_cnt[c] : 0;
-    base_c[c] = seg_base[min(c, ranges)];
+// A stretch of n elements: vectors of four elements per thread in blocks of 4 NT elements, the rest one
+// by one.  begin() requests the first vectors.
+typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // (16-byte loads need 4-byte alignment only)
+template <int NT, int AHEAD>
+struct Stream {
+  const float* s;
+  int n, blocks;
+  f32x4_u v[AHEAD];
+
+  __device__ __forceinline__ f32x4_u request(int block) const {
+    return reinterpret_cast<const f32x4_u*>(s + min(block, blocks - 1) * 4 * NT)[threadIdx.x];
   }
-  for (int off = tid; off < seg_max; off += kTopkThreads) {
-    int2 e[kMaxRanges];
+  __device__ __forceinline__ void begin(const float* s_, int n_) {
+    s = s_;
+    n = n_;
+    blocks = n / (4 * NT);
+    if (blocks == 0) return;
 #pragma unroll
-    for (int c = 0; c < kMaxRanges; ++c) {
-      const int2* ent = reinterpret_cast<const int2*>(segs + (size_t)min(c, ranges - 1) * kSegInts + 64);
-      e[c] = ent[min(off, max(cnt_c[c] - 1, 0))];
-    }
+    for (int u = 0; u < AHEAD; ++u) v[u] = request(u);
+  }
+  __device__ __forceinline__ void filter(float lo, int first, uint2* list, int cap, int* fill) {
+    const int tid = threadIdx.x, rest0 = blocks * 4 * NT;
+    float rest[4];
 #pragma unroll
-    for (int c = 0; c < kMaxRanges; ++c)
-      if (off < cnt_c[c]) {
-        const int j = base_c[c] + off;
-        lidx[j] = e[c].x;
-        lkey[j] = (uint32_t)e[c].y;
-        atomicAdd(&hist[digit((uint32_t)e[c].y)], 1);
+    for (int u = 0; u < 4; ++u) rest[u] = s[min(rest0 + u * NT + tid, n - 1)];
+    auto two_blocks = [&](const f32x4_u& p, const f32x4_u& q, int block) {
+      const float x[8] = {p[0], p[1], p[2], p[3], q[0], q[1], q[2], q[3]};
+      const int i = first + (block * NT + tid) * 4;
+      list_append(x, lo, list, cap, fill, [&](int c) { return i + (c >> 2) * 4 * NT + (c & 3); });
+    };
+    int block = 0;
+    for (; block + AHEAD <= blocks; block += AHEAD) {
+#pragma unroll
+      for (int u = 0; u < AHEAD; u += 2) {
+        two_blocks(v[u], v[u + 1], block + u);
+        v[u] = request(block + u + AHEAD);
+        v[u + 1] = request(block + u + 1 + AHEAD);
       }
-  }
-  __syncthreads();
-  find_threshold_bin(hist, k, scan_scratch, thr);
-  const uint32_t d1 = thr[0];
-  const int need = thr[1], nb = thr[2];
-  if (nb > 64 || d1 == kBins - 1) {   // block-uniform
-    __syncthreads();
-    zero_hist(hist);
-    return false;
-  }
-  for (int i = tid; i < len; i += kTopkThreads) {
-    const uint32_t key = lkey[i], a = digit(key);
-    if (a > d1) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
-    const int b = wave_append(a == d1, list_len);
-    if (b >= 0) { bkey[b] = key; bidx[b] = lidx[i]; }
-  }
-  __syncthreads();
-  if (tid < nb) {
-    const uint32_t key = bkey[tid];
-    const int e = bidx[tid];
-    int rank = 0;
-    for (int j = 0; j < nb; ++j) {
-      const uint32_t kj = bkey[j];
-      rank += (kj > key || (kj == key && bidx[j] < e)) ? 1 : 0;
     }
-    if (rank < need) atomicOr(&sel[e >> 5], 1u << (e & 31));
+    const f32x4_u none = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+    for (int u = 0; u < AHEAD - 1; u += 2)
+      if (block + u < blocks) two_blocks(v[u], block + u + 1 < blocks ? v[u + 1] : none, block + u);
+    if (rest0 < n) {
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        x[u] = rest0 + u * NT + tid < n ? rest[u] : -INFINITY;
+        x[4 + u] = -INFINITY;
+      }
+      list_append(x, lo, list, cap, fill, [&](int u) { return first + rest0 + u * NT + tid; });
+    }
   }
+};
+
+// The top k of a row of n elements from the list of those that reach br.lo into the bitmap sel (whose
+// LDS is hist, cleared, before).  false: see above.
+template <int NT>
+__device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, const Bracket& br,
+                                              uint32_t* sel, TopkLds<NT>& L) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int* hist = reinterpret_cast<int*>(sel);
+  auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
+  const float fine = (float)kBins / (br.edge - br.lo);   // entries above share the last bin
+  if (listed < k || listed > cap) return false;
+  int sure = 0;
+  bool nan = false;
+  for (int j0 = 0; j0 < listed; j0 += NT) {
+    const int j = j0 + tid;
+    const bool live = j < listed;
+    const float x = live ? __uint_as_float(list[j].x) : 0.f;
+    nan |= x != x;
+    sure += __popcll(__builtin_amdgcn_ballot_w64(live && x >= br.hi));
+    if (live && x < br.hi) atomicAdd(&hist[linear_bin(x, br.lo, fine)], 1);
+  }
+  if (nan) L.nan_seen = 1;
+  if (lane == 0) L.wave_sure[wave] = sure;
+  __syncthreads();
+  if (L.nan_seen) return false;
+  int total_sure;
+  waves_before(L.wave_sure, NT / 64, &total_sure);
+  int need = k - total_sure;
+  if (need < 0) return false;
+  find_threshold_bin_n<NT>(hist, max(need, 1), L.scan_scratch, L.thr);
+  const int b = need > 0 ? L.thr[0] : kBins;             // need == 0: the sure ones are all
+  int few = need > 0 ? L.thr[2] : 0;
+  // A crowded bin (the bracket of a row with far outliers is wide) is cut into 2048 finer ones.  rank of an
+  // entry against the need-th: 2 above, 1 undecided, 0 below.
+  const float from2 = br.lo + (float)b / fine, fine2 = fine * (float)kBins;
+  int b2 = -1;
+  auto side = [&](float x) {
+    const int d = x >= br.hi ? kBins + 1 : linear_bin(x, br.lo, fine);
+    if (d != b || b2 < 0) return d > b ? 2 : d == b ? 1 : 0;
+    const int d2 = linear_bin(x, from2, fine2);
+    return d2 > b2 ? 2 : d2 == b2 ? 1 : 0;
+  };
+  if (few > kFew) {
+    need = L.thr[1];
+    __syncthreads();
+    zero_hist_n<NT>(hist);
+    for (int j = tid; j < listed; j += NT) {
+      const float x = __uint_as_float(list[j].x);
+      if (side(x) == 1) atomicAdd(&hist[linear_bin(x, from2, fine2)], 1);
+    }
+    __syncthreads();
+    find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr);
+    b2 = L.thr[0];
+    few = L.thr[2];
+  }
+  need = L.thr[1];
+  if (few > kFew) {
+    // digits of the key, most significant first, then of the index, inverted so that a lower index ranks higher
+    uint64_t prefix = 0;
+    auto rank_of = [&](uint2 e) {
+      return ((uint64_t)order_key(__uint_as_float(e.x)) << 20) | (uint64_t)(0xFFFFFu - e.y);
+    };
+#pragma unroll 1
+    for (int shift = 41; shift >= -3; shift -= 11) {     // 52 bits: 11 at 41, 30, 19, 8 and the last 8
+      const int low = max(shift, 0), bits = shift < 0 ? 11 + shift : 11;
+      __syncthreads();
+      zero_hist_n<NT>(hist);
+      for (int j = tid; j < listed; j += NT) {
+        const uint64_t r = rank_of(list[j]);
+        if (side(__uint_as_float(list[j].x)) != 1) continue;
+        if (low + bits == 52 || (r >> (low + bits)) == prefix) atomicAdd(&hist[(int)(r >> low) & ((1 << bits) - 1)], 1);
+      }
+      __syncthreads();
+      find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr);
+      prefix = (prefix << bits) | (uint64_t)L.thr[0];
+      need = L.thr[1];
+    }
+    for (int i = tid; i < (n + 31) >> 5; i += NT) sel[i] = 0;
+    __syncthreads();
+    for (int j = tid; j < listed; j += NT) {
+      const int where = side(__uint_as_float(list[j].x));
+      if (where == 2 || (where == 1 && rank_of(list[j]) >= prefix)) mark((int)list[j].y);
+    }
+    __syncthreads();
+    return true;
+  }
+  for (int i = tid; i < (n + 31) >> 5; i += NT) sel[i] = 0;
+  __syncthreads();
+  for (int j0 = 0; j0 < listed; j0 += NT) {
+    const int j = j0 + tid;
+    const uint2 e = list[min(j, listed - 1)];
+    const float x = __uint_as_float(e.x);
+    const int where = j < listed ? side(x) : 0;
+    if (where == 2) mark((int)e.y);
+    const int at = wave_append(where == 1, &L.few_len);
+    if (at >= 0) { L.fkey[at] = order_key(x); L.fidx[at] = (int)e.y; }
+  }
+  __syncthreads();
+  {
+    // all pairs, spread over the block: a wavefront compares each of the (at most 64) entries with its
+    // share of the others (one thread per entry and a loop over the others took up to 7 us)
+    constexpr int JP = kFew / (NT / 64);
+    const int j0 = wave * JP;
+    if (lane < few && j0 < few) {
+      const uint32_t key = L.fkey[lane];
+      const int e = L.fidx[lane];
+      int part = 0;
+#pragma unroll
+      for (int j = j0; j < j0 + JP; ++j)
+        part += (j < few && (L.fkey[j] > key || (L.fkey[j] == key && L.fidx[j] < e))) ? 1 : 0;
+      if (part) atomicAdd(&L.frank[lane], part);
+    }
+  }
+  __syncthreads();
+  if (tid < few && L.frank[tid] < need) mark(L.fidx[tid]);
   __syncthreads();
   return true;
 }
 
-template <bool CAND>
+// The selected entries of the list in index order: the place of one is the number of selected elements in
+// the bitmap words before its own (before[], 16 bits: k <= 16384) and below it in its word.
+template <int NT>
+__device__ __forceinline__ void write_listed(const uint2* list, int listed, int n, int k, const uint32_t* sel,
+                                             uint16_t* before, int* scan_scratch, const int* __restrict__ map,
+                                             int* __restrict__ out_idx, float* __restrict__ out_val) {
+  const int tid = threadIdx.x, nwords = (n + 31) / 32;
+  const int wpt = (nwords + NT - 1) / NT;
+  const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
+  int cnt = 0;
+  for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
+  int total;
+  int pos = block_exclusive_scan(cnt, scan_scratch, &total);
+  for (int w = w_lo; w < w_hi; ++w) {
+    before[w] = (uint16_t)pos;
+    pos += __popc(sel[w]);
+  }
+  __syncthreads();
+  for (int j = tid; j < listed; j += NT) {
+    const uint2 e = list[j];
+    const uint32_t word = sel[e.y >> 5], bit = 1u << (e.y & 31);
+    const int at = before[e.y >> 5] + __popc(word & (bit - 1u));
+    if ((word & bit) && at < k) {     // at < k: always true when the selection is consistent
+      out_idx[at] = map ? map[e.y] : (int)e.y;
+      if (out_val) out_val[at] = __uint_as_float(e.x);
+    }
+  }
+}
+
+// ---------------------------------------------------------------- few long rows
+// One workgroup per row would leave most of the chip idle, and a single CU needs longer to read a long
+// row than the rest of the work takes.  Workgroup (range, t, seq) of this
+// kernel finds the row's bracket from the sample, as every workgroup of the row does, and lists the
+// elements of its key range that reach it in the range's segment of the workspace; topk_kernel<LISTED>
+// selects from the segments of a row.  Two launches: rows up to 65536 elements are faster in one (32768:
+// 13.8 us against 17.3 us; 131072: 24.0 us against 21.2 us).
+constexpr int kMaxRanges = 16;      // key ranges (workgroups) per row
+constexpr int kSegCap = 7000;       // entries of a segment
+constexpr int kSegInts = 64 + 2 * (kSegCap + 64);   // header (fill, or -1: no bracket; bracket at 8 .. 10), then entries
+
+// Length of the key ranges a row of L elements is cut into (at most kMaxRanges of them).
+__host__ __device__ inline int range_len(int L) {
+  const int per = (L + kMaxRanges - 1) / kMaxRanges;
+  return max((per + 4095) & ~4095, 8192);
+}
+
+__global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, const float* __restrict__ S, int k,
+                                                                      int rlen, int* __restrict__ pre) {
+  constexpr int NT = kTopkThreads;
+  __shared__ int hist[kBins];
+  __shared__ TopkLds<NT> L;
+  const int range = blockIdx.x, t = blockIdx.y, seq = blockIdx.z;
+  const size_t row = (size_t)seq * p.n_q + t;
+  const int n = visible(p, seq, t);
+  const int lo = range * rlen, hi = min(lo + rlen, n);
+  if (lo >= hi || k >= n) return;       // nothing here / every element is selected anyway
+  const float* s = S + row * p.L;
+  int* seg = pre + (row * gridDim.x + range) * kSegInts;
+  float held[kHeldLong];
+  uint32_t have;
+  Bracket br;
+  Stream<NT, 2> st;
+  const bool ok = sample_bracket<NT, false>(s, n, k, held, have, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
+  if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    seg[0] = ok ? L.list_fill : -1;
+    seg[8] = __float_as_int(br.lo);
+    seg[9] = __float_as_int(br.hi);
+    seg[10] = __float_as_int(br.edge);
+  }
+}
+
+// The segments of a row's ranges into the list; returns its length, or -1 if there is no bracket or a
+// segment or the list overflowed.  Wavefront w takes range w.
+__device__ __forceinline__ int gather_segments(const int* __restrict__ segs, int ranges, uint2* list, int cap, Bracket& br) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int cnt = lane < ranges ? segs[(size_t)lane * kSegInts] : 0;
+  br.lo = __int_as_float(segs[8]);
+  br.hi = __int_as_float(segs[9]);
+  br.edge = __int_as_float(segs[10]);
+  const bool bad = __ballot(cnt < 0 || cnt > kSegCap) != 0;
+  const int end = row16_inclusive_scan(cnt);             // (kMaxRanges = 16 lanes matter)
+  const int total = __builtin_amdgcn_readlane(end, 15);
+  if (bad || total > cap) return -1;
+  if (wave < ranges) {
+    const int mine = __builtin_amdgcn_readlane(cnt, wave), at = __builtin_amdgcn_readlane(end, wave) - mine;
+    const uint2* src = reinterpret_cast<const uint2*>(segs + (size_t)wave * kSegInts + 64);
+    for (int j0 = lane; j0 < mine; j0 += 512) {
+      uint2 e[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) e[u] = src[min(j0 + 64 * u, mine - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (j0 + 64 * u < mine) list[at + j0 + 64 * u] = e[u];
+    }
+  }
+  return total;
+}
+
+// ---------------------------------------------------------------- per-row kernel
+enum { kRowShort, kRowLong, kRowListed };   // held in registers / streamed / listed by topk_prefilter_kernel
+
+template <int NT, int KIND>
 __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict__ S, int row_len,
                                          int k, const int* __restrict__ map, int* __restrict__ idx,
-                                         float* __restrict__ val, const int* __restrict__ pre,
-                                         int rlen, int t, int seq, uint32_t* dyn,
-                                         bool all_slots = false) {
-  // dyn: sel bitmap, then eq bitmap OR list (keys, idx)
-  __shared__ int hist[kBins];
-  __shared__ int scan_scratch[32];
-  __shared__ int thr[3];
+                                         float* __restrict__ val, const int* __restrict__ pre, int cap,
+                                         int list_cap, int t, int seq, uint32_t* dyn, bool all_slots = false) {
+  // dyn: sel bitmap (sampled path: and its histograms), then the list of the sampled path, or the two-pass
+  // path's histogram and its eq bitmap OR list (keys, idx)
+  __shared__ TopkLds<NT> L;
   __shared__ int list_len;
-  __shared__ int few_len;
-  __shared__ uint32_t fkey[kFew];
-  __shared__ int fidx[kFew];
+  int* const scan_scratch = L.scan_scratch;
+  int* const thr = L.thr;
 
   const int tid = threadIdx.x;
   const size_t row = (size_t)seq * p.n_q + t;
   const float* s = S + row * row_len;
   const int n = (map || all_slots) ? row_len : visible(p, seq, t);
-  const int nwords_max = (row_len + 31) / 32;
   uint32_t* sel = dyn;
-  uint32_t* eq = dyn + nwords_max;       // fallback path
-  uint32_t* lkey = dyn + nwords_max;     // list path (aliases eq)
-  int* lidx = reinterpret_cast<int*>(lkey + kCap);
+  uint32_t* region = dyn + sel_words(row_len);
+  int* hist = reinterpret_cast<int*>(region);
+  uint32_t* eq = region + kBins;         // two-pass path
+  uint32_t* lkey = region + kBins;       // its list (aliases eq)
+  int* lidx = reinterpret_cast<int*>(lkey + list_cap);
   const int nwords = (n + 31) / 32;
   int* out_idx = idx + row * k;
   float* out_val = val ? val + row * k : nullptr;
 
-  for (int i = tid; i < nwords; i += kTopkThreads) sel[i] = 0;
-  if (tid == 0) { list_len = 0; few_len = 0; }
-  zero_hist(hist);
-
-  bool done = false;
-  if (CAND && k < n) {   // never with map / all_slots; k >= n: every element is selected below
-    const int ranges_row = (row_len + rlen - 1) / rlen;
-    done = topk_from_candidates(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, k, sel,
-                                lkey, lidx, hist, scan_scratch, thr, &list_len);
+  if (k < n && cap > 0) {
+    bool done = false;
+    uint2* list = reinterpret_cast<uint2*>(region);
+    uint16_t* before = reinterpret_cast<uint16_t*>(list + cap + 64);
+    int listed = 0;
+    int* sample_hist = reinterpret_cast<int*>(sel);
+    Bracket br;
+    if constexpr (KIND == kRowListed) {
+      const int rlen = range_len(row_len), ranges_row = (row_len + rlen - 1) / rlen;
+      for (int i = tid; i < kBins; i += NT) sample_hist[i] = 0;
+      if (tid == 0) { L.few_len = 0; L.nan_seen = 0; }
+      if (tid < kFew) L.frank[tid] = 0;
+      listed = gather_segments(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br);
+      __syncthreads();
+      done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
+    } else if constexpr (KIND == kRowShort) {
+      float held[held_short(NT)];
+      uint32_t have;
+      if (sample_bracket<NT, true>(s, n, k, held, have, sample_hist, L, br, [] {})) {
+#pragma unroll
+        for (int u = 0; u < held_short(NT); u += 8) {
+          float x[8];
+#pragma unroll
+          for (int c = 0; c < 8; ++c) x[c] = (have >> (u + c)) & 1 ? held[u + c] : -INFINITY;
+          list_append(x, br.lo, list, cap, &L.list_fill, [&](int c) { return (u + c) * NT + tid; });
+        }
+        __syncthreads();
+        listed = L.list_fill;
+        done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
+      }
+    } else {
+      float held[kHeldLong];
+      uint32_t have;
+      Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
+      if (sample_bracket<NT, false>(s, n, k, held, have, sample_hist, L, br, [&] { st.begin(s, n); })) {
+        st.filter(br.lo, 0, list, cap, &L.list_fill);
+        __syncthreads();
+        listed = L.list_fill;
+        done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
+      }
+    }
+    if (done) {
+      write_listed<NT>(list, listed, n, k, sel, before, scan_scratch, map ? map + row * row_len : nullptr, out_idx, out_val);
+      return;
+    }
   }
 
-  if (!done) {
-  if (!(CAND && k >= n)) {
+  // ---- two-pass path
+  for (int i = tid; i < nwords; i += NT) sel[i] = 0;
+  if (tid == 0) { list_len = 0; L.few_len = 0; }
+  zero_hist_n<NT>(hist);
+  if (k < n || map || all_slots) {   // otherwise every element is selected
     // ---- pass 1: histogram of the top 11 bits
-    scan_row(s, 0, n, [&](int, float v, bool in) {
+    scan_row<NT>(s, 0, n, [&](int, float v, bool in) {
       if (in) atomicAdd(&hist[order_key(v) >> 21], 1);
     });
     __syncthreads();
@@ -343,29 +583,29 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
     selectable = n - (hist[0] + hist[1] + hist[2] + hist[3]);
   }
   const int k_eff = min(k, selectable);
-  for (int i = k_eff + tid; i < k; i += kTopkThreads) {
+  for (int i = k_eff + tid; i < k; i += NT) {
     out_idx[i] = -1;
     if (out_val) out_val[i] = -INFINITY;
   }
   if (k_eff == 0) return;
 
   if (k_eff == n) {
-    for (int i = tid; i < nwords; i += kTopkThreads) {
+    for (int i = tid; i < nwords; i += NT) {
       const int rem = n - i * 32;
       sel[i] = rem >= 32 ? 0xFFFFFFFFu : ((1u << rem) - 1u);
     }
     __syncthreads();
   } else {
-    find_threshold_bin(hist, k_eff, scan_scratch, thr);
+    find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr);
     const uint32_t d1 = thr[0];
     int need = thr[1];
-    const bool listed = thr[2] <= kCap;
+    const bool listed = thr[2] <= list_cap;
     __syncthreads();
-    zero_hist(hist);
+    zero_hist_n<NT>(hist);
 
     if (listed) {
       // ---- pass 2: mark digit1 > d1, compact digit1 == d1 into the LDS list
-      scan_row(s, 0, n, [&](int i, float v, bool in) {
+      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v), a = key >> 21;
         if (in && a > d1) atomicOr(&sel[i >> 5], 1u << (i & 31));
         const int b = wave_append(in && a == d1, &list_len);
@@ -374,75 +614,75 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       __syncthreads();
       const int len = list_len;
       // ---- digits 2 and 3 on the list
-      for (int i = tid; i < len; i += kTopkThreads) atomicAdd(&hist[(lkey[i] >> 10) & 0x7FF], 1);
+      for (int i = tid; i < len; i += NT) atomicAdd(&hist[(lkey[i] >> 10) & 0x7FF], 1);
       __syncthreads();
-      find_threshold_bin(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
       const uint32_t p22 = (d1 << 11) | (uint32_t)thr[0];
       need = thr[1];
       const int nb = thr[2];
       if (nb <= kFew) {
         // ---- few list entries share the second threshold digit (the usual case): they are
         //      ranked against each other by score, then index, instead of a third digit pass
-        for (int i = tid; i < len; i += kTopkThreads) {
+        for (int i = tid; i < len; i += NT) {
           const uint32_t key = lkey[i], kp = key >> 10;
           if (kp > p22) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
-          const int b = wave_append(kp == p22, &few_len);
-          if (b >= 0) { fkey[b] = key; fidx[b] = lidx[i]; }
+          const int b = wave_append(kp == p22, &L.few_len);
+          if (b >= 0) { L.fkey[b] = key; L.fidx[b] = lidx[i]; }
         }
         __syncthreads();
         if (tid < nb) {
-          const uint32_t key = fkey[tid];
-          const int e = fidx[tid];
+          const uint32_t key = L.fkey[tid];
+          const int e = L.fidx[tid];
           int rank = 0;
           for (int j = 0; j < nb; ++j) {
-            const uint32_t kj = fkey[j];
-            rank += (kj > key || (kj == key && fidx[j] < e)) ? 1 : 0;
+            const uint32_t kj = L.fkey[j];
+            rank += (kj > key || (kj == key && L.fidx[j] < e)) ? 1 : 0;
           }
           if (rank < need) atomicOr(&sel[e >> 5], 1u << (e & 31));
         }
       } else {
       __syncthreads();
-      zero_hist(hist);
-      for (int i = tid; i < len; i += kTopkThreads) {
+      zero_hist_n<NT>(hist);
+      for (int i = tid; i < len; i += NT) {
         const uint32_t key = lkey[i], kp = key >> 10;
         if (kp > p22) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
         else if (kp == p22) atomicAdd(&hist[key & 0x3FF], 1);
       }
       __syncthreads();
-      find_threshold_bin(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
       const uint32_t tkey = (p22 << 10) | (uint32_t)thr[0];
       need = thr[1];
       const int ties = thr[2];
       __syncthreads();
-      zero_hist(hist);
+      zero_hist_n<NT>(hist);
       if (ties == need) {
-        for (int i = tid; i < len; i += kTopkThreads)
+        for (int i = tid; i < len; i += NT)
           if (lkey[i] >= tkey) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
       } else {
         // More ties than places: take the `need` lowest indices among them, by the
         // same digit search on (high, low) halves of the index, inverted so that a
         // lower index ranks higher.  Indices are distinct, so this is exact.
-        for (int i = tid; i < len; i += kTopkThreads) {
+        for (int i = tid; i < len; i += NT) {
           const uint32_t key = lkey[i];
           if (key > tkey) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
           else if (key == tkey) atomicAdd(&hist[kBins - 1 - (lidx[i] >> 10)], 1);
         }
         __syncthreads();
-        find_threshold_bin(hist, need, scan_scratch, thr);
+        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
         const int hi_digit = kBins - 1 - thr[0];
         need = thr[1];
         __syncthreads();
-        zero_hist(hist);
-        for (int i = tid; i < len; i += kTopkThreads) {
+        zero_hist_n<NT>(hist);
+        for (int i = tid; i < len; i += NT) {
           if (lkey[i] != tkey) continue;
           const int e = lidx[i];
           if ((e >> 10) < hi_digit) atomicOr(&sel[e >> 5], 1u << (e & 31));
           else if ((e >> 10) == hi_digit) atomicAdd(&hist[kBins - 1 - (e & 0x3FF)], 1);
         }
         __syncthreads();
-        find_threshold_bin(hist, need, scan_scratch, thr);
+        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
         const int lo_digit = kBins - 1 - thr[0];
-        for (int i = tid; i < len; i += kTopkThreads) {
+        for (int i = tid; i < len; i += NT) {
           if (lkey[i] != tkey) continue;
           const int e = lidx[i];
           if ((e >> 10) == hi_digit && (e & 0x3FF) <= lo_digit) atomicOr(&sel[e >> 5], 1u << (e & 31));
@@ -452,22 +692,22 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       __syncthreads();
     } else {
       // ---- fallback: two more digit passes over the row, ties through a bitmap
-      for (int i = tid; i < nwords; i += kTopkThreads) eq[i] = 0;
+      for (int i = tid; i < nwords; i += NT) eq[i] = 0;
       __syncthreads();
-      scan_row(s, 0, n, [&](int i, float v, bool in) {
+      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v), a = key >> 21;
         if (!in) return;
         if (a > d1) atomicOr(&sel[i >> 5], 1u << (i & 31));
         else if (a == d1) atomicAdd(&hist[(key >> 10) & 0x7FF], 1);
       });
       __syncthreads();
-      find_threshold_bin(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
       const uint32_t d2 = thr[0];
       need = thr[1];
       __syncthreads();
-      zero_hist(hist);
+      zero_hist_n<NT>(hist);
       const uint32_t pre22 = (d1 << 11) | d2;
-      scan_row(s, 0, n, [&](int i, float v, bool in) {
+      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v);
         if (!in || (key >> 21) != d1) return;
         const uint32_t b = (key >> 10) & 0x7FF;
@@ -475,11 +715,11 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         else if (b == d2) atomicAdd(&hist[key & 0x3FF], 1);
       });
       __syncthreads();
-      find_threshold_bin(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
       const uint32_t tkey = (pre22 << 10) | (uint32_t)thr[0];
       need = thr[1];  // how many elements equal to the threshold value are taken
       __syncthreads();
-      scan_row(s, 0, n, [&](int i, float v, bool in) {
+      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v);
         if (!in || (key >> 10) != pre22) return;
         if (key > tkey) atomicOr(&sel[i >> 5], 1u << (i & 31));
@@ -487,7 +727,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       });
       __syncthreads();
       // take the `need` lowest-index elements among the ties
-      const int wpt = (nwords + kTopkThreads - 1) / kTopkThreads;
+      const int wpt = (nwords + NT - 1) / NT;
       const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
       int cnt = 0;
       for (int w = w_lo; w < w_hi; ++w) cnt += __popc(eq[w]);
@@ -510,10 +750,8 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
     }
   }
 
-  }  // !done
-
   // ---- expand the bitmap in index order
-  const int wpt = (nwords + kTopkThreads - 1) / kTopkThreads;
+  const int wpt = (nwords + NT - 1) / NT;
   const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
   int cnt = 0;
   for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
@@ -533,82 +771,116 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
   }
 }
 
-template <bool CAND>
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(Prob p, const float* __restrict__ S,
-                                                            int row_len, int k,
-                                                            const int* __restrict__ map,
-                                                            int* __restrict__ idx,
-                                                            float* __restrict__ val,
-                                                            const int* __restrict__ pre, int rlen,
-                                                            bool all_slots) {
+// Registers: 1024 threads leave room for two workgroups per CU, the smaller ones for 24 wavefronts.
+template <int NT, int KIND>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kTopkThreads ? 8 : 6, 8))) void topk_kernel(
+    Prob p, const float* __restrict__ S, int row_len, int k, const int* __restrict__ map,
+    int* __restrict__ idx, float* __restrict__ val, const int* __restrict__ pre, int cap, int list_cap, bool all_slots) {
   extern __shared__ uint32_t dyn[];
   // queries in descending order: under a causal mask the late ones have the longest rows, and
   // the workgroups with the most work should start first
-  topk_row<CAND>(p, S, row_len, k, map, idx, val, pre, rlen, gridDim.x - 1 - blockIdx.x, blockIdx.y, dyn, all_slots);
+  topk_row<NT, KIND>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, gridDim.x - 1 - blockIdx.x, blockIdx.y,
+                     dyn, all_slots);
 }
 
 // Only the rows r with only[r] != 0 (rows another path could not finish).  Normally
 // there is none, so a small grid strides over the rows.
 __global__ __launch_bounds__(kTopkThreads) void topk_only_kernel(Prob p, const float* __restrict__ S,
                                                                  int k, int* __restrict__ idx,
-                                                                 float* __restrict__ val,
-                                                                 const int* __restrict__ only) {
+                                                                 float* __restrict__ val, int cap,
+                                                                 int list_cap, const int* __restrict__ only) {
   extern __shared__ uint32_t dyn[];
   const int rows = p.n_seq * p.n_q;
   for (int r = blockIdx.x; r < rows; r += gridDim.x) {
     if (!only[r]) continue;
-    topk_row<false>(p, S, p.L, k, nullptr, idx, val, nullptr, 0, r % p.n_q, r / p.n_q, dyn);
+    topk_row<kTopkThreads, kRowLong>(p, S, p.L, k, nullptr, idx, val, nullptr, cap, list_cap, r % p.n_q, r / p.n_q, dyn);
     __syncthreads();
   }
 }
 
-// Rows are split over several workgroups when there are too few of them to fill the chip.
+// Rows are cut into ranges where there are fewer rows than CUs and the rows are long.
 static bool use_split(const Prob& p) {
-  return (long long)p.n_seq * p.n_q < 256 && p.L >= 4 * kMinRange;
+  return (long long)p.n_seq * p.n_q < 256 && p.L > 65536;
 }
 
 size_t topk_ws_bytes(const Prob& p, int k) {
   if (!use_split(p) || k < 1) return 0;
   const int rlen = range_len(p.L);
-  const size_t ranges = (size_t)(p.L + rlen - 1) / rlen;
-  return (size_t)p.n_seq * p.n_q * ranges * kSegInts * sizeof(int);
+  return (size_t)p.n_seq * p.n_q * ((p.L + rlen - 1) / rlen) * kSegInts * sizeof(int);
 }
 
-template <int WHICH>  // 0: topk_kernel<false>, 1: topk_kernel<true>, 2: topk_only_kernel
-static hipError_t set_lds_limit(size_t lds) {
-  static LdsSeen seen;
-  const void* f = WHICH == 0 ? reinterpret_cast<const void*>(topk_kernel<false>)
-                : WHICH == 1 ? reinterpret_cast<const void*>(topk_kernel<true>)
-                             : reinterpret_cast<const void*>(topk_only_kernel);
-  return ensure_dynamic_lds(f, lds, seen);
+// List entries of a row.  With one line of every ls sampled, about r_lo ls elements of the row reach the
+// lower threshold of topk_sampled (r_lo = k / ls + 6 sqrt(k / ls) + 8) and the number scatters by
+// ls sqrt(r_lo): six of those are added.  A short row lists little more than k.
+static int pass_capacity(int row_len, int k, int nt, bool is_short) {
+  const int lines = (row_len + 15) / 16, max_lines = is_short ? lines : sample_lines(row_len, k, nt);
+  const double ls = (lines + max_lines - 1) / max_lines, kf = k / ls;
+  const double r = kf + 6.0 * std::sqrt(kf) + 8.0;
+  return std::min((int)(ls * (r + (ls > 1 ? 6.0 * std::sqrt(r) : 56.0))), row_len);
 }
 
 hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const int* map, int* idx,
                        float* val, void* ws, hipStream_t st, const int* only, bool all_slots) {
-  const size_t nwords = (size_t)(row_len + 31) / 32;
-  const size_t second = nwords * 4 > (size_t)kCap * 8 ? nwords * 4 : (size_t)kCap * 8;
-  const size_t lds = nwords * 4 + second;
+  // Short rows: as many threads as hold the row; few rows of up to 4096 take 512 threads (7.3 us for one
+  // row against 9.3 us with 256).  Long rows: 1024 threads where there are few rows or the lists are
+  // long (a CU then holds one or two rows); many rows with short lists take 512, of which a CU holds
+  // three at different phases, so that memory is never idle (4096 x 65536: 212 us against 244 us).
+  constexpr size_t kLdsMost = 156 * 1024;
+  const bool is_short = !only && row_len <= 8192;
+  const bool split = !map && !all_slots && !only && use_split(p);
+  size_t lds = 0;
+  int cap = 0;
+  auto fits = [&](int nt, size_t most) {
+    cap = pass_capacity(row_len, k, nt, is_short);
+    lds = (size_t)sel_words(row_len) * 4 + (size_t)(cap + 64) * 8 + (size_t)((row_len + 31) / 32) * 2;
+    return lds <= most;
+  };
+  const bool few_rows = (long long)p.n_q * p.n_seq < 256;
+  int nt = row_len > 4096 ? kTopkThreads : few_rows ? 512 : 256;
+  if (is_short) fits(nt, kLdsMost);
+  else if (split || only || (long long)p.n_q * p.n_seq < 512 || !fits(nt = 512, 53 * 1024)) {
+    nt = kTopkThreads;
+    if (!fits(nt, kLdsMost)) cap = 0;              // (k well above 8192: the two-pass path)
+  }
+  // the two-pass path shares the region: histogram and list, or a second bitmap
+  const int list_cap = std::min(row_len, is_short || nt == 512 ? std::max((int)(lds / 8) - sel_words(row_len) / 2 - kBins / 2, 1) : kListTarget);
+  const size_t words = (size_t)sel_words(row_len);
+  lds = std::max(cap ? lds : 0, words * 4 + kBins * 4 + std::max((size_t)list_cap * 8, (size_t)((row_len + 31) / 32) * 4));
   const dim3 grid(p.n_q, p.n_seq);
+  hipError_t e;
+  int* pre = split && cap ? static_cast<int*>(ws) : nullptr;
+#define GO(NT, KIND)                                                                               \
+  do {                                                                                             \
+    static LdsSeen seen;                                                                           \
+    e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_kernel<NT, KIND>), lds, seen);       \
+    if (e != hipSuccess) return e;   /* before the first launch: a failure leaves nothing enqueued */ \
+    if (KIND == kRowListed) {                                                                      \
+      const int rlen = range_len(p.L);                                                             \
+      const dim3 ranges((p.L + rlen - 1) / rlen, p.n_q, p.n_seq);                                  \
+      topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, pre);                  \
+    }                                                                                              \
+    topk_kernel<NT, KIND><<<grid, NT, lds, st>>>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, all_slots); \
+  } while (0)
   if (only) {
-    hipError_t e = set_lds_limit<2>(lds);
+    static LdsSeen seen;
+    e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_only_kernel), lds, seen);
     if (e != hipSuccess) return e;
     const int rows = p.n_seq * p.n_q;
-    topk_only_kernel<<<rows < 256 ? rows : 256, kTopkThreads, lds, st>>>(p, S, k, idx, val, only);
-    return hipGetLastError();
+    topk_only_kernel<<<rows < 256 ? rows : 256, kTopkThreads, lds, st>>>(p, S, k, idx, val, cap, list_cap, only);
+  } else if (is_short && nt == 256) {
+    GO(256, kRowShort);
+  } else if (is_short && nt == 512) {
+    GO(512, kRowShort);
+  } else if (is_short) {
+    GO(kTopkThreads, kRowShort);
+  } else if (nt == 512) {
+    GO(512, kRowLong);
+  } else if (pre) {
+    GO(kTopkThreads, kRowListed);
+  } else {
+    GO(kTopkThreads, kRowLong);
   }
-  if (!map && !all_slots && use_split(p)) {
-    int* pre = static_cast<int*>(ws);
-    const int rlen = range_len(p.L);
-    const dim3 g2((p.L + rlen - 1) / rlen, p.n_q, p.n_seq);
-    hipError_t e = set_lds_limit<1>(lds);   // before the first launch: a failure leaves nothing enqueued
-    if (e != hipSuccess) return e;
-    topk_prefilter_kernel<<<g2, kTopkThreads, 0, st>>>(p, S, k, rlen, pre);
-    topk_kernel<true><<<grid, kTopkThreads, lds, st>>>(p, S, row_len, k, map, idx, val, pre, rlen, false);
-    return hipGetLastError();
-  }
-  hipError_t e = set_lds_limit<0>(lds);
-  if (e != hipSuccess) return e;
-  topk_kernel<false><<<grid, kTopkThreads, lds, st>>>(p, S, row_len, k, map, idx, val, nullptr, 0, all_slots);
+#undef GO
   return hipGetLastError();
 }
 
