@@ -937,7 +937,49 @@ __global__ __launch_bounds__(256) void score_tile_repair_kernel(
 // all k' <= 8192 candidates, the scores replace the candidate indices in LDS as they are
 // produced (a slot's index has been consumed by then) and the row's top-k is taken from there by
 // small_row_topk - no dense score matrix, no second launch.
+//
+// Loads: a load instruction costs the cache lines that its quads of lanes touch.  With bf16 keys, and with
+// fp8 keys that need no widening, the four lanes of a quad read 64 contiguous bytes of one row (row i of
+// the quad's four with load i) and the 16-byte pieces are exchanged inside the quad (quad_transpose),
+// which leaves every lane with its own candidate's bytes: 245 us against 282 us for 1024 x 8192 bf16
+// candidates, 313 us against 335 us for 2 x 1024 x 8192 fp8 ones with their top-k.  Where the codes are
+// widened the vector instructions are the bound, the 32 of the exchange cost more than the lines they
+// save (427 us against 390 us for 2048 x 8192), and a lane reads its half row by itself.
 constexpr int kGatherChunk = 4096;
+
+// The 4 x 4 transpose of 16-byte pieces over the four lanes of a quad: piece r of lane j becomes piece j of
+// lane r.  Two stages of selects between a lane's own and a neighbour's register; 32 vector instructions.
+__device__ __forceinline__ void quad_transpose_2(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3,
+                                                 uint32_t& b0, uint32_t& b1, uint32_t& b2, uint32_t& b3) {
+  uint32_t s0, s1, s2, s3, t0, t1, t2, t3;
+  // (two wait states between a vector write and its quad-permuted read, and before a matrix read: the
+  // operands may come from vector instructions, inside the block the order keeps them apart)
+#define MISA_X1 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+#define MISA_X2 " quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
+  asm("s_mov_b32 vcc_lo, 0x55555555\n\ts_mov_b32 vcc_hi, 0x55555555\n\t"    // even lanes keep their own
+      "v_cndmask_b32_dpp %8, %1, %0, vcc" MISA_X1 "v_cndmask_b32_dpp %10, %3, %2, vcc" MISA_X1
+      "v_cndmask_b32_dpp %12, %5, %4, vcc" MISA_X1 "v_cndmask_b32_dpp %14, %7, %6, vcc" MISA_X1
+      "s_mov_b32 vcc_lo, 0xaaaaaaaa\n\ts_mov_b32 vcc_hi, 0xaaaaaaaa\n\t"    // odd lanes
+      "v_cndmask_b32_dpp %9, %0, %1, vcc" MISA_X1 "v_cndmask_b32_dpp %11, %2, %3, vcc" MISA_X1
+      "v_cndmask_b32_dpp %13, %4, %5, vcc" MISA_X1 "v_cndmask_b32_dpp %15, %6, %7, vcc" MISA_X1
+      "s_mov_b32 vcc_lo, 0x33333333\n\ts_mov_b32 vcc_hi, 0x33333333\n\t"    // lanes 0, 1 of a quad
+      "v_cndmask_b32_dpp %0, %10, %8, vcc" MISA_X2 "v_cndmask_b32_dpp %4, %14, %12, vcc" MISA_X2
+      "v_cndmask_b32_dpp %1, %11, %9, vcc" MISA_X2 "v_cndmask_b32_dpp %5, %15, %13, vcc" MISA_X2
+      "s_mov_b32 vcc_lo, 0xcccccccc\n\ts_mov_b32 vcc_hi, 0xcccccccc\n\t"    // lanes 2, 3
+      "v_cndmask_b32_dpp %2, %8, %10, vcc" MISA_X2 "v_cndmask_b32_dpp %6, %12, %14, vcc" MISA_X2
+      "v_cndmask_b32_dpp %3, %9, %11, vcc" MISA_X2 "v_cndmask_b32_dpp %7, %13, %15, vcc" MISA_X2
+      "s_nop 1"
+      : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1), "+v"(b2), "+v"(b3),
+        "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
+      :
+      : "vcc");
+#undef MISA_X1
+#undef MISA_X2
+}
+__device__ __forceinline__ void quad_transpose(uint4& v0, uint4& v1, uint4& v2, uint4& v3) {
+  quad_transpose_2(v0.x, v1.x, v2.x, v3.x, v0.y, v1.y, v2.y, v3.y);
+  quad_transpose_2(v0.z, v1.z, v2.z, v3.z, v0.w, v1.w, v2.w, v3.w);
+}
 
 template <int KDT, int RT, bool Q8, bool FUSED>
 __global__ __launch_bounds__(256) void score_gather_kernel(
@@ -947,6 +989,7 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
     float* __restrict__ val) {
   constexpr int ROW_BYTES = KDT == MISA_BF16 ? 256 : 128;
   constexpr int NLD = KDT == MISA_BF16 ? 8 : 4;  // 16-byte loads per lane and key (half a row)
+  constexpr bool QUAD = Q8 || KDT == MISA_BF16;  // a quad of lanes reads 64 bytes of one row
   const int t = blockIdx.y, seq = blockIdx.z;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 31, hf = lane >> 5;
@@ -959,7 +1002,7 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
 
   // The candidate indices of this workgroup go through LDS, so that reading them
   // in the loop does not wait on the key loads in flight.
-  __shared__ int s_cand[FUSED ? kSmallTopkMax : kGatherChunk];
+  __shared__ __align__(16) int s_cand[FUSED ? kSmallTopkMax : kGatherChunk];
   for (int i = threadIdx.x; i < chunk; i += 256) s_cand[i] = c_begin + i < c_end ? crow[c_begin + i] : -1;
 
   // Row m of tile rt is head rt*32 + m; half-wave hf holds components 64 hf .. 64 hf + 63,
@@ -998,23 +1041,46 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
   }
 
   // Loads are unconditional and branch-free (slot and row clamped), so the number
-  // of loads in flight is the same on every path and waits stay exact.
+  // of loads in flight is the same on every path and waits stay exact.  QUAD: load i (of every four) of a
+  // lane reads, of the row of candidate i of its quad, the lane's own piece of the half row (64 bytes;
+  // bf16 keys: two such pieces).  Q8: pieces 0, 1 and 4, 5 from 2 hf on, the fp8 instruction's operand.
   struct Raw { uint4 v[NLD]; float scale; int s; };
+  const int piece = !QUAD ? hf * (ROW_BYTES / 32) : Q8 ? 4 * ((lane & 3) >> 1) + 2 * hf + (lane & 1)
+                                                       : hf * (ROW_BYTES / 32) + (lane & 3);
+  const uint32_t piece_off = (uint32_t)piece * 16u;
+  const char* kseq = static_cast<const char*>(K) + (p.page_table ? 0 : (size_t)seq * p.L * ROW_BYTES);
   auto issue = [&](Raw& r, int c0) {
-    const int slot = c0 + col;
-    int s = s_cand[min(slot - c_begin, chunk - 1)];
-    if (slot >= c_end || s >= n) s = -1;
+    const int base = min(c0 - c_begin, chunk - 32);      // (past the end: any slots, nothing of them is kept)
+    int s = s_cand[base + col];
+    if (c0 + col >= c_end || s >= n) s = -1;
     r.s = s;
-    const int row = max(s, 0);
-    const size_t kslot = key_slot(p, seq, row);
-    const uint4* src = reinterpret_cast<const uint4*>(static_cast<const char*>(K) + kslot * ROW_BYTES + hf * (Q8 ? 32 : ROW_BYTES / 2));
+    const size_t own = key_slot(p, seq, max(s, 0));
+    if constexpr (QUAD) {
+      const int4 four = *reinterpret_cast<const int4*>(&s_cand[base + (col & ~3)]);
+      auto visible_row = [&](int s) { return s >= 0 && s < n ? s : 0; };
+      const int rows[4] = {visible_row(four.x), visible_row(four.y), visible_row(four.z), visible_row(four.w)};
+      const char* src[4];
+      if (p.page_table) {
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) r.v[i] = src[Q8 ? 4 * (i >> 1) + (i & 1) : i];   // Q8: chunks 0, 1 and 4, 5 from 32 hf
+        for (int i = 0; i < 4; ++i) src[i] = kseq + key_slot<true>(p, seq, rows[i]) * ROW_BYTES + piece_off;
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) src[i] = kseq + ((uint32_t)rows[i] * (uint32_t)ROW_BYTES + piece_off);
+      }
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) r.v[i] = *reinterpret_cast<const uint4*>(src[i & 3] + (i >> 2) * 64);
+    } else {
+      const uint4* src = reinterpret_cast<const uint4*>(static_cast<const char*>(K) + own * ROW_BYTES + piece_off);
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) r.v[i] = src[i];
+    }
     r.scale = 1.f;
-    if (KDT == MISA_FP8_E4M3) r.scale = kscale[kslot];
+    if (KDT == MISA_FP8_E4M3) r.scale = kscale[own];
   };
-  auto finish = [&](const Raw& r, int c0) {
+  auto finish = [&](Raw& r, int c0) {
     if (c0 >= c_end) return;
+#pragma unroll
+    for (int i = 0; i < (QUAD ? NLD : 0); i += 4) quad_transpose(r.v[i], r.v[i + 1], r.v[i + 2], r.v[i + 3]);
     f32x16 acc[RT];
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt)
@@ -1046,11 +1112,17 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
           acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt][ks].v, b.v, acc[rt], 0, 0, 0);
       }
     }
-    float sum = 0.f;
+    // (bf16 keys: sums of eight heads, then those: as exact as 16-row head tiles would give)
+    constexpr int PER = KDT == MISA_BF16 ? 8 : RT * 16;
+    float part[RT * 16 / PER];
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
+    for (int i = 0; i < RT * 16; ++i) {
+      if (i % PER == 0) part[i / PER] = 0.f;
+      part[i / PER] = fmaf(s_gate[hf][i], relu(acc[i / 16][i % 16]), part[i / PER]);
+    }
+    float sum = part[0];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) sum = fmaf(s_gate[hf][rt * 16 + q], relu(acc[rt][q]), sum);
+    for (int i = 1; i < RT * 16 / PER; ++i) sum += part[i];
     sum += __shfl_xor(sum, 32);
     const int slot = c0 + col;
     if (hf == 0 && slot < c_end) {
@@ -1079,153 +1151,6 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
         c0 += 128;
         if (c0 >= c_end) return;
       }
-    }
-  };
-  stream_candidates();
-  if constexpr (FUSED) {
-    __shared__ SmallTopkLds topk_lds;
-    __syncthreads();                // all scores of the row are in LDS
-    small_row_topk(s_cand, k_cand, k, crow, idx + qrow * k, val ? val + qrow * k : nullptr, topk_lds);
-  }
-}
-
-// score_cand_kernel (bf16 queries, bf16 or fp8 keys, candidate lists): the same re-scoring with
-// the operand layout of the decode kernel.  A wavefront takes 64 candidates per step as four
-// 16-key tiles on v_mfma_f32_16x16x32_bf16; the four lanes that share a key column read 64
-// contiguous bytes of its row per load instruction, so an instruction touches 16 cache lines
-// instead of the 32 of one-lane-per-half-row (the gather is bound by the number of lines its
-// load instructions touch, not by bytes).  All H head rows are the stationary operand (NT 16-row
-// tiles); the head sum is in-lane over the accumulator registers plus the two exchanges that
-// leave lane i with candidate i of the group.  Chunks, the two-buffer pipeline and the FUSED
-// tail are those of score_gather_kernel.  Used for bf16 keys (256-byte rows: 0.54 ms against
-// 0.59 ms for the re-rank of 2048 x 8192 candidates); with fp8 keys the 32-row-tile kernel, whose
-// half rows are 64 contiguous bytes as well, is 2-6 % faster (three wavefronts per SIMD instead
-// of two) and stays in use.
-template <int KDT, int NT, bool FUSED>
-__global__ __launch_bounds__(256) void score_cand_kernel(
-    Prob p, const uint16_t* __restrict__ Q, const float* __restrict__ W,
-    const void* __restrict__ K, const float* __restrict__ kscale, const int* __restrict__ cand,
-    int k_cand, int chunk, float* __restrict__ out, int k, int* __restrict__ idx,
-    float* __restrict__ val) {
-  constexpr int ROW_BYTES = KDT == MISA_BF16 ? 256 : 128;
-  constexpr int NLD = KDT == MISA_BF16 ? 4 : 2;  // 16-byte loads per lane and 16-key tile
-  const int t = blockIdx.y, seq = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c = lane & 15, g = lane >> 4;
-  const int n = visible(p, seq, t);
-  const size_t qrow = (size_t)seq * p.n_q + t;
-  const int c_begin = blockIdx.x * chunk;            // chunk: a multiple of 256
-  const int c_end = min(c_begin + chunk, k_cand);
-  const int* crow = cand + qrow * k_cand;
-  float* orow = out + qrow * k_cand;
-
-  __shared__ int s_cand[FUSED ? kSmallTopkMax : kGatherChunk];
-  for (int i = threadIdx.x; i < chunk; i += 256) s_cand[i] = c_begin + i < c_end ? crow[c_begin + i] : -1;
-
-  // Head rows and gates; component mapping of the k-steps as in score_stream_kernel.
-  Frag a[NT][4];
-  float wv[NT][4];
-#pragma unroll
-  for (int T = 0; T < NT; ++T) {
-    const int head = T * 16 + c;
-    const uint16_t* src = Q + (qrow * p.H + min(head, p.H - 1)) * kD;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int comp = KDT == MISA_BF16 ? 8 * (4 * i + g) : 16 * (4 * (i >> 1) + g) + 8 * (i & 1);
-      const uint4 v = *reinterpret_cast<const uint4*>(src + comp);
-      a[T][i].u = head < p.H ? v : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int hd = T * 16 + 4 * g + j;   // the accumulator of lane (c, g) holds head rows 4 g + j
-      wv[T][j] = hd < p.H ? W[qrow * p.H + min(hd, p.H - 1)] : 0.f;
-    }
-  }
-
-  struct Raw { uint4 v[4][NLD]; float scale; int s; };
-  // candidate of list slot `slot` (-1: none, hole, or not visible to the query)
-  auto candidate = [&](int slot) {
-    int s = s_cand[min(slot - c_begin, chunk - 1)];
-    if (slot >= c_end || s >= n) s = -1;
-    return s;
-  };
-  // Loads are unconditional and branch-free (absent candidates read key 0), so the number of
-  // loads in flight is the same on every path and waits stay exact.
-  auto issue = [&](Raw& r, int c0) {
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt) {
-      const size_t kslot = key_slot(p, seq, max(candidate(c0 + tt * 16 + c), 0));
-      const uint4* src = reinterpret_cast<const uint4*>(static_cast<const char*>(K) + kslot * ROW_BYTES) + g;
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) r.v[tt][i] = src[4 * i];
-    }
-    r.s = candidate(c0 + lane);            // the candidate this lane finally owns
-    r.scale = 1.f;
-    if (KDT == MISA_FP8_E4M3) r.scale = kscale[key_slot(p, seq, max(r.s, 0))];
-  };
-  auto finish = [&](const Raw& r, int c0) {
-    if (c0 >= c_end) return;
-    float part[4];
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt) {
-      Frag b[4];
-      if (KDT == MISA_BF16) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) b[i].u = r.v[tt][i % NLD];
-      } else {
-        const uint4 lo = r.v[tt][0], hi = r.v[tt][NLD - 1];
-        const uint32_t w8[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          fp8x4_to_bf16x4(w8[2 * i], b[i].w[0], b[i].w[1]);
-          fp8x4_to_bf16x4(w8[2 * i + 1], b[i].w[2], b[i].w[3]);
-        }
-      }
-      float sum = 0.f;
-#pragma unroll
-      for (int T = 0; T < NT; ++T) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[T][i].v, b[i].v, acc, 0, 0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) sum = fmaf(wv[T][j], relu(acc[j]), sum);
-      }
-      part[tt] = sum;
-    }
-    // sum over the four lane groups so that group g ends with tile g: lane i owns slot c0 + i
-    const bool up2 = (g & 2) != 0, up1 = (g & 1) != 0;
-    const float r0 = __shfl_xor(up2 ? part[0] : part[2], 32);
-    const float r1 = __shfl_xor(up2 ? part[1] : part[3], 32);
-    const float k0 = (up2 ? part[2] : part[0]) + r0;
-    const float k1 = (up2 ? part[3] : part[1]) + r1;
-    const float r2 = __shfl_xor(up1 ? k0 : k1, 16);
-    const float fin = (up1 ? k1 : k0) + r2;
-    const int slot = c0 + lane;
-    if (slot < c_end) {
-      const float score = r.s >= 0 ? fin * r.scale : -INFINITY;
-      if (FUSED) s_cand[slot] = __float_as_int(score);   // (c_begin = 0; this slot's index was read at issue)
-      else orow[slot] = score;
-    }
-  };
-
-  __builtin_amdgcn_s_waitcnt(0);  // the query operand has landed; in-loop waits concern only loop loads
-  __syncthreads();                // candidate indices are in LDS
-  auto stream_candidates = [&]() {
-    Raw buf[2];
-    int c0 = c_begin + wave * 64;
-    issue(buf[0], c0);
-    while (true) {
-      issue(buf[1], c0 + 256);
-      __builtin_amdgcn_sched_barrier(0);
-      finish(buf[0], c0);
-      c0 += 256;
-      if (c0 >= c_end) return;
-      issue(buf[0], c0 + 256);
-      __builtin_amdgcn_sched_barrier(0);
-      finish(buf[1], c0);
-      c0 += 256;
-      if (c0 >= c_end) return;
     }
   };
   stream_candidates();
@@ -1387,16 +1312,7 @@ static hipError_t launch_gather(const Prob& p, const void* Q, const float* W, co
   while (chunk > 512 && rows * ((k_cand + chunk - 1) / chunk) < 1024) chunk /= 2;
   const dim3 grid((k_cand + chunk - 1) / chunk, p.n_q, p.n_seq);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
-  if constexpr (KDT == MISA_BF16) {   // 256-byte rows: 16-row head tiles, four lanes per key row (see score_cand_kernel)
-#define GO(NT) score_cand_kernel<KDT, NT, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr)
-    switch ((p.H + 15) / 16) {
-      case 1: GO(1); break;
-      case 2: GO(2); break;
-      case 3: GO(3); break;
-      default: GO(4); break;
-    }
-#undef GO
-  } else if (p.H <= 32) {
+  if (p.H <= 32) {
     score_gather_kernel<KDT, 1, Q8, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr);
   } else {
     score_gather_kernel<KDT, 2, Q8, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr);
@@ -1420,16 +1336,7 @@ static hipError_t launch_gather_topk(const Prob& p, const void* Q, const float* 
   const int chunk = (k_cand + 255) / 256 * 256;
   const dim3 grid(1, p.n_q, p.n_seq);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
-  if constexpr (KDT == MISA_BF16) {
-#define GO(NT) score_cand_kernel<KDT, NT, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val)
-    switch ((p.H + 15) / 16) {
-      case 1: GO(1); break;
-      case 2: GO(2); break;
-      case 3: GO(3); break;
-      default: GO(4); break;
-    }
-#undef GO
-  } else if (p.H <= 32) {
+  if (p.H <= 32) {
     score_gather_kernel<KDT, 1, Q8, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val);
   } else {
     score_gather_kernel<KDT, 2, Q8, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val);
