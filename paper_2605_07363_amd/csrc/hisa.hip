@@ -3,13 +3,15 @@
 // selector (Experimental results, "Baselines").
 //
 //   block scores  J[t,b] = sum over ALL heads of w_j ReLU(q_j . k~_b) for the complete
-//                 blocks inside the query's visible prefix (block_score_kernel, fp32
-//                 FMA on the fp32 pooled keys: these scores only rank blocks);
+//                 blocks inside the query's visible prefix (block_score_tile_kernel on the
+//                 matrix core; block_score_kernel, fp32 FMA, for fp32 queries);
 //   block choice  the first and the last block always, the best other blocks up to m in
 //                 all: both get score +inf and the row top-k kernel takes m;
 //   HISA          the tokens of those blocks are the candidate list of the dense fine
 //                 stage (the re-rank kernels of misa_rerank);
 //   Block-Sparse  the tokens of those blocks are the selection.
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace misa {
@@ -18,14 +20,13 @@ namespace misa {
 // Only complete blocks strictly inside the prefix are scored, from Kp: the first block
 // and the last one (the only one that can be partial) are always kept, so their scores
 // are never compared and are set to +inf; blocks past the prefix get -inf.
-template <int QDT>
 __global__ __launch_bounds__(256) void block_score_kernel(Prob p, const void* __restrict__ Q,
                                                           const float* __restrict__ W,
                                                           const float* __restrict__ Kp,
                                                           float* __restrict__ J) {
   __shared__ float qs[kMaxH][kD];
   __shared__ float wsm[kMaxH];
-  using QV = Vec16<QDT>;
+  using QV = Vec16<MISA_F32>;
   const int t = blockIdx.y, seq = blockIdx.z, tid = threadIdx.x;
   const int n = visible(p, seq, t);
   const int Mn = (int)(((long long)n + p.B - 1) / p.B);
@@ -72,19 +73,170 @@ __global__ __launch_bounds__(256) void block_score_kernel(Prob p, const void* __
   J[qrow * p.M + b] = out;
 }
 
+// bf16 queries.  The products run on the matrix core with the fp32 pooled keys as three bf16 pieces (the
+// nearest bf16, the nearest to the remainder, and to what remains of that: all 24 bits), so nothing of
+// a key is lost; products are exact and added in fp32.  A wavefront keeps the pieces of 32 blocks in
+// registers (96) and the head rows of the queries pass through LDS, double buffered, shared by the four
+// wavefronts of the workgroup: a step is 64 (query, head) rows, HS = 64 or 32 head slots per query.
+// Bound: 3 x 2 H 128 flop per (query, block).  1024 queries x 512 blocks x 64 heads: 33 us, 155 us with one
+// thread per block on the vector units; error of the scores against 64 bits 1.3e-7 (1.5e-7 before).
+union BFrag {
+  bf16x8 v;
+  uint4 u;
+  uint32_t w[4];
+};
+
+__device__ __forceinline__ void split_three(float x0, float x1, uint32_t& a, uint32_t& b, uint32_t& c) {
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  union P { b2 v; uint32_t u; } h, m, l;
+  f2 x = {x0, x1};
+  h.v = __builtin_convertvector(x, b2);
+  x = f2{x0 - __uint_as_float(h.u << 16), x1 - __uint_as_float(h.u & 0xFFFF0000u)};
+  m.v = __builtin_convertvector(x, b2);
+  x = f2{x[0] - __uint_as_float(m.u << 16), x[1] - __uint_as_float(m.u & 0xFFFF0000u)};
+  l.v = __builtin_convertvector(x, b2);
+  a = h.u;
+  b = m.u;
+  c = l.u;
+}
+
+template <int HS>
+__global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps, const uint16_t* __restrict__ Q,
+                                                               const float* __restrict__ W,
+                                                               const float* __restrict__ Kp,
+                                                               float* __restrict__ J) {
+  constexpr int QPS = 64 / HS;                  // queries per step
+  constexpr int SLOTS = 17;                     // 16-byte slots per row in LDS: 16 and one of padding
+  __shared__ uint4 rows[2][64 * SLOTS];
+  __shared__ float gate[2][64];
+  __shared__ int blocks_of[2][QPS];             // blocks in a query's prefix
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int col = lane & 31, hf = lane >> 5, seq = blockIdx.z;
+  const int q_first = blockIdx.y * steps * QPS;
+  const int n_steps = min(steps, (p.n_q - q_first + QPS - 1) / QPS);
+  const int b = (blockIdx.x * 4 + wave) * 32 + col;   // this lane's block
+
+  BFrag piece[3][8];
+  {
+    const float* src = Kp + ((size_t)seq * p.M + min(b, p.M - 1)) * kD + hf * 8;
+    float4 x[8][2];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      x[ks][0] = *reinterpret_cast<const float4*>(src + ks * 16);
+      x[ks][1] = *reinterpret_cast<const float4*>(src + ks * 16 + 4);
+    }
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+      const float v[8] = {x[ks][0].x, x[ks][0].y, x[ks][0].z, x[ks][0].w, x[ks][1].x, x[ks][1].y, x[ks][1].z, x[ks][1].w};
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        split_three(v[2 * j], v[2 * j + 1], piece[0][ks].w[j], piece[1][ks].w[j], piece[2][ks].w[j]);
+    }
+  }
+
+  uint4 stage[4];
+  float stage_gate = 0.f;
+  int stage_blocks = 0;
+  auto load = [&](int step) {                   // rows of a step; missing queries and heads are zeros
+    const int q0 = q_first + step * QPS;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = tid + 256 * i, row = e >> 4, q = q0 + row / HS, head = row % HS;
+      const size_t at = (((size_t)seq * p.n_q + min(q, p.n_q - 1)) * p.H + min(head, p.H - 1)) * kD + (e & 15) * 8;
+      const uint4 v = *reinterpret_cast<const uint4*>(Q + at);
+      stage[i] = q < p.n_q && head < p.H ? v : make_uint4(0, 0, 0, 0);
+    }
+    if (tid < 64) {
+      const int q = q0 + tid / HS, head = tid % HS;
+      stage_gate = q < p.n_q && head < p.H ? W[((size_t)seq * p.n_q + q) * p.H + head] : 0.f;
+    }
+    if (tid < QPS)
+      stage_blocks = q0 + tid < p.n_q ? (int)(((long long)visible(p, seq, q0 + tid) + p.B - 1) / p.B) : 0;
+  };
+  auto store = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = tid + 256 * i;
+      rows[buf][(e >> 4) * SLOTS + (e & 15)] = stage[i];
+    }
+    if (tid < 64) gate[buf][tid] = stage_gate;
+    if (tid < QPS) blocks_of[buf][tid] = stage_blocks;
+  };
+
+  load(0);
+  store(0);
+  __syncthreads();
+  for (int step = 0; step < n_steps; ++step) {
+    const int buf = step & 1;
+    load(min(step + 1, n_steps - 1));
+    f32x16 acc[2];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[rt][i] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) {
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        BFrag a;
+        a.u = rows[buf][(rt * 32 + col) * SLOTS + 2 * ks + hf];
+        // smallest pieces first
+        acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, piece[2][ks].v, acc[rt], 0, 0, 0);
+        acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, piece[1][ks].v, acc[rt], 0, 0, 0);
+        acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, piece[0][ks].v, acc[rt], 0, 0, 0);
+      }
+    }
+    float sum[2];                               // heads of row tile rt, block b
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      float part[2] = {0.f, 0.f};
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {             // accumulator registers 4 g .. + 3: rows 8 g + 4 hf .. + 3
+        const float4 w = *reinterpret_cast<const float4*>(&gate[buf][rt * 32 + 8 * g + 4 * hf]);
+        part[g & 1] = fmaf(w.x, relu(acc[rt][4 * g]), part[g & 1]);
+        part[g & 1] = fmaf(w.y, relu(acc[rt][4 * g + 1]), part[g & 1]);
+        part[g & 1] = fmaf(w.z, relu(acc[rt][4 * g + 2]), part[g & 1]);
+        part[g & 1] = fmaf(w.w, relu(acc[rt][4 * g + 3]), part[g & 1]);
+      }
+      sum[rt] = part[0] + part[1];
+      sum[rt] += __shfl_xor(sum[rt], 32);
+    }
+    // HS = 64: both row tiles are one query's, the lower half-wave stores; HS = 32: half-wave hf stores
+    // the query of row tile hf
+    const int q = q_first + step * QPS + (HS == 32 ? hf : 0);
+    const float total = HS == 64 ? sum[0] + sum[1] : hf ? sum[1] : sum[0];
+    const int Mn = blocks_of[buf][HS == 32 ? hf : 0];
+    if ((HS == 32 || hf == 0) && q < p.n_q && b < p.M)
+      J[((size_t)seq * p.n_q + q) * p.M + b] = b >= Mn ? -INFINITY : (b == 0 || b == Mn - 1) ? INFINITY : total;
+    store(buf ^ 1);
+    __syncthreads();
+  }
+}
+
 // cand[row, i * B + o] = token o of the i-th selected block, -1 if the block slot is
 // empty or the token is not visible.
+// V: slots per thread, all of one block (4: 16-byte stores, 20 us with one slot per thread for 1024 x 8192).
+template <int V>
 __global__ __launch_bounds__(256) void expand_blocks_kernel(Prob p, int m, const int* __restrict__ blocks,
                                                             int* __restrict__ cand) {
   const int t = blockIdx.y, seq = blockIdx.z;
   const size_t row = (size_t)seq * p.n_q + t;
   const int n = visible(p, seq, t);
-  const long long slot = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (slot >= (long long)m * p.B) return;
-  const int i = (int)(slot / p.B), o = (int)(slot % p.B);
+  const uint32_t slots = (uint32_t)m * (uint32_t)p.B;      // at most 16384
+  const uint32_t slot = (blockIdx.x * 256 + threadIdx.x) * V;
+  if (slot >= slots) return;
+  const uint32_t i = slot / (uint32_t)p.B, o = slot % (uint32_t)p.B;
   const int b = blocks[row * m + i];
-  const long long tok = (long long)b * p.B + o;
-  cand[row * (size_t)m * p.B + slot] = (b >= 0 && tok < n) ? (int)tok : -1;
+  int tok[V];
+#pragma unroll
+  for (int v = 0; v < V; ++v) {
+    const long long at = (long long)b * p.B + o + v;
+    tok[v] = b >= 0 && at < n ? (int)at : -1;
+  }
+  int* dst = cand + row * (size_t)slots + slot;
+  if constexpr (V == 4) *reinterpret_cast<int4*>(dst) = make_int4(tok[0], tok[1], tok[2], tok[3]);
+  else dst[0] = tok[0];
 }
 
 namespace {
@@ -112,16 +264,30 @@ hipError_t launch_hisa(const Prob& p, int k_dtype, int q_dtype, const void* Q, c
   if (k == 0) cand = idx;
 
   const dim3 g1((p.M + 255) / 256, p.n_q, p.n_seq);
-  if (q_dtype == MISA_F32) block_score_kernel<MISA_F32><<<g1, 256, 0, st>>>(p, Q, W, Kp, J);
-  else block_score_kernel<MISA_BF16><<<g1, 256, 0, st>>>(p, Q, W, Kp, J);
+  if (q_dtype == MISA_F32) block_score_kernel<<<g1, 256, 0, st>>>(p, Q, W, Kp, J);
+  else {
+    // steps per workgroup: as many as leave about two resident sets of workgroups (the pieces of a
+    // workgroup's blocks are made once), at most 16
+    const int qps = p.H > 32 ? 1 : 2, tiles = (p.M + 127) / 128, all = (p.n_q + qps - 1) / qps;
+    const int steps = (int)std::min(16ll, std::max(1ll, (long long)all * tiles * p.n_seq / 1024));
+    const dim3 g(tiles, (all + steps - 1) / steps, p.n_seq);
+    const uint16_t* q = static_cast<const uint16_t*>(Q);
+    if (qps == 1) block_score_tile_kernel<64><<<g, 256, 0, st>>>(p, steps, q, W, Kp, J);
+    else block_score_tile_kernel<32><<<g, 256, 0, st>>>(p, steps, q, W, Kp, J);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // the m best blocks of every row of J (all M slots are scanned, -inf slots never chosen)
   e = launch_topk(p, J, p.M, m, nullptr, C, nullptr, nullptr, st, nullptr, true);
   if (e != hipSuccess) return e;
-  const dim3 g3((unsigned)((kc + 255) / 256), p.n_q, p.n_seq);
-  expand_blocks_kernel<<<g3, 256, 0, st>>>(p, m, C, cand);
+  const bool by_four = p.B % 4 == 0 && (reinterpret_cast<uintptr_t>(cand) & 15) == 0;
+  const dim3 g3((unsigned)((kc + (by_four ? 1023 : 255)) / (by_four ? 1024 : 256)), p.n_q, p.n_seq);
+  if (by_four) expand_blocks_kernel<4><<<g3, 256, 0, st>>>(p, m, C, cand);
+  else expand_blocks_kernel<1><<<g3, 256, 0, st>>>(p, m, C, cand);
   if ((e = hipGetLastError()) != hipSuccess || k == 0) return e;
+  // many queries: dense scores and their top-k in one kernel, as in misa_rerank
+  if (rerank_fused_path(p, k_dtype, q_dtype, (int)kc))
+    return launch_rerank_fused(p, k_dtype, q_dtype, Q, W, K, kscale, cand, (int)kc, k, idx, val, st);
   e = launch_score(p, k_dtype, q_dtype, Q, W, nullptr, K, kscale, cand, (int)kc, dense, st);
   if (e != hipSuccess) return e;
   return launch_topk(p, dense, (int)kc, k, cand, idx, val, nullptr, st);

@@ -171,3 +171,36 @@ def test_hisa_argument_checks(misa):
             misa.hisa_select(p, dv["Q"], dv["W"], Kp, dv["K"], dv["kscale"], m, k, idx, None, None, ws)
     with pytest.raises(misa.MisaError):
         misa.hisa_select(p, dv["Q"], dv["W"], Kp, dv["K"], dv["kscale"], 4, 64, idx, None, None, None)
+
+
+@pytest.mark.parametrize("n_q,H,L,B", [(1, 64, 4100, 32), (2, 32, 4096, 31), (3, 33, 2050, 16), (17, 32, 9000, 64),
+                                       (40, 64, 16500, 128), (5, 1, 130, 1), (2100, 64, 1030, 8), (64, 8, 600, 600)])
+def test_block_scores_on_the_matrix_core(misa, n_q, H, L, B):
+    """Block scores of bf16 queries against fp64, at the edges of the query steps, head slots and block
+    tiles.  They are the first rows of the workspace.  Bound: products are exact, about 128 + H fp32
+    additions of terms whose absolute sum is A: 2^-24 * sqrt(128 + H) * A at one standard deviation of
+    independent roundings; eight are allowed."""
+    g = torch.Generator(device="cuda").manual_seed(n_q * H)
+    M = -(-L // B)
+    Kp = torch.randn(2, M, 128, generator=g, device="cuda") * 0.05
+    Q = (torch.randn(2, n_q, H, 128, generator=g, device="cuda") * 0.09).to(torch.bfloat16)
+    W = torch.randn(2, n_q, H, generator=g, device="cuda")
+    pos = torch.randint(0, L, (n_q,), generator=g, device="cuda", dtype=torch.int32)
+    p = misa.Problem(2, L, n_q, H, B, 1, misa.BF16, misa.BF16, pos)
+    m = 2
+    idx = torch.empty(2, n_q, m * B, dtype=torch.int32, device="cuda")
+    ws = misa.alloc_workspace(p, misa.OP_HISA, m)
+    misa.block_sparse_select(p, Q, W, Kp, m, idx, None, ws)
+    torch.cuda.synchronize()
+    J = ws[:2 * n_q * M * 4].view(torch.float32).view(2, n_q, M).double()
+    for s in range(2):
+        dots = (Q[s].double().reshape(-1, 128) @ Kp[s].double().T).relu().view(n_q, H, M)
+        ref = (W[s].double()[..., None] * dots).sum(1)
+        size = (W[s].double().abs()[..., None] * (Q[s].double().abs().reshape(-1, 128) @ Kp[s].double().abs().T).view(n_q, H, M)).sum(1)
+        Mn = (pos.long()[:, None] + B) // B
+        b = torch.arange(M, device="cuda")[None]
+        forced, none = (b == 0) | (b == Mn - 1), b >= Mn
+        assert bool((J[s][none] == -np.inf).all()) and bool((J[s][forced & ~none] == np.inf).all())
+        inner = ~forced & ~none
+        tol = 8 * 2.0 ** -24 * (128 + H) ** 0.5 * size
+        assert bool(((J[s] - ref).abs() <= tol)[inner].all())
