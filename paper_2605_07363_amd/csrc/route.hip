@@ -99,6 +99,17 @@ __global__ __launch_bounds__(256) void route_partial_kernel(Prob p, int splits,
 
 constexpr int kRouteKT = 32;  // pooled blocks per LDS tile
 
+// Sum over each row of 16 lanes, in its lane 15 (all lanes of the wavefront active).
+__device__ __forceinline__ float row16_sum(float v) {
+#define MISA_DPP_ADD(ctrl) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xf, 0xf, true))
+  MISA_DPP_ADD(0x111);  // row_shr:1
+  MISA_DPP_ADD(0x112);  // row_shr:2
+  MISA_DPP_ADD(0x114);  // row_shr:4
+  MISA_DPP_ADD(0x118);  // row_shr:8
+#undef MISA_DPP_ADD
+  return v;
+}
+
 union RFrag {
   bf16x8 v;
   uint4 u;
@@ -289,73 +300,63 @@ __global__ __launch_bounds__(256) void route_tile_kernel(Prob p, int splits,
     }
 }
 
-// Few query-head rows (decode: n_q * H <= 64): every wavefront works alone on its own tiles
-// of 32 pooled blocks, which it loads straight into matrix fragments (a lane reads 32
-// contiguous bytes of one pooled key per k-step) and splits into bf16 hi/lo pieces in
-// registers: no LDS, no barrier, one round of loads per tile.  RT = 32-row tiles in use.
+// Few query-head rows (decode: n_q * H <= 64 in one workgroup; up to 7 queries of any head count: blockIdx.z
+// is the query): a wavefront takes 16 pooled blocks at a time as the columns
+// of v_mfma_f32_16x16x32_bf16, loads them straight into matrix fragments (a lane reads 32 contiguous bytes
+// of a pooled key per k-step) and splits them into two bf16 pieces in registers; RT 16-row tiles of head
+// rows are the other operand.  The sums over a wavefront's columns are four shifted adds inside rows of 16
+// lanes, the four wavefronts of a workgroup add theirs through LDS: one partial sum per row and 64 blocks.
+// Bound by latency: one round of loads, few instructions.  (32 blocks per wavefront on the 32x32 instruction,
+// the columns added by lane exchanges, a partial sum per wavefront: 14-15 us
+// for 64 heads against 6-8 us; four queries of 64 heads on the tile kernel 19 us.)
 template <int RT>
-__global__ __launch_bounds__(256) void route_wave_kernel(Prob p, int tiles_per_wave, int n_parts,
-                                                         const uint16_t* __restrict__ Q,
-                                                         const float* __restrict__ Kp,
-                                                         float* __restrict__ part) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 31, hf = lane >> 5;
+__global__ __launch_bounds__(256) void route_few_kernel(Prob p, int tiles_per_wave, int n_parts,
+                                                        const uint16_t* __restrict__ Q,
+                                                        const float* __restrict__ Kp,
+                                                        float* __restrict__ part) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c = lane & 15, g = lane >> 4;
   const int seq = blockIdx.y;
-  const int pi = blockIdx.x * 4 + wave;  // partial-sum slot of this wavefront
-  if (pi >= n_parts) return;
-  const int rows_per_seq = p.n_q * p.H;
-  const int len = seq_length(p, seq);
-  // row / H for rows < 64 by one multiplication: exact because row * (H * inv - 65536) < 65536
-  const uint32_t inv = (65536u + (uint32_t)p.H - 1u) / (uint32_t)p.H;
+  const int t0 = blockIdx.z, rows = gridDim.z > 1 ? p.H : p.n_q * p.H;   // first query, its (and the others') rows
+  __shared__ __align__(16) int s_nb[kWave];     // pooled blocks a row may use
+  __shared__ float s_sum[4][kWave];
 
-  RFrag a[RT][8];
-  int nb[RT][16];
+  RFrag a[RT][4];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    const int row = rt * 32 + col;
-    const uint16_t* src = Q + ((size_t)seq * rows_per_seq + min(row, rows_per_seq - 1)) * kD + hf * 8;
+    const int row = rt * 16 + c;
+    const uint16_t* src = Q + (((size_t)seq * p.n_q + t0) * p.H + min(row, rows - 1)) * kD + g * 8;
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      const uint4 v = *reinterpret_cast<const uint4*>(src + ks * 16);
-      a[rt][ks].u = row < rows_per_seq ? v : make_uint4(0, 0, 0, 0);
-    }
-    int t_prev = -1, nb_prev = 0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int rr = rt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-      int v = 0;
-      if (rr < rows_per_seq) {
-        const int t = (int)(((uint32_t)rr * inv) >> 16);
-        if (t != t_prev) { nb_prev = pooled_blocks(visible(p, seq, t), len, p.B); t_prev = t; }
-        v = nb_prev;
-      }
-      nb[rt][r] = v;
-    }
+    for (int ks = 0; ks < 4; ++ks) a[rt][ks].u = *reinterpret_cast<const uint4*>(src + ks * 32);
   }
-  float sum[RT][16];
+  const float* kp_seq = Kp + (size_t)seq * p.M * kD;
+  float4 x[4][2];
+  auto load = [&](int b0) {
+    const float* src = kp_seq + (size_t)min(b0 + c, p.M - 1) * kD + g * 8;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      x[ks][0] = *reinterpret_cast<const float4*>(src + ks * 32);
+      x[ks][1] = *reinterpret_cast<const float4*>(src + ks * 32 + 4);
+    }
+  };
+  const int first = ((int)blockIdx.x * 4 + wave) * tiles_per_wave * 16;
+  load(first);
+  if (tid < kWave)
+    s_nb[tid] = tid < rows ? min(pooled_blocks(visible(p, seq, t0 + tid / p.H), seq_length(p, seq), p.B), p.M) : 0;
+  __syncthreads();
+  float sum[RT][4];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) sum[rt][r] = 0.f;
+    for (int j = 0; j < 4; ++j) sum[rt][j] = 0.f;
 
-  const float* kp_seq = Kp + (size_t)seq * p.M * kD;
   for (int tl = 0; tl < tiles_per_wave; ++tl) {
-    const int b0 = (pi * tiles_per_wave + tl) * kRouteKT;
-    if (b0 >= p.M) break;
-    const float* src = kp_seq + (size_t)min(b0 + col, p.M - 1) * kD + hf * 8;
-    float4 x[8][2];
+    const int b0 = first + tl * 16;
+    f32x4 acc[RT];
 #pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
-      x[ks][0] = *reinterpret_cast<const float4*>(src + ks * 16);
-      x[ks][1] = *reinterpret_cast<const float4*>(src + ks * 16 + 4);
-    }
-    f32x16 acc[RT];
+    for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[rt][r] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 8; ++ks) {
+    for (int ks = 0; ks < 4; ++ks) {
       const float v[8] = {x[ks][0].x, x[ks][0].y, x[ks][0].z, x[ks][0].w,
                           x[ks][1].x, x[ks][1].y, x[ks][1].z, x[ks][1].w};
       uint32_t hi[4], lo[4];
@@ -365,32 +366,34 @@ __global__ __launch_bounds__(256) void route_wave_kernel(Prob p, int tiles_per_w
       bh.u = make_uint4(hi[0], hi[1], hi[2], hi[3]);
       bl.u = make_uint4(lo[0], lo[1], lo[2], lo[3]);
 #pragma unroll
-      for (int rt = 0; rt < RT; ++rt) {
-        acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt][ks].v, bh.v, acc[rt], 0, 0, 0);
-        acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt][ks].v, bl.v, acc[rt], 0, 0, 0);
-      }
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt][ks].v, bh.v, acc[rt], 0, 0, 0);
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt][ks].v, bl.v, acc[rt], 0, 0, 0);
     }
-    const int b = b0 + col;
+    if (tl + 1 < tiles_per_wave) load(b0 + 16);
+    // the accumulator of lane (c, g) holds rows 16 rt + 4 g + j of column c
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sum[rt][r] += (b < nb[rt][r] && b < p.M) ? relu(acc[rt][r]) : 0.f;
+    for (int rt = 0; rt < RT; ++rt) {
+      const int4 nb = *reinterpret_cast<const int4*>(&s_nb[16 * rt + 4 * g]);
+      sum[rt][0] += b0 + c < nb.x ? relu(acc[rt][0]) : 0.f;
+      sum[rt][1] += b0 + c < nb.y ? relu(acc[rt][1]) : 0.f;
+      sum[rt][2] += b0 + c < nb.z ? relu(acc[rt][2]) : 0.f;
+      sum[rt][3] += b0 + c < nb.w ? relu(acc[rt][3]) : 0.f;
+    }
   }
-
-  // sum over the 32 block columns of each half-wave, then one lane per row writes
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float v = sum[rt][r];
-#pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-      const int rr = rt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-      if (col == 0 && rr < rows_per_seq) {
-        const int t = (int)(((uint32_t)rr * inv) >> 16), j = rr - t * p.H;
-        part[(((size_t)seq * p.n_q + t) * n_parts + pi) * kWave + j] = v;
-      }
+    for (int j = 0; j < 4; ++j) {
+      const float v = row16_sum(sum[rt][j]);    // in lane 15 of the 16
+      if (c == 15) s_sum[wave][16 * rt + 4 * g + j] = v;
     }
+  __syncthreads();
+  if (tid < rows) {
+    const int t = tid / p.H, j = tid - t * p.H;
+    part[(((size_t)seq * p.n_q + t0 + t) * n_parts + blockIdx.x) * kWave + j] =
+        (s_sum[0][tid] + s_sum[1][tid]) + (s_sum[2][tid] + s_sum[3][tid]);
+  }
 }
 
 template <int KDT, int QDT>
@@ -399,8 +402,7 @@ __global__ __launch_bounds__(128) void route_finalize_kernel(
     const void* __restrict__ K, const float* __restrict__ kscale, const float* __restrict__ part,
     int* __restrict__ heads, float* __restrict__ E) {
   __shared__ float tailk[kD];
-  __shared__ float Es[kMaxH];
-  __shared__ int sel[kMaxH];
+  __shared__ __align__(16) float Es[kMaxH];
   __shared__ float sred[4][kMaxH];
   __shared__ float sdot[kMaxH];
   using KV = Vec16<KDT>;
@@ -409,6 +411,8 @@ __global__ __launch_bounds__(128) void route_finalize_kernel(
   const int nfull = n / p.B, r = n - nfull * p.B;
   const int Mn = nfull + (r > 0 ? 1 : 0);
   const bool tail = r > 0 && n < len;
+  const size_t q_head = ((size_t)seq * p.n_q + t) * p.H + min(tid, p.H - 1);
+  const float gate = W[q_head];   // (requested before the chain of round trips that it ends)
 
   if (tail) {  // mean of keys nfull*B .. n-1, component tid
     const char* base = static_cast<const char*>(K);
@@ -476,30 +480,30 @@ __global__ __launch_bounds__(128) void route_finalize_kernel(
     __syncthreads();
   }
 
-  if (tid < p.H) {
-    const size_t qi = ((size_t)seq * p.n_q + t) * p.H + tid;
-    float s = sred[0][tid] + sred[1][tid];
-    if (p.H <= 32) s += sred[2][tid] + sred[3][tid];
-    if (tail) s += fmaxf(sdot[tid], 0.f);
-    const float e = Mn > 0 ? fabsf(W[qi]) * s / (float)Mn : 0.f;
-    Es[tid] = e;
-    if (E) E[qi] = e;
-  }
-  __syncthreads();
-  if (tid < p.H) {
-    const float e = Es[tid];
-    int rank = 0;
-    for (int i = 0; i < p.H; ++i) {
-      const float o = Es[i];
-      rank += (o > e || (o == e && i < tid)) ? 1 : 0;
+  if (tid < kMaxH) {   // one wavefront
+    float e = -INFINITY;
+    if (tid < p.H) {
+      float s = sred[0][tid] + sred[1][tid];
+      if (p.H <= 32) s += sred[2][tid] + sred[3][tid];
+      if (tail) s += fmaxf(sdot[tid], 0.f);
+      e = Mn > 0 ? fabsf(gate) * s / (float)Mn : 0.f;
+      if (E) E[q_head] = e;
     }
-    sel[tid] = rank < p.h ? 1 : 0;
-  }
-  __syncthreads();
-  if (tid < p.H && sel[tid]) {
-    int pos = 0;
-    for (int i = 0; i < tid; ++i) pos += sel[i];
-    heads[((size_t)seq * p.n_q + t) * p.h + pos] = tid;
+    Es[tid] = e;
+    __builtin_amdgcn_wave_barrier();   // (the wavefront's own writes: LDS keeps their order)
+    int rank = 0;
+#pragma unroll 4
+    for (int i = 0; i < kMaxH; i += 4) {   // (rows past H hold -inf and rank behind every head)
+      const float4 o = *reinterpret_cast<const float4*>(&Es[i]);
+      rank += (o.x > e || (o.x == e && i < tid)) ? 1 : 0;
+      rank += (o.y > e || (o.y == e && i + 1 < tid)) ? 1 : 0;
+      rank += (o.z > e || (o.z == e && i + 2 < tid)) ? 1 : 0;
+      rank += (o.w > e || (o.w == e && i + 3 < tid)) ? 1 : 0;
+    }
+    const bool chosen = tid < p.H && rank < p.h;
+    const unsigned long long mask = __ballot(chosen);
+    const int pos = __popcll(mask & ((1ull << tid) - 1ull));
+    if (chosen && pos < p.h) heads[((size_t)seq * p.n_q + t) * p.h + pos] = tid;   // (NaN scores rank first together)
   }
 }
 
@@ -577,22 +581,22 @@ int route_splits(const Prob& p) {
   return (int)s;
 }
 
-// The per-wavefront kernel is used when all (query, head) rows of a sequence fit one wavefront.
-static bool route_by_wave(const Prob& p) { return (long long)p.n_q * p.H <= 64; }
+// Whether all (query, head) rows of a sequence fit one wavefront.
+static bool route_few_rows(const Prob& p) { return (long long)p.n_q * p.H <= 64; }
 
-// Tiles per wavefront and partial sums per query of the per-wavefront kernel: one tile each
-// up to 64 partial sums, more tiles per wavefront beyond.
-static void route_wave_shape(const Prob& p, int* tiles_per_wave, int* n_parts) {
-  const int tiles = (p.M + kRouteKT - 1) / kRouteKT;
-  *tiles_per_wave = (tiles + 63) / 64;
-  *n_parts = (tiles + *tiles_per_wave - 1) / *tiles_per_wave;
+// 16-block tiles per wavefront and partial sums (workgroups) per query of route_few_kernel: one tile each
+// up to the partial sums there is room for, more tiles per wavefront beyond.
+static void route_few_shape(const Prob& p, int* tiles_per_wave, int* n_parts) {
+  const int groups = (p.M + 63) / 64, most = route_few_rows(p) ? 64 : 4 * route_splits(p);
+  *tiles_per_wave = (groups + most - 1) / most;
+  *n_parts = (groups + *tiles_per_wave - 1) / *tiles_per_wave;
 }
 
 size_t route_ws_bytes(const Prob& p) {
   // partial sums [n_seq, n_q, parts, 64]; the tiled kernel needs room for every column phase
-  // (splits * 4), the per-wavefront kernel for its (at most 64) parts
+  // (splits * 4), the kernels for few rows for their (at most 64) parts
   size_t parts = (size_t)route_splits(p) * 4;
-  if (route_by_wave(p)) parts = std::max<size_t>(parts, 64);
+  if (route_few_rows(p)) parts = std::max<size_t>(parts, 64);
   return (size_t)p.n_seq * p.n_q * parts * kWave * sizeof(float);
 }
 
@@ -602,14 +606,17 @@ hipError_t launch_route(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
   const int splits = route_splits(p);
   float* part = static_cast<float*>(ws);
   int total_splits = splits;
-  if (q_dtype == MISA_BF16 && route_by_wave(p)) {
+  if (q_dtype == MISA_BF16 && (route_few_rows(p) || p.n_q < 8)) {
     int tpw, parts;
-    route_wave_shape(p, &tpw, &parts);
+    route_few_shape(p, &tpw, &parts);
     total_splits = parts;
-    const dim3 g1((parts + 3) / 4, p.n_seq);
+    const bool together = route_few_rows(p);
+    const dim3 g1(parts, p.n_seq, together ? 1 : p.n_q);
     const uint16_t* q = static_cast<const uint16_t*>(Q);
-    if (p.n_q * p.H <= 32) route_wave_kernel<1><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
-    else route_wave_kernel<2><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
+    const int rows = together ? p.n_q * p.H : p.H;
+    if (rows <= 16) route_few_kernel<1><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
+    else if (rows <= 32) route_few_kernel<2><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
+    else route_few_kernel<4><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
   } else if (q_dtype == MISA_BF16) {
     const int rg = route_row_groups(p);
     total_splits = splits * (4 / rg);
@@ -617,11 +624,13 @@ hipError_t launch_route(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
     const dim3 g1(splits, (rows + 64 * rg - 1) / (64 * rg), p.n_seq);
     const uint16_t* q = static_cast<const uint16_t*>(Q);
     if (rg == 4) route_tile_kernel<4><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);
-    else if (rg == 2) route_tile_kernel<2><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);
-    else route_tile_kernel<1><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);
+    else route_tile_kernel<2><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);   // (one group: few rows)
   } else {
-    const dim3 g1(splits, p.n_q, p.n_seq);
-    route_partial_kernel<MISA_F32><<<g1, 256, 0, st>>>(p, splits, Q, Kp, part);
+    // few rows: a block per wavefront while that makes at most 64 partial sums (64 blocks: 6.8 us; 25 us in
+    // one workgroup, whose wavefronts then take 16 blocks each one after the other)
+    if (route_few_rows(p)) total_splits = std::min(64, (p.M + 3) / 4);
+    const dim3 g1(total_splits, p.n_q, p.n_seq);
+    route_partial_kernel<MISA_F32><<<g1, 256, 0, st>>>(p, total_splits, Q, Kp, part);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

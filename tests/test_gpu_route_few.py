@@ -1,0 +1,44 @@
+"""Router of decode-like problems (a few queries per sequence): head scores against fp64 at the edges of the
+block tiles, partial sums and row tiles, and the chosen heads by the margin rule on them."""
+import numpy as np
+import pytest
+
+from oracle import misa_oracle as O
+from paper_2605_07363_amd import workloads as WL
+from helpers import assert_scores_close, check_index_set, oracle_view
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def misa():
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2605_07363_amd import misa as m
+    return m
+
+
+@pytest.mark.parametrize("q_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_q,H,L,B", [(1, 64, 1024, 16), (1, 64, 1025, 16), (1, 33, 4111, 1), (1, 16, 63, 64), (1, 17, 16 * 65, 16),
+                                       (3, 64, 2000, 16), (7, 40, 1031, 8), (2, 32, 700, 7), (5, 12, 515, 4), (7, 64, 1, 1),
+                                       (1, 1, 9001, 2), (4, 64, 70000, 8)])
+def test_head_scores(misa, n_q, H, L, B, q_dtype):
+    wl = WL.scaled(WL.WORKLOADS["c1"], n_seq=2, L=L, n_q=n_q, H=H, h=min(H, 8), B=B, decode=n_q == 1, q_dtype=q_dtype, needles=0)
+    inp = WL.make_inputs(wl, seed=L + H, seq_len=[L, max(1, L - L // 3)])
+    if n_q > 1:
+        inp["q_pos"] = np.maximum(0, L - 1 - np.array([0, 1, 5, L // 2, L, 2, L // 4])[:n_q]).astype(np.int32)
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    Kp = torch.empty(2, p.M, 128, device="cuda")
+    misa.pool_keys(p, dv["K"], dv["kscale"], Kp, misa.alloc_workspace(p, misa.OP_POOL))
+    heads = torch.empty(2, n_q, p.h, dtype=torch.int32, device="cuda")
+    E = torch.empty(2, n_q, H, device="cuda")
+    misa.route_heads(p, dv["Q"], dv["W"], Kp, dv["K"], dv["kscale"], heads, E, misa.alloc_workspace(p, misa.OP_ROUTE))
+    torch.cuda.synchronize()
+    for s in range(2):
+        for t in range(n_q):
+            K, q, w, n = oracle_view(inp, s, t)
+            _, ref = O.route_heads(q, w, K, B, p.h, n)
+            assert_scores_close(E[s, t].cpu().numpy(), ref, f"E {s} {t}")
+            check_index_set(heads[s, t].cpu().numpy(), ref, p.h, f"heads {s} {t}")
