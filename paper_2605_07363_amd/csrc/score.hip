@@ -152,7 +152,10 @@ __global__ __launch_bounds__(256) void score_stream_kernel(
   constexpr int NLD = KDT == MISA_BF16 ? 4 : 2;  // 16-byte loads per lane and 16-key tile
   constexpr int KPW = 256 * STEPS * G;           // keys per workgroup
   constexpr int NQ = MQ ? NT * MQ : 1;           // queries per workgroup
-  const int t = blockIdx.y * NQ, seq = blockIdx.z;   // (first) query
+  // Last sequence and last keys first: a pass that has just pooled the cache read those last, and the
+  // memory-side cache (256 MB) still holds part of them (32 x 131072 fp8 keys, whole pass: 215.5 us against
+  // 221.0 us; a cache that was not read right before costs the same in either order).
+  const int t = blockIdx.y * NQ, seq = gridDim.z - 1 - blockIdx.z;   // (first) query
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c = lane & 15, g = lane >> 4;
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(256) void score_stream_kernel(
   const char* kbase = static_cast<const char*>(K) + (size_t)seq * p.L * ROW_BYTES;
   const float* sbase = kscale + (size_t)seq * p.L;
   float* srow = S + qrow * p.L;
-  const int k_begin = blockIdx.x * KPW;
+  const int k_begin = (gridDim.x - 1 - blockIdx.x) * KPW;
   const int k_end = min(k_begin + KPW, p.L);
 
   Frag a[NT][4];   // query operand and gates, filled after the first key loads are issued
