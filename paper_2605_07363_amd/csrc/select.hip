@@ -204,9 +204,11 @@ __global__ __launch_bounds__(kThrThreads) void select_threshold_kernel(
 // One workgroup of NT threads per row: exact top-k of the row's candidate list.
 // Thread t owns list entries t, t + NT, ... (at most EPT of them) and keeps them in
 // registers for all passes, so LDS only holds the histogram and the row bitmaps and
-// several rows share a compute unit.
+// several rows share a compute unit.  The chain of barriers of one row is the bound, so the second row
+// on a CU counts: index and score of 13 entries, without their keys, leave 46 registers (2048 rows of
+// about 10500 entries: 95 us; 127 us with the keys kept, 83 registers and one workgroup of 1024 per CU).
 template <int NT, int EPT>
-__global__ __launch_bounds__(NT) void select_rows_kernel(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void select_rows_kernel(
     Prob p, const int2* __restrict__ cand, const int* __restrict__ seg, const int* __restrict__ seg_count,
     int ranges, const float* __restrict__ tau, const uint32_t* __restrict__ upper, int cap, int k, int qwg,
     int q_tiles, int* __restrict__ idx, float* __restrict__ val, int* __restrict__ row_flag,
@@ -260,9 +262,9 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
   const int nwords = (n + 31) / 32;
   uint32_t* sel = dyn;
   int* wpre = reinterpret_cast<int*>(dyn + (p.L + 31) / 32);
-  // this thread's entries: index (-1 = none) and order-preserving key of the score
+  // this thread's entries: index (-1 = none) and score; the order-preserving key is made again in every
+  // pass, so that two workgroups of 1024 threads fit a CU (64 registers)
   int ei[EPT];
-  uint32_t ek[EPT];
   float ev[EPT];
   const int2* src = cand + row * (size_t)cap;
   int rg = 0, rg_begin = 0, rg_end = seg_pre[1];   // the range whose entries [rg_begin, rg_end) hold entry i
@@ -280,8 +282,8 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
     }
     ei[u] = e.x;
     ev[u] = __int_as_float(e.y);
-    ek[u] = order_key(ev[u]);
   }
+  auto key_of = [&](int u) { return order_key(ev[u]); };
   for (int i = tid; i < nwords; i += NT) sel[i] = 0;
   if (tid == 0) b_len = 0;
   if (tid < 64) brank[tid] = 0;
@@ -306,18 +308,24 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
     };
 #pragma unroll
     for (int u = 0; u < EPT; ++u)
-      if (ei[u] >= 0) atomicAdd(&hist[digit(ek[u])], 1);
+      if (ei[u] >= 0) atomicAdd(&hist[digit(key_of(u))], 1);
     __syncthreads();
     find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr);
     const uint32_t d1 = thr[0];
     const int need = thr[1], nb = thr[2];
     if (nb <= 64 && d1 != kBins - 1) {   // block-uniform
+      // (digit > d1 and == d1 as compares of the shifted distance; d1 < 2047, and what lies past the span
+      // shares 2047)
+      const uint32_t from = d1 << 21, past = (d1 + 1) << 21;
 #pragma unroll
       for (int u = 0; u < EPT; ++u) {
-        const uint32_t a = ei[u] >= 0 ? digit(ek[u]) : 0u;
-        if (ei[u] >= 0 && a > d1) mark(ei[u]);
-        const int b = wave_append(ei[u] >= 0 && a == d1, &b_len);
-        if (b >= 0) { bkey[b] = ek[u]; bidx[b] = ei[u]; }
+        const uint32_t key = key_of(u), x = key > klo ? key - klo : 0u, y = x > span ? 0xFFFFFFFFu : x << sh;
+        if (ei[u] >= 0 && y >= past) mark(ei[u]);
+        const bool edge = ei[u] >= 0 && y >= from && y < past;
+        if (__builtin_amdgcn_ballot_w64(edge)) {
+          const int b = wave_append(edge, &b_len);
+          if (b >= 0) { bkey[b] = key_of(u); bidx[b] = ei[u]; }
+        }
       }
       __syncthreads();
       {
@@ -352,7 +360,7 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
     // most significant digit first: 11 + 11 + 10 bits of the key
 #pragma unroll
     for (int u = 0; u < EPT; ++u)
-      if (ei[u] >= 0) atomicAdd(&hist[ek[u] >> 21], 1);
+      if (ei[u] >= 0) atomicAdd(&hist[key_of(u) >> 21], 1);
     __syncthreads();
     find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr);
     const uint32_t d1 = thr[0];
@@ -362,9 +370,9 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
       if (ei[u] < 0) continue;
-      const uint32_t a = ek[u] >> 21;
+      const uint32_t a = key_of(u) >> 21;
       if (a > d1) mark(ei[u]);
-      else if (a == d1) atomicAdd(&hist[(ek[u] >> 10) & 0x7FF], 1);
+      else if (a == d1) atomicAdd(&hist[(key_of(u) >> 10) & 0x7FF], 1);
     }
     __syncthreads();
     find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
@@ -374,9 +382,9 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
     zero_hist_n<NT>(hist);
 #pragma unroll
     for (int u = 0; u < EPT; ++u) {
-      if (ei[u] < 0 || (ek[u] >> 21) != d1) continue;
-      if ((ek[u] >> 10) > pre22) mark(ei[u]);
-      else if ((ek[u] >> 10) == pre22) atomicAdd(&hist[ek[u] & 0x3FF], 1);
+      if (ei[u] < 0 || (key_of(u) >> 21) != d1) continue;
+      if ((key_of(u) >> 10) > pre22) mark(ei[u]);
+      else if ((key_of(u) >> 10) == pre22) atomicAdd(&hist[key_of(u) & 0x3FF], 1);
     }
     __syncthreads();
     find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
@@ -387,7 +395,7 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
     if (ties == need) {
 #pragma unroll
       for (int u = 0; u < EPT; ++u)
-        if (ei[u] >= 0 && (ek[u] >> 10) == pre22 && ek[u] >= tkey) mark(ei[u]);
+        if (ei[u] >= 0 && (key_of(u) >> 10) == pre22 && key_of(u) >= tkey) mark(ei[u]);
     } else {
       // More entries equal to the threshold value than places: the `need` lowest
       // indices among them win, found by the same digit search on the (high, low)
@@ -396,8 +404,8 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
 #pragma unroll
       for (int u = 0; u < EPT; ++u) {
         if (ei[u] < 0) continue;
-        if ((ek[u] >> 10) == pre22 && ek[u] > tkey) mark(ei[u]);
-        else if (ek[u] == tkey) atomicAdd(&hist[kBins - 1 - (ei[u] >> 10)], 1);
+        if ((key_of(u) >> 10) == pre22 && key_of(u) > tkey) mark(ei[u]);
+        else if (key_of(u) == tkey) atomicAdd(&hist[kBins - 1 - (ei[u] >> 10)], 1);
       }
       __syncthreads();
       find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
       zero_hist_n<NT>(hist);
 #pragma unroll
       for (int u = 0; u < EPT; ++u) {
-        if (ei[u] < 0 || ek[u] != tkey) continue;
+        if (ei[u] < 0 || key_of(u) != tkey) continue;
         if ((ei[u] >> 10) < hi_digit) mark(ei[u]);
         else if ((ei[u] >> 10) == hi_digit) atomicAdd(&hist[kBins - 1 - (ei[u] & 0x3FF)], 1);
       }
@@ -416,7 +424,7 @@ __global__ __launch_bounds__(NT) void select_rows_kernel(
       const int lo_digit = kBins - 1 - thr[0];
 #pragma unroll
       for (int u = 0; u < EPT; ++u) {
-        if (ei[u] < 0 || ek[u] != tkey) continue;
+        if (ei[u] < 0 || key_of(u) != tkey) continue;
         if ((ei[u] >> 10) == hi_digit && (ei[u] & 0x3FF) <= lo_digit) mark(ei[u]);
       }
     }
