@@ -1,5 +1,5 @@
 // Building blocks of the radix select shared by the top-k kernels: 2048-bin
-// LDS histograms scanned from the top by a block of 1024 threads, and
+// LDS histograms scanned from the top by a block of threads, and
 // wavefront-aggregated list appends.
 #pragma once
 
@@ -44,18 +44,11 @@ __device__ __forceinline__ void find_threshold_bin_n(const int* hist, int need, 
   __syncthreads();
 }
 
-__device__ __forceinline__ void find_threshold_bin(const int* hist, int need, int* scan_scratch,
-                                                   int* out, int need2 = 0, int* out2 = nullptr) {
-  find_threshold_bin_n<kTopkThreads>(hist, need, scan_scratch, out, need2, out2);
-}
-
 template <int NT>
 __device__ __forceinline__ void zero_hist_n(int* hist) {
   for (int i = threadIdx.x; i < kBins; i += NT) hist[i] = 0;
   __syncthreads();
 }
-
-__device__ __forceinline__ void zero_hist(int* hist) { zero_hist_n<kTopkThreads>(hist); }
 
 // Appends the flagged lanes' values to a list whose length counter lives at *counter
 // (LDS or global); one atomic per wavefront.  Returns the slot of this lane (or -1).

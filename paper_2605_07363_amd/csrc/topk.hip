@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   int* seg = pre + (row * gridDim.x + range) * kSegInts;
   float held[kHeldLong];
   uint32_t have;
-  Bracket br;
+  Bracket br = {0.f, 0.f, 0.f};
   Stream<NT, 2> st;
   const bool ok = sample_bracket<NT, false>(s, n, k, held, have, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
   if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
