@@ -426,7 +426,7 @@ __device__ __forceinline__ void write_listed(const uint2* list, int listed, int 
 // selects from the segments of a row.  Two launches: rows up to 65536 elements are faster in one (32768:
 // 13.8 us against 17.3 us; 131072: 24.0 us against 21.2 us).
 constexpr int kMaxRanges = 16;      // key ranges (workgroups) per row
-constexpr int kSegCap = 7000;       // entries of a segment
+constexpr int kSegCap = 6936;       // entries of a segment, behind them 64 of slack
 constexpr int kSegInts = 64 + 2 * (kSegCap + 64);   // header (fill, or -1: no bracket; bracket at 8 .. 10), then entries
 
 // Length of the key ranges a row of L elements is cut into (at most kMaxRanges of them).
