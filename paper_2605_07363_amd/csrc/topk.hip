@@ -14,6 +14,7 @@
 // repeat so much that the list overflows) is redone by the radix select on the row itself, which
 // reads it twice (or four times if the values around the k-th are heavily repeated).
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 #include <utility>
@@ -174,7 +175,8 @@ __device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int 
     find_threshold_bin_n<NT>(hist, r_lo, L.scan_scratch, L.thr, max(r_hi, 1), L.thr_up);
     const int b_lo = L.thr[0], b_hi = L.thr_up[0];
     const int crowd = max(L.thr[2], L.thr_up[2]);
-    br.lo = lo + ((float)b_lo - 0.02f) * width;
+    // (never -inf, which pads the list appends: a row's lowest finite values may be in the bracket)
+    br.lo = fmaxf(lo + ((float)b_lo - 0.02f) * width, -FLT_MAX);
     br.edge = lo + ((float)b_hi + 1.02f) * width;
     br.hi = r_hi >= 1 ? br.edge : INFINITY;
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;   // (read by everybody: find_threshold_bin ends with a barrier)

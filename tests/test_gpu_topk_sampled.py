@@ -58,3 +58,27 @@ def test_rows_match_the_oracle(misa, L, k, many):
         assert np.array_equal(v[t, :len(ref)], x[t, ref])
     for r in range(1, rep):
         assert np.array_equal(got[r * rows:(r + 1) * rows], got[:rows])
+
+
+@pytest.mark.parametrize("many", [False, True])
+@pytest.mark.parametrize("L,n,k,first,last", [(4096, 4000, 3976, 384, 413), (8192, 8100, 8080, 1280, 1320),
+                                              (4096, 4095, 4090, 100, 163), (4096, 4000, 3950, 3900, 3959)])
+def test_lowest_finite_values_below_a_prefix(misa, L, n, k, first, last, many):
+    """The k-th largest is one of a few entries of the lowest finite value (a usual mask), the row ends
+    before the buffer does: only visible keys, and of the masked ones the first."""
+    x = np.random.default_rng(L + n + k).standard_normal(L).astype(np.float32)
+    x[first:last + 1] = np.finfo(np.float32).min
+    rows = 600 if many else 1
+    S = torch.from_numpy(np.tile(x, (rows, 1))).cuda()
+    seq_len = torch.full((rows,), n, dtype=torch.int32, device="cuda")
+    p = misa.Problem(rows, L, 1, 64, 64, 8, misa.BF16, misa.BF16, None, seq_len)
+    idx = torch.full((rows, 1, k), -9, dtype=torch.int32, device="cuda")
+    val = torch.full((rows, 1, k), -9.0, dtype=torch.float32, device="cuda")
+    misa.topk(p, S, k, idx, val, misa.alloc_workspace(p, misa.OP_TOPK, k))
+    torch.cuda.synchronize()
+    got, v = idx[:, 0].cpu().numpy(), val[:, 0].cpu().numpy()
+    ref = O.topk(x[:n].astype(np.float64), k)
+    assert len(ref) == k
+    for t in range(rows):
+        assert np.array_equal(got[t], ref), t
+        assert np.array_equal(v[t], x[ref]), t
