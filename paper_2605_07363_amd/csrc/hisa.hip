@@ -78,6 +78,9 @@ __global__ __launch_bounds__(256) void block_score_kernel(Prob p, const void* __
 // a key is lost; products are exact and added in fp32.  A wavefront keeps the pieces of 32 blocks in
 // registers (96) and the head rows of the queries pass through LDS, double buffered, shared by the four
 // wavefronts of the workgroup: a step is 64 (query, head) rows, HS = 64 or 32 head slots per query.
+// The pieces of an infinite (or larger than bf16) component are not numbers, and an infinity times a zero
+// piece or a zero head slot is none either: blocks with such a key and queries with such a component, found
+// from the exponents of the operands, are scored by themselves in fp32, in the order of block_score_kernel.
 // Bound: 3 x 2 H 128 flop per (query, block).  1024 queries x 512 blocks x 64 heads: 33 us, 155 us with one
 // thread per block on the vector units; error of the scores against 64 bits 1.3e-7 (1.5e-7 before).
 union BFrag {
@@ -101,6 +104,34 @@ __device__ __forceinline__ void split_three(float x0, float x1, uint32_t& a, uin
   c = l.u;
 }
 
+// Whether one of the two bf16 values of a word has all exponent bits set (collected in bits 15 and 31).
+__device__ __forceinline__ uint32_t exponents_full(uint32_t w) {
+  return ((w & 0x7F807F80u) + 0x00800080u) & 0x80008000u;
+}
+
+// The score of one block by itself: heads rows of a query in LDS, `slots` 16-byte pieces apart.
+__device__ __forceinline__ float block_score_plain(const uint4* rows, int slots, const float* gate, int heads,
+                                                const float* __restrict__ key) {
+  float total = 0.f;
+  for (int j = 0; j < heads; ++j) {
+    float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
+    for (int c = 0; c < 16; ++c) {
+      const uint4 q = rows[j * slots + c];
+      const float4 x = *reinterpret_cast<const float4*>(key + 8 * c), y = *reinterpret_cast<const float4*>(key + 8 * c + 4);
+      d0 = fmaf(__uint_as_float(q.x << 16), x.x, d0);
+      d1 = fmaf(__uint_as_float(q.x & 0xFFFF0000u), x.y, d1);
+      d2 = fmaf(__uint_as_float(q.y << 16), x.z, d2);
+      d3 = fmaf(__uint_as_float(q.y & 0xFFFF0000u), x.w, d3);
+      d0 = fmaf(__uint_as_float(q.z << 16), y.x, d0);
+      d1 = fmaf(__uint_as_float(q.z & 0xFFFF0000u), y.y, d1);
+      d2 = fmaf(__uint_as_float(q.w << 16), y.z, d2);
+      d3 = fmaf(__uint_as_float(q.w & 0xFFFF0000u), y.w, d3);
+    }
+    total = fmaf(gate[j], relu((d0 + d1) + (d2 + d3)), total);
+  }
+  return total;
+}
+
 template <int HS>
 __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps, const uint16_t* __restrict__ Q,
                                                                const float* __restrict__ W,
@@ -111,13 +142,16 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
   __shared__ uint4 rows[2][64 * SLOTS];
   __shared__ float gate[2][64];
   __shared__ int blocks_of[2][QPS];             // blocks in a query's prefix
+  __shared__ int odd_step[2];                   // the step itself (from 1) if a query component is not finite
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int col = lane & 31, hf = lane >> 5, seq = blockIdx.z;
   const int q_first = blockIdx.y * steps * QPS;
   const int n_steps = min(steps, (p.n_q - q_first + QPS - 1) / QPS);
   const int b = (blockIdx.x * 4 + wave) * 32 + col;   // this lane's block
 
+  if (tid < 2) odd_step[tid] = 0;
   BFrag piece[3][8];
+  uint32_t odd_key = 0;                         // a component of this lane's block has no three pieces
   {
     const float* src = Kp + ((size_t)seq * p.M + min(b, p.M - 1)) * kD + hf * 8;
     float4 x[8][2];
@@ -132,14 +166,18 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         split_three(v[2 * j], v[2 * j + 1], piece[0][ks].w[j], piece[1][ks].w[j], piece[2][ks].w[j]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) odd_key |= exponents_full(piece[0][ks].w[j]);
     }
+    odd_key |= (uint32_t)__shfl_xor((int)odd_key, 32);
   }
 
   uint4 stage[4];
   float stage_gate = 0.f;
-  int stage_blocks = 0;
+  int stage_blocks = 0, stage_step = 0;
   auto load = [&](int step) {                   // rows of a step; missing queries and heads are zeros
     const int q0 = q_first + step * QPS;
+    stage_step = step + 1;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = tid + 256 * i, row = e >> 4, q = q0 + row / HS, head = row % HS;
@@ -155,16 +193,20 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
       stage_blocks = q0 + tid < p.n_q ? (int)(((long long)visible(p, seq, q0 + tid) + p.B - 1) / p.B) : 0;
   };
   auto store = [&](int buf) {
+    uint32_t odd = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int e = tid + 256 * i;
       rows[buf][(e >> 4) * SLOTS + (e & 15)] = stage[i];
+      odd |= exponents_full(stage[i].x) | exponents_full(stage[i].y) | exponents_full(stage[i].z) | exponents_full(stage[i].w);
     }
+    if (odd) odd_step[buf] = stage_step;
     if (tid < 64) gate[buf][tid] = stage_gate;
     if (tid < QPS) blocks_of[buf][tid] = stage_blocks;
   };
 
   load(0);
+  __syncthreads();                              // (odd_step is clear)
   store(0);
   __syncthreads();
   for (int step = 0; step < n_steps; ++step) {
@@ -205,7 +247,14 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
     // HS = 64: both row tiles are one query's, the lower half-wave stores; HS = 32: half-wave hf stores
     // the query of row tile hf
     const int q = q_first + step * QPS + (HS == 32 ? hf : 0);
-    const float total = HS == 64 ? sum[0] + sum[1] : hf ? sum[1] : sum[0];
+    float total = HS == 64 ? sum[0] + sum[1] : hf ? sum[1] : sum[0];
+    const bool odd = odd_key != 0 || odd_step[buf] == step + 1;
+    if (__builtin_amdgcn_ballot_w64(odd)) {
+      const int first = HS == 32 ? 32 * hf : 0;
+      if (odd)
+        total = block_score_plain(&rows[buf][first * SLOTS], SLOTS, &gate[buf][first], p.H,
+                                  Kp + ((size_t)seq * p.M + min(b, p.M - 1)) * kD);
+    }
     const int Mn = blocks_of[buf][HS == 32 ? hf : 0];
     if ((HS == 32 || hf == 0) && q < p.n_q && b < p.M)
       J[((size_t)seq * p.n_q + q) * p.M + b] = b >= Mn ? -INFINITY : (b == 0 || b == Mn - 1) ? INFINITY : total;

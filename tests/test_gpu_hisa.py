@@ -204,3 +204,45 @@ def test_block_scores_on_the_matrix_core(misa, n_q, H, L, B):
         inner = ~forced & ~none
         tol = 8 * 2.0 ** -24 * (128 + H) ** 0.5 * size
         assert bool(((J[s] - ref).abs() <= tol)[inner].all())
+
+
+@pytest.mark.parametrize("H", [64, 40, 32, 24])
+@pytest.mark.parametrize("what", ["key", "negative_gates", "large_key", "query"])
+def test_block_scores_of_infinite_components(misa, H, what):
+    """A block with an infinite component (or one above the largest bf16) and a query with an infinite
+    component score as their products say; every other block and query as without them.  One such
+    component per block or query, so that no dot product is infinity minus infinity."""
+    n_q, L, B = 5, 1000, 20
+    g = torch.Generator().manual_seed(H)
+    M = L // B
+    Kp = torch.randn(M, 128, generator=g) * 0.05
+    Q = (torch.randn(n_q, H, 128, generator=g) * 0.09).to(torch.bfloat16)
+    W = torch.rand(n_q, H, generator=g) + 0.1
+    if what == "query":
+        Q[2, 3, 17] = float("inf")
+        Q[4, H - 1, 100] = -float("inf")
+    else:
+        for i, b in enumerate((1, 7, 31, 32, 40, 48)):
+            Kp[b, (37 * i) % 128] = 3.4e38 if what == "large_key" else float("inf") if i % 2 else -float("inf")
+    if what == "negative_gates":
+        W = -W
+    if what == "large_key":
+        W *= 0.05                                # (the sums stay finite)
+    p = misa.Problem(1, L, n_q, H, B, 1, misa.BF16, misa.BF16, torch.full((n_q,), L - 1, dtype=torch.int32, device="cuda"))
+    idx = torch.empty(1, n_q, 2 * B, dtype=torch.int32, device="cuda")
+    ws = misa.alloc_workspace(p, misa.OP_HISA, 2)
+    misa.block_sparse_select(p, Q[None].cuda(), W[None].cuda().contiguous(), Kp[None].cuda(), 2, idx, None, ws)
+    torch.cuda.synchronize()
+    J = ws[:n_q * M * 4].view(torch.float32).view(n_q, M).double().cpu()
+    products = Q.double()[:, :, None, :] * Kp.double()[None, None]
+    terms = W.double()[:, :, None] * products.sum(-1).relu()
+    ref, size = terms.sum(1), (W.double().abs()[:, :, None] * products.abs().sum(-1)).sum(1)
+    assert not ref[:, 1:-1].isnan().any()
+    assert what == "large_key" or ref[:, 1:-1].isinf().any()
+    for q in range(n_q):
+        for b in range(1, M - 1):
+            r, got = ref[q, b].item(), J[q, b].item()
+            if abs(r) > 3.4e38:                  # infinite in fp32
+                assert got == float("inf") * np.sign(r), (q, b, got, r)
+            else:
+                assert abs(got - r) <= 8 * 2.0 ** -24 * (128 + H) ** 0.5 * size[q, b].item(), (q, b, got, r)
