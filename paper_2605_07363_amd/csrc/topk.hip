@@ -61,8 +61,9 @@ __host__ __device__ inline int sample_lines(int n, int k, int nt) {
   return nt == kTopkThreads && (n <= 8192 || k > 4096 || n > 131072) ? 512 : 256;
 }
 
-// LDS words of the bitmap of a row, which a histogram has to fit as well.
-__host__ __device__ inline int sel_words(int row_len) { return max((row_len + 31) / 32, kBins); }
+// LDS words of the bitmap of a row, which a histogram has to fit as well; even, because the list behind
+// it has 8-byte entries.
+__host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 31) / 32, kBins) + 1) & ~1; }
 
 // ---------------------------------------------------------------- sampled path
 //
