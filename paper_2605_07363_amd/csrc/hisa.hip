@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
   constexpr int QPS = 64 / HS;                  // queries per step
   constexpr int SLOTS = 17;                     // 16-byte slots per row in LDS: 16 and one of padding
   __shared__ uint4 rows[2][64 * SLOTS];
-  __shared__ float gate[2][64];
+  __shared__ __align__(16) float gate[2][64];
   __shared__ int blocks_of[2][QPS];             // blocks in a query's prefix
   __shared__ int odd_step[2];                   // the step itself (from 1) if a query component is not finite
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
