@@ -55,10 +55,12 @@ __device__ __forceinline__ void scan_row(const float* __restrict__ s, int lo, in
   }
 }
 
-// Sampled 16-element lines of a long row of n elements: about 4096 elements, 8192 for large k and very
-// long rows (they narrow the bracket, whose width in elements grows with sqrt(k n / samples)).
-__host__ __device__ inline int sample_lines(int n, int k, int nt) {
-  return nt == kTopkThreads && (n <= 8192 || k > 4096 || n > 131072) ? 512 : 256;
+// Sampled 16-element lines of the n visible elements of a long row of row_len: about 4096 elements, 8192 for
+// large k and where rows may be very long (they narrow the bracket, whose width in elements grows with
+// sqrt(k n / samples)).  row_len decides and not n: the list is sized for a row of row_len elements, and a
+// shorter one may not be sampled more coarsely.
+__host__ __device__ inline int sample_lines(int n, int row_len, int k, int nt) {
+  return nt == kTopkThreads && (n <= 8192 || k > 4096 || row_len > 131072) ? 512 : 256;
 }
 
 // LDS words of the bitmap of a row, which a histogram has to fit as well; even, because the list behind
@@ -121,12 +123,12 @@ __device__ __forceinline__ int linear_bin(float v, float from, float scale) {
 // `held` receives the thread's sample, `have` says which of it are elements; `also` is called once the
 // sample's loads have been issued.  Leaves hist cleared.
 template <int NT, bool SHORT, int HELD, typename F>
-__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int k, float (&held)[HELD],
+__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int row_len, int k, float (&held)[HELD],
                                                uint32_t& have, int* hist, TopkLds<NT>& L, Bracket& br, F also) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   have = 0;
-  const int lines = (n + 15) >> 4, max_lines = SHORT ? lines : sample_lines(n, k, NT);
+  const int lines = (n + 15) >> 4, max_lines = SHORT ? lines : sample_lines(n, row_len, k, NT);
   const int ls = (lines + max_lines - 1) / max_lines;
   const int groups = lines / ls;       // >= 1
   // (16-bit hash and ls <= 128: 24-bit products)
@@ -454,7 +456,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   uint32_t have;
   Bracket br = {0.f, 0.f, 0.f};
   Stream<NT, 2> st;
-  const bool ok = sample_bracket<NT, false>(s, n, k, held, have, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
+  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, held, have, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
   if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -540,7 +542,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
     } else if constexpr (KIND == kRowShort) {
       float held[held_short(NT)];
       uint32_t have;
-      if (sample_bracket<NT, true>(s, n, k, held, have, sample_hist, L, br, [] {})) {
+      if (sample_bracket<NT, true>(s, n, row_len, k, held, have, sample_hist, L, br, [] {})) {
 #pragma unroll
         for (int u = 0; u < held_short(NT); u += 8) {
           float x[8];
@@ -556,7 +558,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       float held[kHeldLong];
       uint32_t have;
       Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
-      if (sample_bracket<NT, false>(s, n, k, held, have, sample_hist, L, br, [&] { st.begin(s, n); })) {
+      if (sample_bracket<NT, false>(s, n, row_len, k, held, have, sample_hist, L, br, [&] { st.begin(s, n); })) {
         st.filter(br.lo, 0, list, cap, &L.list_fill);
         __syncthreads();
         listed = L.list_fill;
@@ -813,10 +815,11 @@ size_t topk_ws_bytes(const Prob& p, int k) {
 }
 
 // List entries of a row.  With one line of every ls sampled, about r_lo ls elements of the row reach the
-// lower threshold of topk_sampled (r_lo = k / ls + 6 sqrt(k / ls) + 8) and the number scatters by
-// ls sqrt(r_lo): six of those are added.  A short row lists little more than k.
+// lower end of sample_bracket (r_lo = k / ls + 6 sqrt(k / ls) + 8) and the number scatters by
+// ls sqrt(r_lo): six of those are added, also for a row that ends early, whose ls is no larger.  A short row
+// lists little more than k.
 static int pass_capacity(int row_len, int k, int nt, bool is_short) {
-  const int lines = (row_len + 15) / 16, max_lines = is_short ? lines : sample_lines(row_len, k, nt);
+  const int lines = (row_len + 15) / 16, max_lines = is_short ? lines : sample_lines(row_len, row_len, k, nt);
   const double ls = (lines + max_lines - 1) / max_lines, kf = k / ls;
   const double r = kf + 6.0 * std::sqrt(kf) + 8.0;
   return std::min((int)(ls * (r + (ls > 1 ? 6.0 * std::sqrt(r) : 56.0))), row_len);
