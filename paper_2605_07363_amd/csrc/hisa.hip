@@ -78,8 +78,9 @@ __global__ __launch_bounds__(256) void block_score_kernel(Prob p, const void* __
 // a key is lost; products are exact and added in fp32.  A wavefront keeps the pieces of 32 blocks in
 // registers (96) and the head rows of the queries pass through LDS, double buffered, shared by the four
 // wavefronts of the workgroup: a step is 64 (query, head) rows, HS = 64 or 32 head slots per query.
-// The pieces of an infinite (or larger than bf16) component are not numbers, and an infinity times a zero
-// piece or a zero head slot is none either: blocks with such a key and queries with such a component, found
+// The pieces of an infinite (or larger than bf16) component are not numbers, an infinity times a zero
+// piece or a zero head slot is none either, and of a product above the largest fp32 the pieces' products may
+// be infinities of both signs: blocks with such a key and queries with such a component, found
 // from the exponents of the operands, are scored by themselves in fp32, in the order of block_score_kernel.
 // Bound: 3 x 2 H 128 flop per (query, block).  1024 queries x 512 blocks x 64 heads: 33 us, 155 us with one
 // thread per block on the vector units; error of the scores against 64 bits 1.3e-7 (1.5e-7 before).
@@ -104,9 +105,10 @@ __device__ __forceinline__ void split_three(float x0, float x1, uint32_t& a, uin
   c = l.u;
 }
 
-// Whether one of the two bf16 values of a word has all exponent bits set (collected in bits 15 and 31).
-__device__ __forceinline__ uint32_t exponents_full(uint32_t w) {
-  return ((w & 0x7F807F80u) + 0x00800080u) & 0x80008000u;
+// Whether one of the two bf16 values of a word is 2^63 or more, infinite or not a number (in bits 15 and 31).
+// Products of smaller ones stay below 2^126 and those of the second and third piece, 128 of them added, too.
+__device__ __forceinline__ uint32_t exponents_large(uint32_t w) {
+  return ((w & 0x7F807F80u) + 0x21002100u) & 0x80008000u;
 }
 
 // The score of one block by itself: heads rows of a query in LDS, `slots` 16-byte pieces apart.
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
       for (int j = 0; j < 4; ++j)
         split_three(v[2 * j], v[2 * j + 1], piece[0][ks].w[j], piece[1][ks].w[j], piece[2][ks].w[j]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) odd_key |= exponents_full(piece[0][ks].w[j]);
+      for (int j = 0; j < 4; ++j) odd_key |= exponents_large(piece[0][ks].w[j]);
     }
     odd_key |= (uint32_t)__shfl_xor((int)odd_key, 32);
   }
@@ -198,7 +200,7 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
     for (int i = 0; i < 4; ++i) {
       const int e = tid + 256 * i;
       rows[buf][(e >> 4) * SLOTS + (e & 15)] = stage[i];
-      odd |= exponents_full(stage[i].x) | exponents_full(stage[i].y) | exponents_full(stage[i].z) | exponents_full(stage[i].w);
+      odd |= exponents_large(stage[i].x) | exponents_large(stage[i].y) | exponents_large(stage[i].z) | exponents_large(stage[i].w);
     }
     if (odd) odd_step[buf] = stage_step;
     if (tid < 64) gate[buf][tid] = stage_gate;

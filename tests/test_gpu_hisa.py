@@ -207,11 +207,12 @@ def test_block_scores_on_the_matrix_core(misa, n_q, H, L, B):
 
 
 @pytest.mark.parametrize("H", [64, 40, 32, 24])
-@pytest.mark.parametrize("what", ["key", "negative_gates", "large_key", "query"])
+@pytest.mark.parametrize("what", ["key", "negative_gates", "large_key", "query", "large_product"])
 def test_block_scores_of_infinite_components(misa, H, what):
-    """A block with an infinite component (or one above the largest bf16) and a query with an infinite
-    component score as their products say; every other block and query as without them.  One such
-    component per block or query, so that no dot product is infinity minus infinity."""
+    """A block with an infinite component (or one above the largest bf16), a query with an infinite
+    component and a finite product above the largest fp32 score as their products say; every other block and
+    query as without them.  One such component per block or query, so that no dot product is infinity minus
+    infinity (large_product: all components of a block have the sign of the query's and one is large)."""
     n_q, L, B = 5, 1000, 20
     g = torch.Generator().manual_seed(H)
     M = L // B
@@ -221,6 +222,10 @@ def test_block_scores_of_infinite_components(misa, H, what):
     if what == "query":
         Q[2, 3, 17] = float("inf")
         Q[4, H - 1, 100] = -float("inf")
+    elif what == "large_product":                # the key's nearest bf16 is above it: its second piece is negative
+        Q, Kp, W = Q.abs(), Kp.abs(), W * 0.05
+        Q[2] *= 1e6
+        Kp[7, 5] = Kp[31, 17] = 1.0085e38
     else:
         for i, b in enumerate((1, 7, 31, 32, 40, 48)):
             Kp[b, (37 * i) % 128] = 3.4e38 if what == "large_key" else float("inf") if i % 2 else -float("inf")
@@ -238,7 +243,7 @@ def test_block_scores_of_infinite_components(misa, H, what):
     terms = W.double()[:, :, None] * products.sum(-1).relu()
     ref, size = terms.sum(1), (W.double().abs()[:, :, None] * products.abs().sum(-1)).sum(1)
     assert not ref[:, 1:-1].isnan().any()
-    assert what == "large_key" or ref[:, 1:-1].isinf().any()
+    assert what == "large_key" or (ref[:, 1:-1].abs() > 3.4e38).any()
     for q in range(n_q):
         for b in range(1, M - 1):
             r, got = ref[q, b].item(), J[q, b].item()
