@@ -250,14 +250,15 @@ __global__ __launch_bounds__(256) void block_score_tile_kernel(Prob p, int steps
     // the query of row tile hf
     const int q = q_first + step * QPS + (HS == 32 ? hf : 0);
     float total = HS == 64 ? sum[0] + sum[1] : hf ? sum[1] : sum[0];
-    const bool odd = odd_key != 0 || odd_step[buf] == step + 1;
+    const int Mn = blocks_of[buf][HS == 32 ? hf : 0];
+    // (only blocks whose score is used: what lies behind a prefix may hold anything)
+    const bool odd = (odd_key != 0 || odd_step[buf] == step + 1) && b > 0 && b < Mn - 1;
     if (__builtin_amdgcn_ballot_w64(odd)) {
       const int first = HS == 32 ? 32 * hf : 0;
       if (odd)
         total = block_score_plain(&rows[buf][first * SLOTS], SLOTS, &gate[buf][first], p.H,
                                   Kp + ((size_t)seq * p.M + min(b, p.M - 1)) * kD);
     }
-    const int Mn = blocks_of[buf][HS == 32 ? hf : 0];
     if ((HS == 32 || hf == 0) && q < p.n_q && b < p.M)
       J[((size_t)seq * p.n_q + q) * p.M + b] = b >= Mn ? -INFINITY : (b == 0 || b == Mn - 1) ? INFINITY : total;
     store(buf ^ 1);
