@@ -251,3 +251,62 @@ def test_block_scores_of_infinite_components(misa, H, what):
                 assert got == float("inf") * np.sign(r), (q, b, got, r)
             else:
                 assert abs(got - r) <= 8 * 2.0 ** -24 * (128 + H) ** 0.5 * size[q, b].item(), (q, b, got, r)
+
+
+MANY = {
+    # from 1024 rows on the dense scores of up to 8192 candidates and their top-k are one kernel
+    "bf16": (small("c2", L=3001, n_q=1024, B=64, k=200, H=32, h=8), 9),
+    "fp8_keys": (small("c4", L=2500, n_q=1100, B=32, k=128, k_cand=0, H=64, needles=16), 12),
+    "two_sequences": (small("c2", n_seq=2, L=2777, n_q=513, B=100, k=300, H=40, h=8), 7),
+    "fp8_queries": (small("c4", n_seq=2, L=2000, n_q=512, B=64, k=64, k_cand=0, H=17, h=8, q_dtype="e4m3", needles=4), 5),
+    "8192_candidates": (small("c2", L=9000, n_q=1030, B=128, k=2048, H=8, h=8), 64),
+    "8256_candidates": (small("c2", L=9000, n_q=1030, B=129, k=2048, H=8, h=8), 64),
+    "k_of_all": (small("c2", L=600, n_q=1024, B=50, k=250, H=16, h=8), 5),
+}
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_many_rows_equal_their_queries_by_themselves(misa, name):
+    """All rows of a call, from queries that see one key to those that see all and of sequences of several
+    lengths, bit for bit against calls of at most 500 rows, and some rows against the oracle."""
+    wl, m = MANY[name]
+    n_q, seq_len = wl.n_q, (None if wl.n_seq == 1 else [wl.L, wl.L // 3])
+    inp = WL.make_inputs(wl, seed=41, seq_len=seq_len)
+    q_pos = np.unique(np.concatenate([np.arange(8), np.linspace(0, wl.L - 1, n_q - 8).astype(int)]))
+    q_pos = np.sort(np.concatenate([q_pos, np.full(n_q - len(q_pos), wl.L - 1)])).astype(np.int32)
+    inp["q_pos"] = q_pos
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    Kp = torch.empty((wl.n_seq, p.M, wl.d), dtype=torch.float32, device="cuda")
+    misa.pool_keys(p, dv["K"], dv["kscale"], Kp, misa.alloc_workspace(p, misa.OP_POOL))
+
+    def select(p, Q, W, Kp, K, kscale):
+        rows = (p.n_seq, p.n_q)
+        blocks = torch.full(rows + (m,), -9, dtype=torch.int32, device="cuda")
+        idx = torch.full(rows + (wl.k,), -9, dtype=torch.int32, device="cuda")
+        val = torch.full(rows + (wl.k,), 9.0, dtype=torch.float32, device="cuda")
+        misa.hisa_select(p, Q, W, Kp, K, kscale, m, wl.k, idx, val, blocks, misa.alloc_workspace(p, misa.OP_HISA, m))
+        torch.cuda.synchronize()
+        return blocks, idx, val
+
+    blocks, idx, val = select(p, dv["Q"], dv["W"], Kp, dv["K"], dv["kscale"])
+    for s in range(wl.n_seq):
+        one = None if p.seq_len is None else p.seq_len[s:s + 1].contiguous()
+        for t in range(0, n_q, 500):
+            part = misa.Problem(1, p.L, min(500, n_q - t), p.H, p.B, p.h, p.k_dtype, p.q_dtype, p.q_pos[t:t + 500].contiguous(), one)
+            b1, i1, v1 = select(part, dv["Q"][s:s + 1, t:t + 500].contiguous(), dv["W"][s:s + 1, t:t + 500].contiguous(), Kp[s:s + 1].contiguous(),
+                                dv["K"][s:s + 1].contiguous(), None if dv["kscale"] is None else dv["kscale"][s:s + 1].contiguous())
+            assert torch.equal(blocks[s:s + 1, t:t + 500], b1), (s, t)
+            assert torch.equal(idx[s:s + 1, t:t + 500], i1), (s, t)
+            assert torch.equal(val[s:s + 1, t:t + 500].view(torch.int32), v1.view(torch.int32)), (s, t)
+    some = np.unique(np.concatenate([[0, 1, 7, n_q - 1], np.random.default_rng(5).integers(0, n_q, 6)]))
+    few = dict(inp, wl=WL.scaled(wl, n_q=len(some)), Q=inp["Q"][:, some], W=inp["W"][:, some], q_pos=q_pos[some])
+    sel = lambda x: x.cpu().numpy()[:, some]
+    bs = np.full((wl.n_seq, len(some), m * wl.B), -1, dtype=np.int64)
+    for s in range(wl.n_seq):
+        for i, t in enumerate(some):
+            n = oracle_view(few, s, i)[3]
+            for j, b in enumerate(sel(blocks)[s, i]):
+                toks = np.arange(max(b, 0) * wl.B, min((b + 1) * wl.B, n)) if b >= 0 else np.arange(0)
+                bs[s, i, j * wl.B:j * wl.B + len(toks)] = toks
+    check(few, few["wl"], m, sel(blocks), sel(idx), sel(val), bs)
