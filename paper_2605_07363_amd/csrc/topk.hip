@@ -781,7 +781,7 @@ template <int NT, int KIND>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kTopkThreads ? 8 : 6, 8))) void topk_kernel(
     Prob p, const float* __restrict__ S, int row_len, int k, const int* __restrict__ map,
     int* __restrict__ idx, float* __restrict__ val, const int* __restrict__ pre, int cap, int list_cap, bool all_slots) {
-  extern __shared__ uint32_t dyn[];
+  extern __shared__ __align__(16) uint32_t dyn[];
   // queries in descending order: under a causal mask the late ones have the longest rows, and
   // the workgroups with the most work should start first
   topk_row<NT, KIND>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, gridDim.x - 1 - blockIdx.x, blockIdx.y,
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_only_kernel(Prob p, const f
                                                                  int k, int* __restrict__ idx,
                                                                  float* __restrict__ val, int cap,
                                                                  int list_cap, const int* __restrict__ only) {
-  extern __shared__ uint32_t dyn[];
+  extern __shared__ __align__(16) uint32_t dyn[];
   const int rows = p.n_seq * p.n_q;
   for (int r = blockIdx.x; r < rows; r += gridDim.x) {
     if (!only[r]) continue;
