@@ -816,13 +816,13 @@ size_t topk_ws_bytes(const Prob& p, int k) {
 
 // List entries of a row.  With one line of every ls sampled, about r_lo ls elements of the row reach the
 // lower end of sample_bracket (r_lo = k / ls + 6 sqrt(k / ls) + 8) and the number scatters by
-// ls sqrt(r_lo): six of those are added, also for a row that ends early, whose ls is no larger.  A short row
+// ls sqrt(r_lo): `sd` of those are added, also for a row that ends early, whose ls is no larger.  A short row
 // lists little more than k.
-static int pass_capacity(int row_len, int k, int nt, bool is_short) {
+static int pass_capacity(int row_len, int k, int nt, bool is_short, double sd) {
   const int lines = (row_len + 15) / 16, max_lines = is_short ? lines : sample_lines(row_len, row_len, k, nt);
   const double ls = (lines + max_lines - 1) / max_lines, kf = k / ls;
   const double r = kf + 6.0 * std::sqrt(kf) + 8.0;
-  return std::min((int)(ls * (r + (ls > 1 ? 6.0 * std::sqrt(r) : 56.0))), row_len);
+  return std::min((int)(ls * (r + (ls > 1 ? sd * std::sqrt(r) : 56.0))), row_len);
 }
 
 hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const int* map, int* idx,
@@ -836,8 +836,8 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
   const bool split = !map && !all_slots && !only && use_split(p);
   size_t lds = 0;
   int cap = 0;
-  auto fits = [&](int nt, size_t most) {
-    cap = pass_capacity(row_len, k, nt, is_short);
+  auto fits = [&](int nt, size_t most, double sd = 6.0) {
+    cap = pass_capacity(row_len, k, nt, is_short, sd);
     lds = (size_t)sel_words(row_len) * 4 + (size_t)(cap + 64) * 8 + (size_t)((row_len + 31) / 32) * 2;
     return lds <= most;
   };
@@ -846,7 +846,8 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
   if (is_short) fits(nt, kLdsMost);
   else if (split || only || (long long)p.n_q * p.n_seq < 512 || !fits(nt = 512, 53 * 1024)) {
     nt = kTopkThreads;
-    if (!fits(nt, kLdsMost)) cap = 0;              // (k well above 8192: the two-pass path)
+    // the longest rows have room for half the reserve; k well above 8192: the two-pass path
+    if (!fits(nt, kLdsMost) && !fits(nt, kLdsMost, 3.0)) cap = 0;
   }
   // the two-pass path shares the region: histogram and list, or a second bitmap
   const int list_cap = std::min(row_len, is_short || nt == 512 ? std::max((int)(lds / 8) - sel_words(row_len) / 2 - kBins / 2, 1) : kListTarget);

@@ -53,6 +53,11 @@ def listed(misa, x, k, n=None):
     return np.array(out)
 
 
+def test_the_longest_rows_are_listed(misa):
+    got = listed(misa, np.random.default_rng(9).standard_normal((4, 524288)).astype(np.float32), 2048)
+    assert (got >= 2048).all(), got
+
+
 def test_rows_that_end_early_are_sampled_as_finely_as_the_list_expects(misa):
     x = np.random.default_rng(3).standard_normal((48, 140000)).astype(np.float32)
     k = 2048
