@@ -10,6 +10,15 @@ namespace misa {
 constexpr int kTopkThreads = 1024;
 constexpr int kBins = 2048;
 
+// The thread's number in the block as a value that the compiler does not compute ahead with: addresses kept
+// from one search for a later one, or from one attempt at a row for the next, cost the registers of the loads
+// in flight.
+__device__ __forceinline__ int this_thread() {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  return tid;
+}
+
 // Finds the digit d (scanning from the top) with count(digit > d) < need <= count(digit >= d).
 // A block of NT threads, the histogram complete; thread i owns the 2048 / NT bins from
 // 2047 - i * 2048 / NT downwards.  Writes {d, need - count(digit > d), hist[d]} to out
@@ -18,10 +27,11 @@ constexpr int kBins = 2048;
 // need2 > 0: the digit for a second count is searched in the same scan and written to out2.
 template <int NT>
 __device__ __forceinline__ void find_threshold_bin_n(const int* hist, int need, int* scan_scratch,
-                                                     int* out, int need2 = 0, int* out2 = nullptr) {
+                                                     int* out, int need2 = 0, int* out2 = nullptr,
+                                                     int tid = threadIdx.x) {
   constexpr int BPT = kBins / NT, NW = NT / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int top = kBins - 1 - BPT * (int)threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int top = kBins - 1 - BPT * tid;
   int* wave_total = scan_scratch + 16;
   int h[BPT], sum = 0;
 #pragma unroll

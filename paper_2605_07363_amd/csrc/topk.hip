@@ -7,12 +7,12 @@
 // prefix sum, so the output is ascending and bit-reproducible without a sort.
 //
 // Usual case (sampled path): the row is read once.  A sample of the row brackets the k-th largest
-// value between two thresholds; while the row streams through registers everything above the
-// upper one goes to the bitmap straight from ballots, and only the few elements between the two
-// are listed and selected from exactly.  The counts found on the way prove the bracket right or
-// wrong, so the result never depends on the sample: a row whose bracket fails (or whose values
-// repeat so much that the list overflows) is redone by the radix select on the row itself, which
-// reads it twice (or four times if the values around the k-th are heavily repeated).
+// value between two thresholds; while the row streams through registers the elements above the
+// lower one are listed, and the list is selected from exactly.  The counts found on the way prove
+// the bracket right or wrong, so the result never depends on the sample: a row whose list is too short
+// or too long gets another bracket from the count of the first, a row whose k-th largest lies on a plateau
+// of equal values is marked in one more pass, and what is left (NaN, further wrong brackets) is redone
+// by the radix select on the row itself, which reads it twice or four times.
 #include <algorithm>
 #include <cfloat>
 #include <cmath>
@@ -31,6 +31,8 @@ constexpr int kListTarget = 6000;    // boundary list entries of the two-pass pa
 // thread stays in registers and is its own sample.  Otherwise the row is streamed and at most eight
 // elements per thread are sampled.
 constexpr int kHeldLong = 8;
+constexpr int kAttempts = 4;         // further brackets tried on a row
+__host__ __device__ constexpr int held_hard(int nt) { return nt == 256 ? 16 : 8; }
 __host__ __device__ constexpr int held_short(int nt) { return nt == 256 ? 16 : 8; }
 
 // Visits elements lo..hi-1 of a row with all threads of the block.  Eight
@@ -72,10 +74,12 @@ __host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 3
 //   sample   16-element lines, one of every `ls` at a hashed place (the short rows of the smaller
 //            blocks are their own sample and stay in registers).  The k-th largest of the row lies
 //            between the sample elements of rank r_hi and r_lo = k m/n -+ (6 sqrt(k m/n) + 8): the
-//            number of the top k in the sample has mean k m/n and no larger variance.  Both are
-//            found by a histogram that is linear between the smallest and the largest sample, again
-//            on the bins around them where outliers left these too coarse, and rounded outwards to
-//            the values lo and hi of the bracket.
+//            number of the top k in the sample has mean k m/n and, if the elements of a line are
+//            independent, no larger variance (lines of like elements: up to 16 times; see "again").
+//            Both are found by a histogram that is linear between the smallest and the largest
+//            sample and rounded outwards to the values lo and hi of the bracket.  Where outliers leave
+//            the bin of lo too coarse it is repeated inside that bin, then (hard_row) cut by digits of
+//            the key until few samples are left in it, or one value.
 //   stream   Elements >= lo (and NaN) go to the list, at places counted from the ballots of the
 //            compares; a wavefront claims the places of eight ballots with one atomic: five vector
 //            instructions per 64 elements.  (At the 6 TB/s of the memory a CU has time for that many
@@ -89,8 +93,10 @@ __host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 3
 //            entries in the bin of the need-th are ranked against each other, or, if there are many
 //            (repeated values), resolved by the digits of key and index.
 //
-// The row is left to the two-pass path if sure > k, or fewer than k or more than the list holds pass, or
-// a NaN turns up.  Candidate rows never select -inf: it lies below the bracket.
+//   again    If sure > k, the upper end is dropped.  If fewer than k or more than the list holds pass, the
+//            row is sampled and streamed again with the rank r_lo scaled by what the last count says of it.
+//            One value: hard_row marks what lies above it and the first of it.
+// A NaN leaves the row to the two-pass path.  Candidate rows never select -inf: it lies below the bracket.
 // The histograms share their LDS with the bitmap, which is cleared once the last of them has been read.
 //
 // Measured: 4096 rows of 65536, k = 2048: 212 us = 5.1 TB/s (two passes over each row: 402 us; sample and
@@ -100,6 +106,7 @@ struct Bracket {
   float lo, hi;
   float edge;   // upper end of the histogram: hi where it is finite
 };
+enum Found { kNoBracket, kBracket, kPlateau };   // kPlateau: the lower end is one value that repeats
 
 // What the phases of a block share.
 template <int NT>
@@ -107,7 +114,7 @@ struct TopkLds {
   int scan_scratch[32];
   int thr[3], thr_up[3];
   int list_fill, few_len, nan_seen;
-  int wave_sure[NT / 64];
+  int wave_sure[NT / 64], wave_more[NT / 64];
   float wave_min[NT / 64], wave_max[NT / 64];
   uint32_t fkey[kFew];
   int fidx[kFew];
@@ -119,74 +126,178 @@ __device__ __forceinline__ int linear_bin(float v, float from, float scale) {
   return (int)__builtin_amdgcn_fmed3f((v - from) * scale, 0.f, (float)(kBins - 1));
 }
 
-// The bracket of a row's k-th largest of n > k elements; false if the sample gives none (block-uniform).
-// `held` receives the thread's sample, `have` says which of it are elements; `also` is called once the
-// sample's loads have been issued.  Leaves hist cleared.
+// Value of a key (the inverse of order_key; a key between those of -0 and +0 gives -0).
+__device__ __forceinline__ float key_value(uint32_t key) {
+  return __uint_as_float(key & 0x80000000u ? key ^ 0x80000000u : ~key);
+}
+constexpr uint32_t kKeyPosInf = 0xFF800000u;
+
+// Counts bins in an LDS histogram: U of each lane (all active; bin_of(u) < 0: none).  LDS adds of a wavefront to
+// one address go one after the other, so where the first lane's bin is that of a quarter of the lanes (far outliers,
+// plateaus) its count is taken from ballots and added once.
+template <int U, typename F>
+__device__ __forceinline__ void count_bins(int* hist, F bin_of) {
+  const int first = __builtin_amdgcn_readfirstlane(bin_of(0));
+  if (__popcll(__builtin_amdgcn_ballot_w64(bin_of(0) == first)) >= 16 && first >= 0) {   // wavefront-uniform
+    int same = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int bin = bin_of(u);
+      same += __popcll(__builtin_amdgcn_ballot_w64(bin == first));
+      if (bin >= 0 && bin != first) atomicAdd(&hist[bin], 1);
+    }
+    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], same);
+  } else {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int bin = bin_of(u);
+      if (bin >= 0) atomicAdd(&hist[bin], 1);
+    }
+  }
+}
+
+// The sample of a row of n elements: of every ls lines one, HELD elements per thread (-inf where there is none).
+struct Sample {
+  int m, ls;          // sample elements; lines per sampled line
+  int r_lo, r_hi;     // ranks of the bracket's ends in the sample
+  int rank_up;        // rank of the upper end of the histogram of the list
+  int spare;          // samples past the r_lo-th that the list has room for
+};
 template <int NT, bool SHORT, int HELD, typename F>
-__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int row_len, int k, float (&held)[HELD],
-                                               uint32_t& have, int* hist, TopkLds<NT>& L, Bracket& br, F also) {
-  constexpr int NW = NT / 64;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  have = 0;
+__device__ __forceinline__ Sample take_sample(const float* __restrict__ s, int n, int row_len, int k, int cap, int tid,
+                                              float (&held)[HELD], F also) {
+  Sample sm;
   const int lines = (n + 15) >> 4, max_lines = SHORT ? lines : sample_lines(n, row_len, k, NT);
   const int ls = (lines + max_lines - 1) / max_lines;
   const int groups = lines / ls;       // >= 1
   // (16-bit hash and ls <= 128: 24-bit products)
   auto line_of = [&](uint32_t g) { return (int)(__umul24(g, ls) + (__umul24((g * 2654435761u) >> 16, ls) >> 16)); };
+  uint32_t none = 0;
 #pragma unroll
   for (int u = 0; u < HELD; ++u) {
     const int smp = tid + u * NT, g = smp >> 4;
     const int i = SHORT ? smp : line_of(g) * 16 + (smp & 15);
     const bool in = (SHORT || g < groups) && i < n;
-    have |= in ? 1u << u : 0u;
     held[u] = s[in ? i : 0];
+    none |= in ? 0u : 1u << u;
   }
   also();
-  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
-  if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
-  if (tid < kFew) L.frank[tid] = 0;
   // number of samples: 16 per sampled line, less what the row's last line lacks if it is one
   int m = 16 * groups;
   {
     const int last = lines - 1, g = last / ls;
     if (g < groups && line_of(g) == last) m -= 16 * lines - n;
   }
-  int r_lo = k, r_hi = k;
+  sm.m = m;
+  sm.ls = ls;
+  sm.r_lo = sm.r_hi = k;
   if (ls > 1) {
     const float kf = (float)k * (float)m / (float)n, margin = 6.f * sqrtf(kf) + 8.f;
-    r_lo = (int)ceilf(kf + margin);
-    r_hi = (int)floorf(kf - margin);
+    sm.r_lo = (int)ceilf(kf + margin);
+    sm.r_hi = (int)floorf(kf - margin);
   }
-  if (r_lo > m) return false;           // (block-uniform, as every early return here)
-  float lo = INFINITY, hi = -INFINITY;
+  sm.spare = ls == 1 ? (cap - k) / 2 : (int)(3.f * sqrtf((float)sm.r_lo));
+  sm.rank_up = sm.r_hi >= 1 ? sm.r_hi : max(sm.r_lo / 16, 1);   // (hi open: the histogram ends above most of the top k)
 #pragma unroll
-  for (int u = 0; u < HELD; ++u)
-    if (((have >> u) & 1) && fabsf(held[u]) < INFINITY) { lo = fminf(lo, held[u]); hi = fmaxf(hi, held[u]); }
-  lo = -wave_max_f32(-lo);
-  hi = wave_max_f32(hi);
-  if (lane == 0) { L.wave_min[wave] = lo; L.wave_max[wave] = hi; }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
+  for (int u = 0; u < HELD; ++u) held[u] = (none >> u) & 1 ? -INFINITY : held[u];
+  return sm;
+}
+
+// The bracket of a row's k-th largest of n > k elements (block-uniform) from a histogram of the sample that is
+// linear between the smallest and the largest one (masks and the like left out: below they are not counted, above
+// they share the last bin), and while that is too coarse (far outliers, heavy tails) from a second and a third one
+// between those of the r_lo-th sample's bin; false if the third is, too.  `cap`: what the list holds.  `also` is
+// called once the sample's loads have been issued.  Leaves hist cleared if there is a bracket.
+template <int NT, bool SHORT, int HELD, typename F>
+__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int row_len, int k, int cap,
+                                               float (&held)[HELD], Sample& sm, int* hist, TopkLds<NT>& L, Bracket& br,
+                                               F also) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  sm = take_sample<NT, SHORT>(s, n, row_len, k, cap, tid, held, [&] {
+    also();
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+    if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
+    if (tid < kFew) L.frank[tid] = 0;
+  });
+  if (sm.r_lo > sm.m) return false;
+  float from = -1e30f, to = 1e30f;
+#pragma unroll 1
   for (int pass = 0;; ++pass) {
-    const float width = (hi - lo) * (1.f / kBins), per = (float)kBins / (hi - lo);
-    if (!(width > 0.f) || !(per < 3e38f) || !(per > 0.f)) return false;
+    float lo = INFINITY, hi = -INFINITY;
 #pragma unroll
     for (int u = 0; u < HELD; ++u)
-      if ((have >> u) & 1) atomicAdd(&hist[linear_bin(held[u], lo, per)], 1);
+      if (held[u] >= from && held[u] <= to) { lo = fminf(lo, held[u]); hi = fmaxf(hi, held[u]); }
+    lo = -wave_max_f32(-lo);
+    hi = wave_max_f32(hi);
+    if (lane == 0) { L.wave_min[wave] = lo; L.wave_max[wave] = hi; }
+    if (tid == 0) L.thr[2] = 0;
     __syncthreads();
-    find_threshold_bin_n<NT>(hist, r_lo, L.scan_scratch, L.thr, max(r_hi, 1), L.thr_up);
-    const int b_lo = L.thr[0], b_hi = L.thr_up[0];
-    const int crowd = max(L.thr[2], L.thr_up[2]);
-    // (never -inf, which pads the list appends: a row's lowest finite values may be in the bracket)
-    br.lo = fmaxf(lo + ((float)b_lo - 0.02f) * width, -FLT_MAX);
-    br.edge = lo + ((float)b_hi + 1.02f) * width;
-    br.hi = r_hi >= 1 ? br.edge : INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
+    const float width = (hi - lo) * (1.f / kBins), per = (float)kBins / (hi - lo);
+    if (!(width > 0.f) || !(per < 3e38f)) return false;
+    count_bins<HELD>(hist, [&](int u) { return held[u] >= lo ? linear_bin(held[u], lo, per) : -1; });
+    __syncthreads();
+    find_threshold_bin_n<NT>(hist, sm.r_lo, L.scan_scratch, L.thr, sm.rank_up, L.thr_up, this_thread());
+    const int b_lo = L.thr[0], b_hi = L.thr_up[0], crowd = L.thr[2], rest = crowd - L.thr[1];
+    if (crowd == 0) return false;   // the r_lo-th sample lies below lo (the threshold was not written)
+    // rounding of the bins: 2048 x 2^-22 of one, and what lo and hi have lost by their size
+    const float slack = 0.001f * width + 2.5e-7f * fmaxf(fabsf(lo), fabsf(hi));
+    br.lo = fmaxf(lo + (float)b_lo * width - slack, -FLT_MAX);   // (never -inf, which pads the list appends)
+    const float edge = lo + (float)(b_hi + 1) * width + slack;
+    br.edge = pass == 0 || b_hi < kBins - 1 ? edge : br.edge;
+    br.hi = sm.r_hi >= 1 ? br.edge : INFINITY;
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;   // (read by everybody: find_threshold_bin ends with a barrier)
     __syncthreads();
-    if (crowd <= 64 || pass == 2) return true;
-    lo = br.lo;
-    hi = br.edge;
+    if (rest <= sm.spare) return true;
+    if (pass == 2) return false;
+    from = br.lo;
+    to = b_lo == kBins - 1 ? INFINITY : lo + (float)(b_lo + 1) * width + slack;
+  }
+}
+
+// The same by digits of the key, 11 bits each time until few samples are left beside the r_lo-th, or one value.
+template <int NT, int HELD>
+__device__ __forceinline__ Found key_bracket(const Sample& sm, const float (&held)[HELD], int* hist,
+                                             TopkLds<NT>& L, Bracket& br) {
+  constexpr int NW = NT / 64;
+  const int tid = this_thread(), lane = tid & 63, wave = tid >> 6;
+  if (sm.r_lo > sm.m) return kNoBracket;
+  __syncthreads();
+  zero_hist_n<NT>(hist);
+  uint32_t key_lo = order_key(-FLT_MAX), key_hi = kKeyPosInf;   // key range of the r_lo-th sample
+  br.hi = br.edge = INFINITY;
+#pragma unroll 1
+  for (;;) {
+    const int sh = max(21 - (int)__clz(key_hi - key_lo), 0);
+    auto digit = [&](uint32_t key) { return key >= key_lo && key <= key_hi ? (int)((key - key_lo) >> sh) : -1; };
+    int above = 0;
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) above += order_key(held[u]) > key_hi ? 1 : 0;
+    count_bins<HELD>(hist, [&](int u) { return digit(order_key(held[u])); });
+    above = wave_inclusive_scan(above);
+    if (lane == 63) L.wave_sure[wave] = above;
+    if (tid == 0) L.thr[2] = 0;
+    __syncthreads();
+    waves_before(L.wave_sure, NW, &above);
+    const int r = sm.r_lo - above;
+    find_threshold_bin_n<NT>(hist, r, L.scan_scratch, L.thr, sm.rank_up - above, L.thr_up, this_thread());
+    const int b_lo = L.thr[0], crowd = L.thr[2], rest = crowd - L.thr[1];
+    if (r < 1 || crowd == 0) return kNoBracket;   // the r_lo-th sample is infinite
+    if (sm.rank_up - above >= 1) {
+      br.edge = key_value(min(key_lo + ((uint32_t)(L.thr_up[0] + 1) << sh), kKeyPosInf));
+      br.hi = sm.r_hi >= 1 ? br.edge : INFINITY;
+    }
+    key_lo += (uint32_t)b_lo << sh;
+    key_hi = min(key_hi, key_lo + ((1u << sh) - 1u));
+    br.lo = key_value(key_lo);
+    if (key_lo == kKeyPosInf) return kPlateau;
+    br.edge = fmaxf(br.edge, key_value(key_lo + 1));
+    for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+    __syncthreads();
+    if (rest <= sm.spare) return kBracket;
+    if (sh == 0) return kPlateau;
   }
 }
 
@@ -279,37 +390,44 @@ struct Stream {
 // The top k of a row of n elements from the list of those that reach br.lo into the bitmap sel (whose
 // LDS is hist, cleared, before).  false: see above.
 template <int NT>
-__device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, const Bracket& br,
+__device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, Bracket br,
                                               uint32_t* sel, TopkLds<NT>& L) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int* hist = reinterpret_cast<int*>(sel);
   auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
-  const float fine = (float)kBins / (br.edge - br.lo);   // entries above share the last bin
+  const float fine = fminf(fmaxf((float)kBins / (br.edge - br.lo), 1e-35f), 3e38f);   // entries above share the last bin
   if (listed < k || listed > cap) return false;
-  int sure = 0;
-  bool nan = false;
-  for (int j0 = 0; j0 < listed; j0 += NT) {
-    const int j = j0 + tid;
-    const bool live = j < listed;
-    const float x = live ? __uint_as_float(list[j].x) : 0.f;
-    nan |= x != x;
-    sure += __popcll(__builtin_amdgcn_ballot_w64(live && x >= br.hi));
-    if (live && x < br.hi) atomicAdd(&hist[linear_bin(x, br.lo, fine)], 1);
+  int need;
+  for (;;) {
+    int sure = 0;
+    bool nan = false;
+    for (int j0 = 0; j0 < listed; j0 += NT) {
+      const int j = j0 + tid;
+      const bool live = j < listed;
+      const float x = live ? __uint_as_float(list[j].x) : 0.f;
+      nan |= x != x;
+      sure += __popcll(__builtin_amdgcn_ballot_w64(live && x >= br.hi));
+      if (live && x < br.hi) atomicAdd(&hist[linear_bin(x, br.lo, fine)], 1);
+    }
+    if (nan) L.nan_seen = 1;
+    if (lane == 0) L.wave_sure[wave] = sure;
+    __syncthreads();
+    if (L.nan_seen) return false;
+    int total_sure;
+    waves_before(L.wave_sure, NT / 64, &total_sure);
+    need = k - total_sure;
+    if (need >= 0) break;
+    if (br.hi == INFINITY) return false;                 // more than k infinite entries
+    br.hi = INFINITY;                                    // (the others share the last bin, which is resolved by digits)
+    __syncthreads();
+    zero_hist_n<NT>(hist);
   }
-  if (nan) L.nan_seen = 1;
-  if (lane == 0) L.wave_sure[wave] = sure;
-  __syncthreads();
-  if (L.nan_seen) return false;
-  int total_sure;
-  waves_before(L.wave_sure, NT / 64, &total_sure);
-  int need = k - total_sure;
-  if (need < 0) return false;
-  find_threshold_bin_n<NT>(hist, max(need, 1), L.scan_scratch, L.thr);
+  find_threshold_bin_n<NT>(hist, max(need, 1), L.scan_scratch, L.thr, this_thread());
   const int b = need > 0 ? L.thr[0] : kBins;             // need == 0: the sure ones are all
   int few = need > 0 ? L.thr[2] : 0;
   // A crowded bin (the bracket of a row with far outliers is wide) is cut into 2048 finer ones.  rank of an
   // entry against the need-th: 2 above, 1 undecided, 0 below.
-  const float from2 = br.lo + (float)b / fine, fine2 = fine * (float)kBins;
+  const float from2 = br.lo + (float)b / fine, fine2 = fminf(fine * (float)kBins, 3e38f);
   int b2 = -1;
   auto side = [&](float x) {
     const int d = x >= br.hi ? kBins + 1 : linear_bin(x, br.lo, fine);
@@ -326,7 +444,7 @@ __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int
       if (side(x) == 1) atomicAdd(&hist[linear_bin(x, from2, fine2)], 1);
     }
     __syncthreads();
-    find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr);
+    find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr, 0, nullptr, this_thread());
     b2 = L.thr[0];
     few = L.thr[2];
   }
@@ -348,7 +466,7 @@ __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int
         if (low + bits == 52 || (r >> (low + bits)) == prefix) atomicAdd(&hist[(int)(r >> low) & ((1 << bits) - 1)], 1);
       }
       __syncthreads();
-      find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr);
+      find_threshold_bin_n<NT>(hist, need, L.scan_scratch, L.thr, 0, nullptr, this_thread());
       prefix = (prefix << bits) | (uint64_t)L.thr[0];
       need = L.thr[1];
     }
@@ -441,7 +559,7 @@ __host__ __device__ inline int range_len(int L) {
 }
 
 __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, const float* __restrict__ S, int k,
-                                                                      int rlen, int* __restrict__ pre) {
+                                                                      int rlen, int cap, int* __restrict__ pre) {
   constexpr int NT = kTopkThreads;
   __shared__ int hist[kBins];
   __shared__ TopkLds<NT> L;
@@ -453,10 +571,10 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   const float* s = S + row * p.L;
   int* seg = pre + (row * gridDim.x + range) * kSegInts;
   float held[kHeldLong];
-  uint32_t have;
   Bracket br = {0.f, 0.f, 0.f};
   Stream<NT, 2> st;
-  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, held, have, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
+  Sample sm;
+  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, cap, held, sm, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
   if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -467,19 +585,21 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   }
 }
 
-// The segments of a row's ranges into the list; returns its length, or -1 if there is no bracket or a
-// segment or the list overflowed.  Wavefront w takes range w.
-__device__ __forceinline__ int gather_segments(const int* __restrict__ segs, int ranges, uint2* list, int cap, Bracket& br) {
+// The segments of a row's ranges into the list; returns how many elements passed, or -1 if there is no
+// bracket.  whole: no segment overflowed, nor the list.  Wavefront w takes range w.
+__device__ __forceinline__ int gather_segments(const int* __restrict__ segs, int ranges, uint2* list, int cap, Bracket& br,
+                                               bool& whole) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int cnt = lane < ranges ? segs[(size_t)lane * kSegInts] : 0;
   br.lo = __int_as_float(segs[8]);
   br.hi = __int_as_float(segs[9]);
   br.edge = __int_as_float(segs[10]);
-  const bool bad = __ballot(cnt < 0 || cnt > kSegCap) != 0;
   const int end = row16_inclusive_scan(cnt);             // (kMaxRanges = 16 lanes matter)
   const int total = __builtin_amdgcn_readlane(end, 15);
-  if (bad || total > cap) return -1;
+  whole = __ballot(cnt < 0 || cnt > kSegCap) == 0 && total <= cap;
+  if (__ballot(cnt < 0) != 0) return -1;
+  if (!whole) return total;
   if (wave < ranges) {
     const int mine = __builtin_amdgcn_readlane(cnt, wave), at = __builtin_amdgcn_readlane(end, wave) - mine;
     const uint2* src = reinterpret_cast<const uint2*>(segs + (size_t)wave * kSegInts + 64);
@@ -496,86 +616,81 @@ __device__ __forceinline__ int gather_segments(const int* __restrict__ segs, int
 }
 
 // ---------------------------------------------------------------- per-row kernel
-enum { kRowShort, kRowLong, kRowListed };   // held in registers / streamed / listed by topk_prefilter_kernel
+enum { kRowShort, kRowLong, kRowListed, kRowPlain };   // held in registers / streamed / listed by topk_prefilter_kernel / two passes
 
-template <int NT, int KIND>
-__device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict__ S, int row_len,
-                                         int k, const int* __restrict__ map, int* __restrict__ idx,
-                                         float* __restrict__ val, const int* __restrict__ pre, int cap,
-                                         int list_cap, int t, int seq, uint32_t* dyn, bool all_slots = false) {
-  // dyn: sel bitmap (sampled path: and its histograms), then the list of the sampled path, or the two-pass
-  // path's histogram and its eq bitmap OR list (keys, idx)
-  __shared__ TopkLds<NT> L;
-  __shared__ int list_len;
+// The `need` lowest-index elements of the bitmap eq into sel (words are owned by one thread here).
+template <int NT>
+__device__ __forceinline__ void mark_lowest(const uint32_t* eq, uint32_t* sel, int nwords, int need, int* scan_scratch) {
+  const int tid = threadIdx.x;
+  const int wpt = (nwords + NT - 1) / NT;
+  const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
+  int cnt = 0;
+  for (int w = w_lo; w < w_hi; ++w) cnt += __popc(eq[w]);
+  int total;
+  int before = block_exclusive_scan(cnt, scan_scratch, &total);
+  for (int w = w_lo; w < w_hi && before < need; ++w) {
+    uint32_t bits = eq[w];
+    const int c = __popc(bits);
+    int take = min(c, need - before);
+    before += c;
+    uint32_t kept = 0;
+    if (take == c) kept = bits;
+    else
+      while (take-- > 0) {
+        const uint32_t low = bits & (0u - bits);
+        kept |= low;
+        bits ^= low;
+      }
+    sel[w] |= kept;
+  }
+  __syncthreads();
+}
+
+// The marked elements of a row in index order.
+template <int NT>
+__device__ __forceinline__ void write_marked(const float* __restrict__ s, int n, int k, const uint32_t* sel, int* scan_scratch,
+                                             const int* __restrict__ map, int* __restrict__ out_idx, float* __restrict__ out_val) {
+  const int tid = threadIdx.x, nwords = (n + 31) / 32;
+  const int wpt = (nwords + NT - 1) / NT;
+  const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
+  int cnt = 0;
+  for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
+  int total;
+  int pos = block_exclusive_scan(cnt, scan_scratch, &total);
+  for (int w = w_lo; w < w_hi; ++w) {
+    uint32_t bits = sel[w];
+    while (bits) {
+      const int i = w * 32 + __ffs(bits) - 1;
+      bits &= bits - 1;
+      if (pos < k) {  // always true when the selection is consistent
+        out_idx[pos] = map ? map[i] : i;
+        if (out_val) out_val[pos] = s[i];
+      }
+      ++pos;
+    }
+  }
+}
+
+// The top k of a row by the radix select on the row itself.  skip_lowest: -inf is never selected.
+template <int NT>
+__device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n, int row_len, int k, const int* __restrict__ map,
+                                             int* __restrict__ out_idx, float* __restrict__ out_val, int list_cap,
+                                             bool skip_lowest, uint32_t* dyn, TopkLds<NT>& L) {
+  // dyn: sel bitmap, histogram, then eq bitmap OR list (keys, idx)
   int* const scan_scratch = L.scan_scratch;
   int* const thr = L.thr;
-
   const int tid = threadIdx.x;
-  const size_t row = (size_t)seq * p.n_q + t;
-  const float* s = S + row * row_len;
-  const int n = (map || all_slots) ? row_len : visible(p, seq, t);
   uint32_t* sel = dyn;
   uint32_t* region = dyn + sel_words(row_len);
   int* hist = reinterpret_cast<int*>(region);
-  uint32_t* eq = region + kBins;         // two-pass path
-  uint32_t* lkey = region + kBins;       // its list (aliases eq)
+  uint32_t* eq = region + kBins;
+  uint32_t* lkey = region + kBins;       // (aliases eq)
   int* lidx = reinterpret_cast<int*>(lkey + list_cap);
   const int nwords = (n + 31) / 32;
-  int* out_idx = idx + row * k;
-  float* out_val = val ? val + row * k : nullptr;
-
-  if (k < n && cap > 0) {
-    bool done = false;
-    uint2* list = reinterpret_cast<uint2*>(region);
-    uint16_t* before = reinterpret_cast<uint16_t*>(list + cap + 64);
-    int listed = 0;
-    int* sample_hist = reinterpret_cast<int*>(sel);
-    Bracket br;
-    if constexpr (KIND == kRowListed) {
-      const int rlen = range_len(row_len), ranges_row = (row_len + rlen - 1) / rlen;
-      for (int i = tid; i < kBins; i += NT) sample_hist[i] = 0;
-      if (tid == 0) { L.few_len = 0; L.nan_seen = 0; }
-      if (tid < kFew) L.frank[tid] = 0;
-      listed = gather_segments(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br);
-      __syncthreads();
-      done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
-    } else if constexpr (KIND == kRowShort) {
-      float held[held_short(NT)];
-      uint32_t have;
-      if (sample_bracket<NT, true>(s, n, row_len, k, held, have, sample_hist, L, br, [] {})) {
-#pragma unroll
-        for (int u = 0; u < held_short(NT); u += 8) {
-          float x[8];
-#pragma unroll
-          for (int c = 0; c < 8; ++c) x[c] = (have >> (u + c)) & 1 ? held[u + c] : -INFINITY;
-          list_append(x, br.lo, list, cap, &L.list_fill, [&](int c) { return (u + c) * NT + tid; });
-        }
-        __syncthreads();
-        listed = L.list_fill;
-        done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
-      }
-    } else {
-      float held[kHeldLong];
-      uint32_t have;
-      Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
-      if (sample_bracket<NT, false>(s, n, row_len, k, held, have, sample_hist, L, br, [&] { st.begin(s, n); })) {
-        st.filter(br.lo, 0, list, cap, &L.list_fill);
-        __syncthreads();
-        listed = L.list_fill;
-        done = select_listed<NT>(list, listed, cap, n, k, br, sel, L);
-      }
-    }
-    if (done) {
-      write_listed<NT>(list, listed, n, k, sel, before, scan_scratch, map ? map + row * row_len : nullptr, out_idx, out_val);
-      return;
-    }
-  }
-
-  // ---- two-pass path
   for (int i = tid; i < nwords; i += NT) sel[i] = 0;
-  if (tid == 0) { list_len = 0; L.few_len = 0; }
+  if (tid == 0) { L.list_fill = 0; L.few_len = 0; }
   zero_hist_n<NT>(hist);
-  if (k < n || map || all_slots) {   // otherwise every element is selected
+  if (k < n || skip_lowest) {   // otherwise every element is selected
     // ---- pass 1: histogram of the top 11 bits
     scan_row<NT>(s, 0, n, [&](int, float v, bool in) {
       if (in) atomicAdd(&hist[order_key(v) >> 21], 1);
@@ -584,7 +699,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
   }
 
   int selectable = n;
-  if (map || all_slots) {  // never select -inf slots (skipped candidates): they live in bins <= 3
+  if (skip_lowest) {  // never select -inf slots (skipped candidates): they live in bins <= 3
     selectable = n - (hist[0] + hist[1] + hist[2] + hist[3]);
   }
   const int k_eff = min(k, selectable);
@@ -601,7 +716,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
     }
     __syncthreads();
   } else {
-    find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr);
+    find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr, 0, nullptr, this_thread());
     const uint32_t d1 = thr[0];
     int need = thr[1];
     const bool listed = thr[2] <= list_cap;
@@ -613,15 +728,15 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v), a = key >> 21;
         if (in && a > d1) atomicOr(&sel[i >> 5], 1u << (i & 31));
-        const int b = wave_append(in && a == d1, &list_len);
+        const int b = wave_append(in && a == d1, &L.list_fill);
         if (b >= 0) { lkey[b] = key; lidx[b] = i; }
       });
       __syncthreads();
-      const int len = list_len;
+      const int len = L.list_fill;
       // ---- digits 2 and 3 on the list
       for (int i = tid; i < len; i += NT) atomicAdd(&hist[(lkey[i] >> 10) & 0x7FF], 1);
       __syncthreads();
-      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
       const uint32_t p22 = (d1 << 11) | (uint32_t)thr[0];
       need = thr[1];
       const int nb = thr[2];
@@ -654,7 +769,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         else if (kp == p22) atomicAdd(&hist[key & 0x3FF], 1);
       }
       __syncthreads();
-      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
       const uint32_t tkey = (p22 << 10) | (uint32_t)thr[0];
       need = thr[1];
       const int ties = thr[2];
@@ -673,7 +788,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
           else if (key == tkey) atomicAdd(&hist[kBins - 1 - (lidx[i] >> 10)], 1);
         }
         __syncthreads();
-        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
         const int hi_digit = kBins - 1 - thr[0];
         need = thr[1];
         __syncthreads();
@@ -685,7 +800,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
           else if ((e >> 10) == hi_digit) atomicAdd(&hist[kBins - 1 - (e & 0x3FF)], 1);
         }
         __syncthreads();
-        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+        find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
         const int lo_digit = kBins - 1 - thr[0];
         for (int i = tid; i < len; i += NT) {
           if (lkey[i] != tkey) continue;
@@ -706,7 +821,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         else if (a == d1) atomicAdd(&hist[(key >> 10) & 0x7FF], 1);
       });
       __syncthreads();
-      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
       const uint32_t d2 = thr[0];
       need = thr[1];
       __syncthreads();
@@ -720,7 +835,7 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         else if (b == d2) atomicAdd(&hist[key & 0x3FF], 1);
       });
       __syncthreads();
-      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr);
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, thr, 0, nullptr, this_thread());
       const uint32_t tkey = (pre22 << 10) | (uint32_t)thr[0];
       need = thr[1];  // how many elements equal to the threshold value are taken
       __syncthreads();
@@ -731,49 +846,220 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         else if (key == tkey) atomicOr(&eq[i >> 5], 1u << (i & 31));
       });
       __syncthreads();
-      // take the `need` lowest-index elements among the ties
-      const int wpt = (nwords + NT - 1) / NT;
-      const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
-      int cnt = 0;
-      for (int w = w_lo; w < w_hi; ++w) cnt += __popc(eq[w]);
-      int total;
-      int before = block_exclusive_scan(cnt, scan_scratch, &total);
-      for (int w = w_lo; w < w_hi && before < need; ++w) {
-        uint32_t bits = eq[w];
-        const int c = __popc(bits);
-        int take = min(c, need - before);
-        before += c;
-        uint32_t kept = 0;
-        while (take-- > 0) {
-          const uint32_t low = bits & (0u - bits);
-          kept |= low;
-          bits ^= low;
+      mark_lowest<NT>(eq, sel, nwords, need, scan_scratch);
+    }
+  }
+  write_marked<NT>(s, n, k, sel, scan_scratch, map, out_idx, out_val);
+}
+
+// Wavefront-uniform copies of a function's arguments (they arrive in vector registers).
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+template <typename T>
+__device__ __forceinline__ T* uniform(T* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t u = (uint64_t)(uint32_t)uniform((int)(a >> 32)) << 32 | (uint32_t)uniform((int)a);
+  return (T*)(__attribute__((address_space(1))) T*)u;   // (in global memory)
+}
+using LdsWord = __attribute__((address_space(3))) uint32_t;
+
+// A row that the linear bracket did not do.  A function of its own: inlined, its registers cost the others 0.8 us
+// (8192 scores) to 2 us (32768), and 1000 rows of 131072 129 us instead of 110.  s: the row, n of row_len elements;
+// map: its candidates or null; skip_lowest: -inf is never selected.  passed: elements that reached the lower end of
+// the first bracket, -1: it had none, -2: not worth another.
+template <int NT>
+__device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int row_len, int k, const int* __restrict__ map,
+                                         int* __restrict__ out_idx, float* __restrict__ out_val, int cap, int list_cap,
+                                         int passed, int skip_lowest, uint32_t* dyn, TopkLds<NT>& L) {
+  int* const scan_scratch = L.scan_scratch;
+  const int tid = threadIdx.x;
+  uint32_t* sel = dyn;
+  uint32_t* region = dyn + sel_words(row_len);
+  uint32_t* eq = region + kBins;
+  const int nwords = (n + 31) / 32;
+
+  if (k < n && passed >= -1) {
+    Found found = kNoBracket;
+    uint2* list = reinterpret_cast<uint2*>(region);
+    uint16_t* before = reinterpret_cast<uint16_t*>(list + cap + 64);
+    int* sample_hist = reinterpret_cast<int*>(sel);
+    Bracket br;
+    // where a list was not usable: the rank that would have listed a number between k and the capacity
+    const float aim = 0.5f * (float)(k + cap);
+    float adjust = passed < 0 ? 0.f : aim / (float)max(passed, 1);
+#pragma unroll 1
+    for (int attempt = 0; attempt < kAttempts; ++attempt) {
+      // adjust > 0: the lower end is the sample of adjust times the rank, the upper end is open
+      float held[held_hard(NT)];
+      __syncthreads();
+      Sample sm = take_sample<NT, false>(s, n, row_len, k, cap, this_thread(), held, [] {});
+      if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
+      if (tid < kFew) L.frank[tid] = 0;
+      if (adjust > 0.f) {
+        sm.r_lo = (int)ceilf(fminf((float)sm.r_lo * adjust, 1e6f));
+        sm.r_hi = 0;
+        sm.rank_up = max(sm.r_lo / 16, 1);
+      }
+      found = key_bracket<NT>(sm, held, sample_hist, L, br);
+      if (found != kBracket) break;
+      Stream<NT, 2> st;
+      st.begin(s, n);
+      st.filter(br.lo, 0, list, cap, &L.list_fill);
+      __syncthreads();
+      const int listed = L.list_fill;
+      if (select_listed<NT>(list, listed, cap, n, k, br, sel, L)) {
+        write_listed<NT>(list, listed, n, k, sel, before, scan_scratch, map, out_idx, out_val);
+        return;
+      }
+      if (listed >= k && listed <= cap) break;           // (a NaN)
+      adjust = (adjust > 0.f ? adjust : 1.f) * aim / (float)max(listed, 1);
+    }
+    // ---- the k-th largest is one of many equal values: marked from the ballots of one more pass, the counts prove it
+    // (2048 rows of 65536, 99.5 % zeros: 1960 us when they were left to the two-pass path)
+    if (found == kPlateau) {
+      const uint32_t level = order_key(br.lo);
+      int above = 0, equal = 0;
+      __syncthreads();
+      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
+        const uint32_t key = order_key(v);
+        const unsigned long long a = __builtin_amdgcn_ballot_w64(in && key > level), e = __builtin_amdgcn_ballot_w64(in && key == level);
+        const int lane = tid & 63, w = ((i - lane) >> 5) + lane;
+        if (lane < 2 && w < nwords) {
+          sel[w] = (uint32_t)(lane ? a >> 32 : a);
+          eq[w] = (uint32_t)(lane ? e >> 32 : e);
         }
-        sel[w] |= kept;  // words are owned by one thread here
+        above += __popcll(a);
+        equal += __popcll(e);
+      });
+      if ((tid & 63) == 0) { L.wave_sure[tid >> 6] = above; L.wave_more[tid >> 6] = equal; }
+      __syncthreads();
+      waves_before(L.wave_sure, NT / 64, &above);
+      waves_before(L.wave_more, NT / 64, &equal);
+      if (above < k && above + equal >= k) {
+        mark_lowest<NT>(eq, sel, nwords, k - above, scan_scratch);
+        write_marked<NT>(s, n, k, sel, scan_scratch, map, out_idx, out_val);
+        return;
+      }
+      if (above >= k && above <= cap) {
+        // the plateau ends above the k-th largest: what lies above it is the list
+        const int wpt = (nwords + NT - 1) / NT;
+        const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
+        int cnt = 0, total;
+        for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
+        int pos = block_exclusive_scan(cnt, scan_scratch, &total);
+        for (int w = w_lo; w < w_hi; ++w)
+          for (uint32_t bits = sel[w]; bits; bits &= bits - 1) {
+            const int i = w * 32 + __ffs(bits) - 1;
+            list[pos++] = make_uint2(__float_as_uint(s[i]), (uint32_t)i);
+          }
+        __syncthreads();
+        zero_hist_n<NT>(sample_hist);
+        br.lo = key_value(level + 1);
+        br.hi = INFINITY;
+        br.edge = fmaxf(br.edge, key_value(level + 2));
+        if (select_listed<NT>(list, above, cap, n, k, br, sel, L)) {
+          write_listed<NT>(list, above, n, k, sel, before, scan_scratch, map, out_idx, out_val);
+          return;
+        }
       }
       __syncthreads();
     }
   }
+  __syncthreads();
 
-  // ---- expand the bitmap in index order
-  const int wpt = (nwords + NT - 1) / NT;
-  const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
-  int cnt = 0;
-  for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
-  int total;
-  int pos = block_exclusive_scan(cnt, scan_scratch, &total);
-  for (int w = w_lo; w < w_hi; ++w) {
-    uint32_t bits = sel[w];
-    while (bits) {
-      const int i = w * 32 + __ffs(bits) - 1;
-      bits &= bits - 1;
-      if (pos < k) {  // always true when the selection is consistent
-        out_idx[pos] = map ? map[row * row_len + i] : i;
-        if (out_val) out_val[pos] = s[i];
+  two_pass_row<NT>(s, n, row_len, k, map, out_idx, out_val, list_cap, skip_lowest != 0, dyn, L);
+}
+
+template <int NT>
+__device__ __attribute__((noinline)) void call_hard_row(const float* s, int n, int row_len, int k, const int* map, int* out_idx,
+                                                        float* out_val, int cap, int list_cap, int passed, int skip_lowest,
+                                                        LdsWord* dyn, LdsWord* lds) {
+  auto words = [](LdsWord* p) { return (uint32_t*)(LdsWord*)(uintptr_t)(uint32_t)uniform((int)(uintptr_t)p); };
+  hard_row<NT>(uniform(s), uniform(n), uniform(row_len), uniform(k), uniform(map), uniform(out_idx), uniform(out_val),
+               uniform(cap), uniform(list_cap), uniform(passed), uniform(skip_lowest), words(dyn),
+               *reinterpret_cast<TopkLds<NT>*>(words(lds)));
+}
+
+template <int NT, int KIND>
+__device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict__ S, int row_len,
+                                         int k, const int* __restrict__ map, int* __restrict__ idx,
+                                         float* __restrict__ val, const int* __restrict__ pre, int cap,
+                                         int list_cap, int t, int seq, uint32_t* dyn, bool all_slots = false) {
+  // dyn: sel bitmap (sampled path: and its histograms), then the list of the sampled path, or the two-pass
+  // path's histogram and its eq bitmap OR list (keys, idx)
+  __shared__ TopkLds<NT> L;
+
+  const int tid = threadIdx.x;
+  const size_t row = (size_t)seq * p.n_q + t;
+  const float* s = S + row * row_len;
+  const int n = (map || all_slots) ? row_len : visible(p, seq, t);
+  uint32_t* sel = dyn;
+  uint2* list = reinterpret_cast<uint2*>(dyn + sel_words(row_len));
+  int* out_idx = idx + row * k;
+  float* out_val = val ? val + row * k : nullptr;
+  const int* map_row = map ? map + row * row_len : nullptr;
+  int passed = -1;
+
+  if (k >= n && !map && !all_slots) {   // every element
+    for (int i = tid; i < k; i += NT) {
+      out_idx[i] = i < n ? i : -1;
+      if (out_val) out_val[i] = i < n ? s[i] : -INFINITY;
+    }
+    return;
+  }
+  if constexpr (KIND == kRowPlain) {
+    two_pass_row<NT>(s, n, row_len, k, map_row, out_idx, out_val, list_cap, map || all_slots, dyn, L);
+    return;
+  } else if (k < n) {
+    bool done = false;
+    uint16_t* before = reinterpret_cast<uint16_t*>(list + cap + 64);
+    int* sample_hist = reinterpret_cast<int*>(sel);
+    Bracket br;
+    if constexpr (KIND == kRowListed) {
+      const int rlen = range_len(row_len), ranges_row = (row_len + rlen - 1) / rlen;
+      for (int i = tid; i < kBins; i += NT) sample_hist[i] = 0;
+      if (tid == 0) { L.few_len = 0; L.nan_seen = 0; }
+      if (tid < kFew) L.frank[tid] = 0;
+      bool whole;
+      passed = gather_segments(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br, whole);
+      __syncthreads();
+      if (whole) done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+      if (!whole && passed >= k && passed <= cap) passed = (k + cap) / 2;   // (a segment overflowed, the list will not)
+      else if (!done && passed >= k && passed <= cap) passed = -2;          // (a NaN)
+    } else if constexpr (KIND == kRowShort) {
+      float held[held_short(NT)];
+      Sample sm;
+      if (sample_bracket<NT, true>(s, n, row_len, k, cap, held, sm, sample_hist, L, br, [] {})) {
+#pragma unroll
+        for (int u = 0; u < held_short(NT); u += 8) {
+          float x[8];
+#pragma unroll
+          for (int c = 0; c < 8; ++c) x[c] = held[u + c];
+          list_append(x, br.lo, list, cap, &L.list_fill, [&](int c) { return (u + c) * NT + tid; });
+        }
+        __syncthreads();
+        passed = L.list_fill;
+        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+        if (!done && passed >= k && passed <= cap) passed = -2;
       }
-      ++pos;
+    } else {
+      float held[kHeldLong];
+      Sample sm;
+      Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
+      if (sample_bracket<NT, false>(s, n, row_len, k, cap, held, sm, sample_hist, L, br, [&] { st.begin(s, n); })) {
+        st.filter(br.lo, 0, list, cap, &L.list_fill);
+        __syncthreads();
+        passed = L.list_fill;
+        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+        if (!done && passed >= k && passed <= cap) passed = -2;
+      }
+    }
+    if (done) {
+      write_listed<NT>(list, passed, n, k, sel, before, L.scan_scratch, map_row, out_idx, out_val);
+      return;
     }
   }
+  call_hard_row<NT>(s, n, row_len, k, map_row, out_idx, out_val, cap, list_cap, passed, map || all_slots ? 1 : 0,
+                    (LdsWord*)dyn, (LdsWord*)reinterpret_cast<uint32_t*>(&L));
 }
 
 // Registers: 1024 threads leave room for two workgroups per CU, the smaller ones for 24 wavefronts.
@@ -792,13 +1078,16 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kTopkT
 // there is none, so a small grid strides over the rows.
 __global__ __launch_bounds__(kTopkThreads) void topk_only_kernel(Prob p, const float* __restrict__ S,
                                                                  int k, int* __restrict__ idx,
-                                                                 float* __restrict__ val, int cap,
-                                                                 int list_cap, const int* __restrict__ only) {
+                                                                 float* __restrict__ val, int list_cap,
+                                                                 const int* __restrict__ only) {
   extern __shared__ __align__(16) uint32_t dyn[];
+  __shared__ TopkLds<kTopkThreads> L;
   const int rows = p.n_seq * p.n_q;
   for (int r = blockIdx.x; r < rows; r += gridDim.x) {
     if (!only[r]) continue;
-    topk_row<kTopkThreads, kRowLong>(p, S, p.L, k, nullptr, idx, val, nullptr, cap, list_cap, r % p.n_q, r / p.n_q, dyn);
+    const size_t row = r;
+    two_pass_row<kTopkThreads>(S + row * p.L, visible(p, r / p.n_q, r % p.n_q), p.L, k, nullptr, idx + row * k,
+                               val ? val + row * k : nullptr, list_cap, false, dyn, L);
     __syncthreads();
   }
 }
@@ -844,7 +1133,8 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
   const bool few_rows = (long long)p.n_q * p.n_seq < 256;
   int nt = row_len > 4096 ? kTopkThreads : few_rows ? 512 : 256;
   if (is_short) fits(nt, kLdsMost);
-  else if (split || only || (long long)p.n_q * p.n_seq < 512 || !fits(nt = 512, 53 * 1024)) {
+  else if (only) nt = kTopkThreads;
+  else if (split || (long long)p.n_q * p.n_seq < 512 || !fits(nt = 512, 53 * 1024)) {
     nt = kTopkThreads;
     // the longest rows have room for half the reserve; k well above 8192: the two-pass path
     if (!fits(nt, kLdsMost) && !fits(nt, kLdsMost, 3.0)) cap = 0;
@@ -864,7 +1154,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     if (KIND == kRowListed) {                                                                      \
       const int rlen = range_len(p.L);                                                             \
       const dim3 ranges((p.L + rlen - 1) / rlen, p.n_q, p.n_seq);                                  \
-      topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, pre);                  \
+      topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, cap, pre);                 \
     }                                                                                              \
     topk_kernel<NT, KIND><<<grid, NT, lds, st>>>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, all_slots); \
   } while (0)
@@ -873,7 +1163,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_only_kernel), lds, seen);
     if (e != hipSuccess) return e;
     const int rows = p.n_seq * p.n_q;
-    topk_only_kernel<<<rows < 256 ? rows : 256, kTopkThreads, lds, st>>>(p, S, k, idx, val, cap, list_cap, only);
+    topk_only_kernel<<<rows < 256 ? rows : 256, kTopkThreads, lds, st>>>(p, S, k, idx, val, list_cap, only);
   } else if (is_short && nt == 256) {
     GO(256, kRowShort);
   } else if (is_short && nt == 512) {
@@ -882,6 +1172,8 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     GO(kTopkThreads, kRowShort);
   } else if (nt == 512) {
     GO(512, kRowLong);
+  } else if (cap == 0) {
+    GO(kTopkThreads, kRowPlain);
   } else if (pre) {
     GO(kTopkThreads, kRowListed);
   } else {
