@@ -93,9 +93,9 @@ __host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 3
 //            entries in the bin of the need-th are ranked against each other, or, if there are many
 //            (repeated values), resolved by the digits of key and index.
 //
-//   again    If sure > k, the upper end is dropped.  If fewer than k or more than the list holds pass, the
-//            row is sampled and streamed again with the rank r_lo scaled by what the last count says of it.
-//            One value: hard_row marks what lies above it and the first of it.
+//   again    (hard_row)  If sure > k, the row is sampled and streamed again without an upper end; if fewer than
+//            k or more than the list holds pass, with the rank r_lo scaled by what the last count says of it.
+//            One value: what lies above it and the first of it are marked.
 // A NaN leaves the row to the two-pass path.  Candidate rows never select -inf: it lies below the bracket.
 // The histograms share their LDS with the bitmap, which is cleared once the last of them has been read.
 //
@@ -161,10 +161,9 @@ struct Sample {
   int m, ls;          // sample elements; lines per sampled line
   int r_lo, r_hi;     // ranks of the bracket's ends in the sample
   int rank_up;        // rank of the upper end of the histogram of the list
-  int spare;          // samples past the r_lo-th that the list has room for
 };
 template <int NT, bool SHORT, int HELD, typename F>
-__device__ __forceinline__ Sample take_sample(const float* __restrict__ s, int n, int row_len, int k, int cap, int tid,
+__device__ __forceinline__ Sample take_sample(const float* __restrict__ s, int n, int row_len, int k, int tid,
                                               float (&held)[HELD], F also) {
   Sample sm;
   const int lines = (n + 15) >> 4, max_lines = SHORT ? lines : sample_lines(n, row_len, k, NT);
@@ -172,14 +171,13 @@ __device__ __forceinline__ Sample take_sample(const float* __restrict__ s, int n
   const int groups = lines / ls;       // >= 1
   // (16-bit hash and ls <= 128: 24-bit products)
   auto line_of = [&](uint32_t g) { return (int)(__umul24(g, ls) + (__umul24((g * 2654435761u) >> 16, ls) >> 16)); };
-  uint32_t none = 0;
+  bool in[HELD];
 #pragma unroll
   for (int u = 0; u < HELD; ++u) {
     const int smp = tid + u * NT, g = smp >> 4;
     const int i = SHORT ? smp : line_of(g) * 16 + (smp & 15);
-    const bool in = (SHORT || g < groups) && i < n;
-    held[u] = s[in ? i : 0];
-    none |= in ? 0u : 1u << u;
+    in[u] = (SHORT || g < groups) && i < n;
+    held[u] = s[in[u] ? i : 0];
   }
   also();
   // number of samples: 16 per sampled line, less what the row's last line lacks if it is one
@@ -196,74 +194,81 @@ __device__ __forceinline__ Sample take_sample(const float* __restrict__ s, int n
     sm.r_lo = (int)ceilf(kf + margin);
     sm.r_hi = (int)floorf(kf - margin);
   }
-  sm.spare = ls == 1 ? (cap - k) / 2 : (int)(3.f * sqrtf((float)sm.r_lo));
   sm.rank_up = sm.r_hi >= 1 ? sm.r_hi : max(sm.r_lo / 16, 1);   // (hi open: the histogram ends above most of the top k)
 #pragma unroll
-  for (int u = 0; u < HELD; ++u) held[u] = (none >> u) & 1 ? -INFINITY : held[u];
+  for (int u = 0; u < HELD; ++u) held[u] = in[u] ? held[u] : -INFINITY;
   return sm;
 }
 
 // The bracket of a row's k-th largest of n > k elements (block-uniform) from a histogram of the sample that is
-// linear between the smallest and the largest one (masks and the like left out: below they are not counted, above
+// linear between the smallest and the largest one, masks and the like left out (below they are not counted, above
 // they share the last bin), and while that is too coarse (far outliers, heavy tails) from a second and a third one
-// between those of the r_lo-th sample's bin; false if the third is, too.  `cap`: what the list holds.  `also` is
-// called once the sample's loads have been issued.  Leaves hist cleared if there is a bracket.
+// inside the r_lo-th sample's bin; false if the third is, too.  The lowest bin is not counted: it holds nearly all
+// samples of a row with heavy tails, and LDS adds to one address go one after the other.  `also` is called once the
+// sample's loads have been issued.  Leaves hist cleared if there is a bracket.
 template <int NT, bool SHORT, int HELD, typename F>
-__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int row_len, int k, int cap,
-                                               float (&held)[HELD], Sample& sm, int* hist, TopkLds<NT>& L, Bracket& br,
-                                               F also) {
+__device__ __forceinline__ bool sample_bracket(const float* __restrict__ s, int n, int row_len, int k, float (&held)[HELD],
+                                               int* hist, TopkLds<NT>& L, Bracket& br, F also) {
   constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  sm = take_sample<NT, SHORT>(s, n, row_len, k, cap, tid, held, [&] {
+  const Sample sm = take_sample<NT, SHORT>(s, n, row_len, k, tid, held, [&] {
     also();
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;
-    if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
+    if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; L.thr[2] = 0; L.thr_up[2] = 0; }
     if (tid < kFew) L.frank[tid] = 0;
   });
   if (sm.r_lo > sm.m) return false;
-  float from = -1e30f, to = 1e30f;
-#pragma unroll 1
+  float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < HELD; ++u)
+    if (fabsf(held[u]) < 1e30f) { lo = fminf(lo, held[u]); hi = fmaxf(hi, held[u]); }
+  lo = -wave_max_f32(-lo);
+  hi = wave_max_f32(hi);
+  if (lane == 0) { L.wave_min[wave] = lo; L.wave_max[wave] = hi; }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
+  br.edge = INFINITY;
   for (int pass = 0;; ++pass) {
-    float lo = INFINITY, hi = -INFINITY;
-#pragma unroll
-    for (int u = 0; u < HELD; ++u)
-      if (held[u] >= from && held[u] <= to) { lo = fminf(lo, held[u]); hi = fmaxf(hi, held[u]); }
-    lo = -wave_max_f32(-lo);
-    hi = wave_max_f32(hi);
-    if (lane == 0) { L.wave_min[wave] = lo; L.wave_max[wave] = hi; }
-    if (tid == 0) L.thr[2] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { lo = fminf(lo, L.wave_min[w]); hi = fmaxf(hi, L.wave_max[w]); }
     const float width = (hi - lo) * (1.f / kBins), per = (float)kBins / (hi - lo);
     if (!(width > 0.f) || !(per < 3e38f)) return false;
-    count_bins<HELD>(hist, [&](int u) { return held[u] >= lo ? linear_bin(held[u], lo, per) : -1; });
+    const float counted = lo + width;
+    if constexpr (SHORT) {   // (a whole row; for 4096 samples the test costs 0.1 to 0.6 us and a shared bin 1.7 us)
+      count_bins<HELD>(hist, [&](int u) { return held[u] >= counted ? linear_bin(held[u], lo, per) : -1; });
+    } else {
+#pragma unroll
+      for (int u = 0; u < HELD; ++u)
+        if (held[u] >= counted) atomicAdd(&hist[linear_bin(held[u], lo, per)], 1);
+    }
     __syncthreads();
     find_threshold_bin_n<NT>(hist, sm.r_lo, L.scan_scratch, L.thr, sm.rank_up, L.thr_up, this_thread());
-    const int b_lo = L.thr[0], b_hi = L.thr_up[0], crowd = L.thr[2], rest = crowd - L.thr[1];
-    if (crowd == 0) return false;   // the r_lo-th sample lies below lo (the threshold was not written)
+    const int crowd = L.thr[2], b_lo = crowd ? L.thr[0] : 0, b_hi = L.thr_up[0];   // (crowd 0: not among the counted)
     // rounding of the bins: 2048 x 2^-22 of one, and what lo and hi have lost by their size
     const float slack = 0.001f * width + 2.5e-7f * fmaxf(fabsf(lo), fabsf(hi));
     br.lo = fmaxf(lo + (float)b_lo * width - slack, -FLT_MAX);   // (never -inf, which pads the list appends)
-    const float edge = lo + (float)(b_hi + 1) * width + slack;
-    br.edge = pass == 0 || b_hi < kBins - 1 ? edge : br.edge;
-    br.hi = sm.r_hi >= 1 ? br.edge : INFINITY;
+    if (L.thr_up[2] != 0 && (b_hi < kBins - 1 || br.edge == INFINITY)) br.edge = lo + (float)(b_hi + 1) * width + slack;
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;   // (read by everybody: find_threshold_bin ends with a barrier)
     __syncthreads();
-    if (rest <= sm.spare) return true;
+    if (crowd != 0 && crowd <= 64) {
+      br.hi = sm.r_hi >= 1 ? br.edge : INFINITY;
+      return true;
+    }
     if (pass == 2) return false;
-    from = br.lo;
-    to = b_lo == kBins - 1 ? INFINITY : lo + (float)(b_lo + 1) * width + slack;
+    hi = lo + (float)(b_lo + 1) * width + slack;
+    lo = br.lo;
+    if (tid == 0) { L.thr[2] = 0; L.thr_up[2] = 0; }
   }
 }
 
 // The same by digits of the key, 11 bits each time until few samples are left beside the r_lo-th, or one value.
 template <int NT, int HELD>
-__device__ __forceinline__ Found key_bracket(const Sample& sm, const float (&held)[HELD], int* hist,
+__device__ __forceinline__ Found key_bracket(int cap, const Sample& sm, const float (&held)[HELD], int* hist,
                                              TopkLds<NT>& L, Bracket& br) {
   constexpr int NW = NT / 64;
   const int tid = this_thread(), lane = tid & 63, wave = tid >> 6;
   if (sm.r_lo > sm.m) return kNoBracket;
+  // samples past the r_lo-th that the list has room for
+  const int spare = sm.ls == 1 ? max(cap - sm.r_lo, 0) : (int)(3.f * sqrtf((float)sm.r_lo));
   __syncthreads();
   zero_hist_n<NT>(hist);
   uint32_t key_lo = order_key(-FLT_MAX), key_hi = kKeyPosInf;   // key range of the r_lo-th sample
@@ -296,7 +301,7 @@ __device__ __forceinline__ Found key_bracket(const Sample& sm, const float (&hel
     br.edge = fmaxf(br.edge, key_value(key_lo + 1));
     for (int i = tid; i < kBins; i += NT) hist[i] = 0;
     __syncthreads();
-    if (rest <= sm.spare) return kBracket;
+    if (rest <= spare) return kBracket;
     if (sh == 0) return kPlateau;
   }
 }
@@ -390,38 +395,31 @@ struct Stream {
 // The top k of a row of n elements from the list of those that reach br.lo into the bitmap sel (whose
 // LDS is hist, cleared, before).  false: see above.
 template <int NT>
-__device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, Bracket br,
+__device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, const Bracket& br,
                                               uint32_t* sel, TopkLds<NT>& L) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int* hist = reinterpret_cast<int*>(sel);
   auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
   const float fine = fminf(fmaxf((float)kBins / (br.edge - br.lo), 1e-35f), 3e38f);   // entries above share the last bin
   if (listed < k || listed > cap) return false;
-  int need;
-  for (;;) {
-    int sure = 0;
-    bool nan = false;
-    for (int j0 = 0; j0 < listed; j0 += NT) {
-      const int j = j0 + tid;
-      const bool live = j < listed;
-      const float x = live ? __uint_as_float(list[j].x) : 0.f;
-      nan |= x != x;
-      sure += __popcll(__builtin_amdgcn_ballot_w64(live && x >= br.hi));
-      if (live && x < br.hi) atomicAdd(&hist[linear_bin(x, br.lo, fine)], 1);
-    }
-    if (nan) L.nan_seen = 1;
-    if (lane == 0) L.wave_sure[wave] = sure;
-    __syncthreads();
-    if (L.nan_seen) return false;
-    int total_sure;
-    waves_before(L.wave_sure, NT / 64, &total_sure);
-    need = k - total_sure;
-    if (need >= 0) break;
-    if (br.hi == INFINITY) return false;                 // more than k infinite entries
-    br.hi = INFINITY;                                    // (the others share the last bin, which is resolved by digits)
-    __syncthreads();
-    zero_hist_n<NT>(hist);
+  int sure = 0;
+  bool nan = false;
+  for (int j0 = 0; j0 < listed; j0 += NT) {
+    const int j = j0 + tid;
+    const bool live = j < listed;
+    const float x = live ? __uint_as_float(list[j].x) : 0.f;
+    nan |= x != x;
+    sure += __popcll(__builtin_amdgcn_ballot_w64(live && x >= br.hi));
+    if (live && x < br.hi) atomicAdd(&hist[linear_bin(x, br.lo, fine)], 1);
   }
+  if (nan) L.nan_seen = 1;
+  if (lane == 0) L.wave_sure[wave] = sure;
+  __syncthreads();
+  if (L.nan_seen) return false;
+  int total_sure;
+  waves_before(L.wave_sure, NT / 64, &total_sure);
+  int need = k - total_sure;
+  if (need < 0) return false;
   find_threshold_bin_n<NT>(hist, max(need, 1), L.scan_scratch, L.thr, this_thread());
   const int b = need > 0 ? L.thr[0] : kBins;             // need == 0: the sure ones are all
   int few = need > 0 ? L.thr[2] : 0;
@@ -559,7 +557,7 @@ __host__ __device__ inline int range_len(int L) {
 }
 
 __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, const float* __restrict__ S, int k,
-                                                                      int rlen, int cap, int* __restrict__ pre) {
+                                                                      int rlen, int* __restrict__ pre) {
   constexpr int NT = kTopkThreads;
   __shared__ int hist[kBins];
   __shared__ TopkLds<NT> L;
@@ -573,8 +571,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   float held[kHeldLong];
   Bracket br = {0.f, 0.f, 0.f};
   Stream<NT, 2> st;
-  Sample sm;
-  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, cap, held, sm, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
+  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, held, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
   if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -891,7 +888,7 @@ __device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int
       // adjust > 0: the lower end is the sample of adjust times the rank, the upper end is open
       float held[held_hard(NT)];
       __syncthreads();
-      Sample sm = take_sample<NT, false>(s, n, row_len, k, cap, this_thread(), held, [] {});
+      Sample sm = take_sample<NT, false>(s, n, row_len, k, this_thread(), held, [] {});
       if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
       if (tid < kFew) L.frank[tid] = 0;
       if (adjust > 0.f) {
@@ -899,7 +896,7 @@ __device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int
         sm.r_hi = 0;
         sm.rank_up = max(sm.r_lo / 16, 1);
       }
-      found = key_bracket<NT>(sm, held, sample_hist, L, br);
+      found = key_bracket<NT>(cap, sm, held, sample_hist, L, br);
       if (found != kBracket) break;
       Stream<NT, 2> st;
       st.begin(s, n);
@@ -910,7 +907,11 @@ __device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int
         write_listed<NT>(list, listed, n, k, sel, before, scan_scratch, map, out_idx, out_val);
         return;
       }
-      if (listed >= k && listed <= cap) break;           // (a NaN)
+      if (listed >= k && listed <= cap) {
+        if (L.nan_seen || adjust > 0.f) break;           // (adjust: more than k infinite entries)
+        adjust = 1.f;
+        continue;
+      }
       adjust = (adjust > 0.f ? adjust : 1.f) * aim / (float)max(listed, 1);
     }
     // ---- the k-th largest is one of many equal values: marked from the ballots of one more pass, the counts prove it
@@ -1023,12 +1024,11 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       passed = gather_segments(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br, whole);
       __syncthreads();
       if (whole) done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
-      if (!whole && passed >= k && passed <= cap) passed = (k + cap) / 2;   // (a segment overflowed, the list will not)
-      else if (!done && passed >= k && passed <= cap) passed = -2;          // (a NaN)
+      // (a segment overflowed that the list will hold, or sure > k: the same lower end once more, the upper end open)
+      if (!done && passed >= k && passed <= cap) passed = whole && L.nan_seen ? -2 : (k + cap) / 2;
     } else if constexpr (KIND == kRowShort) {
       float held[held_short(NT)];
-      Sample sm;
-      if (sample_bracket<NT, true>(s, n, row_len, k, cap, held, sm, sample_hist, L, br, [] {})) {
+      if (sample_bracket<NT, true>(s, n, row_len, k, held, sample_hist, L, br, [] {})) {
 #pragma unroll
         for (int u = 0; u < held_short(NT); u += 8) {
           float x[8];
@@ -1039,18 +1039,17 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         __syncthreads();
         passed = L.list_fill;
         done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
-        if (!done && passed >= k && passed <= cap) passed = -2;
+        if (!done && passed >= k && passed <= cap) passed = L.nan_seen ? -2 : (k + cap) / 2;
       }
     } else {
       float held[kHeldLong];
-      Sample sm;
       Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
-      if (sample_bracket<NT, false>(s, n, row_len, k, cap, held, sm, sample_hist, L, br, [&] { st.begin(s, n); })) {
+      if (sample_bracket<NT, false>(s, n, row_len, k, held, sample_hist, L, br, [&] { st.begin(s, n); })) {
         st.filter(br.lo, 0, list, cap, &L.list_fill);
         __syncthreads();
         passed = L.list_fill;
         done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
-        if (!done && passed >= k && passed <= cap) passed = -2;
+        if (!done && passed >= k && passed <= cap) passed = L.nan_seen ? -2 : (k + cap) / 2;
       }
     }
     if (done) {
@@ -1154,7 +1153,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     if (KIND == kRowListed) {                                                                      \
       const int rlen = range_len(p.L);                                                             \
       const dim3 ranges((p.L + rlen - 1) / rlen, p.n_q, p.n_seq);                                  \
-      topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, cap, pre);                 \
+      topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, pre);                 \
     }                                                                                              \
     topk_kernel<NT, KIND><<<grid, NT, lds, st>>>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, all_slots); \
   } while (0)
