@@ -606,7 +606,11 @@ hipError_t launch_route(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
   const int splits = route_splits(p);
   float* part = static_cast<float*>(ws);
   int total_splits = splits;
-  if (q_dtype == MISA_BF16 && (route_few_rows(p) || p.n_q < 8)) {
+  // A query of route_few_kernel reads all pooled blocks by itself.  Where the rows of a sequence are more than one
+  // wavefront's that pays until the workgroups of all queries fill the chip (64 heads, us, tile kernel / this one:
+  // 3 queries of 64 x 512 blocks 33 / 30, 4 of them 31 / 35; 4 of 256 x 64 blocks 34 / 30; 7 of 64 x 2048 59 / 113).
+  const bool few_queries = p.n_q < 8 && (long long)p.n_seq * p.n_q * ((p.M + 63) / 64) <= 1536;
+  if (q_dtype == MISA_BF16 && (route_few_rows(p) || few_queries)) {
     int tpw, parts;
     route_few_shape(p, &tpw, &parts);
     total_splits = parts;
@@ -627,8 +631,11 @@ hipError_t launch_route(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
     else route_tile_kernel<2><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);   // (one group: few rows)
   } else {
     // few rows: a block per wavefront while that makes at most 64 partial sums (64 blocks: 6.8 us; 25 us in
-    // one workgroup, whose wavefronts then take 16 blocks each one after the other)
-    if (route_few_rows(p)) total_splits = std::min(64, (p.M + 3) / 4);
+    // one workgroup, whose wavefronts then take 16 blocks each one after the other), and no more workgroups
+    // than two per CU (256 sequences of 64 blocks: 19 us; 64 us with a workgroup for 4 blocks; one per CU: 64 x 256
+    // blocks of 32 heads 19 us instead of 16)
+    const long long most = std::min<long long>(std::min(64, (p.M + 3) / 4), 512 / ((long long)p.n_seq * p.n_q));
+    while (route_few_rows(p) && 2 * total_splits <= most) total_splits *= 2;
     const dim3 g1(total_splits, p.n_q, p.n_seq);
     route_partial_kernel<MISA_F32><<<g1, 256, 0, st>>>(p, total_splits, Q, Kp, part);
   }

@@ -42,3 +42,33 @@ def test_head_scores(misa, n_q, H, L, B, q_dtype):
             _, ref = O.route_heads(q, w, K, B, p.h, n)
             assert_scores_close(E[s, t].cpu().numpy(), ref, f"E {s} {t}")
             check_index_set(heads[s, t].cpu().numpy(), ref, p.h, f"heads {s} {t}")
+
+
+@pytest.mark.parametrize("q_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n_seq,n_q,H,L,B", [(128, 4, 64, 768, 4), (128, 4, 64, 772, 4), (520, 3, 32, 130, 2), (64, 1, 64, 1024, 2),
+                                             (600, 1, 64, 500, 2), (96, 6, 8, 1500, 4)])
+def test_head_scores_of_many_sequences(misa, n_seq, n_q, H, L, B, q_dtype):
+    """Both sides of the rules that count the workgroups of all sequences: a block of queries per read of the
+    pooled keys or one, and the partial sums of a query.  A few sequences, repeated."""
+    wl = WL.scaled(WL.WORKLOADS["c1"], n_seq=2, L=L, n_q=n_q, H=H, h=8, B=B, decode=n_q == 1, q_dtype=q_dtype, needles=0)
+    inp = WL.make_inputs(wl, seed=L + H, seq_len=[L, max(1, L - L // 3)])
+    if n_q > 1:
+        inp["q_pos"] = np.maximum(0, L - 1 - np.array([0, 1, 5, L // 2, L, 2, L // 4])[:n_q]).astype(np.int32)
+    dv = misa.to_device(inp)
+    from dataclasses import replace
+    rep = lambda x: x if x is None else x[torch.arange(n_seq, device="cuda") % 2].contiguous()
+    p = replace(dv["problem"], n_seq=n_seq, seq_len=rep(dv["problem"].seq_len))
+    K, ks, Q, W = rep(dv["K"]), rep(dv["kscale"]), rep(dv["Q"]), rep(dv["W"])
+    Kp = torch.empty(n_seq, p.M, 128, device="cuda")
+    misa.pool_keys(p, K, ks, Kp, misa.alloc_workspace(p, misa.OP_POOL))
+    heads = torch.empty(n_seq, n_q, p.h, dtype=torch.int32, device="cuda")
+    E = torch.empty(n_seq, n_q, H, device="cuda")
+    misa.route_heads(p, Q, W, Kp, K, ks, heads, E, misa.alloc_workspace(p, misa.OP_ROUTE))
+    torch.cuda.synchronize()
+    assert torch.equal(E[2:], rep(E[:2])[2:]) and torch.equal(heads[2:], rep(heads[:2])[2:])
+    for s in range(2):
+        for t in range(n_q):
+            Ks, q, w, n = oracle_view(inp, s, t)
+            _, ref = O.route_heads(q, w, Ks, B, p.h, n)
+            assert_scores_close(E[s, t].cpu().numpy(), ref, f"E {s} {t}")
+            check_index_set(heads[s, t].cpu().numpy(), ref, p.h, f"heads {s} {t}")
