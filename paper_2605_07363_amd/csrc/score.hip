@@ -1197,7 +1197,12 @@ static hipError_t launch_stream(const Prob& p, const void* Q, const float* W, co
       score_stream_kernel<KDT, NT, STEPS, 1, false, MQ><<<grid, 256, 0, st>>>(p, q, W, heads, K, kscale, S); \
     return hipGetLastError();                                                                     \
   } while (0)
-  if (p.n_q > 1 && hc <= 16) {   // several queries per read of the keys
+  // Several queries per read of the keys, where a workgroup per query and 1024 keys would be more than one per CU
+  // (us, a query each / together: 7 queries of 8 heads, bf16, 32768 keys 9.9 / 13.2; 2 queries of 131072 10.4 / 10.8,
+  // 3 of them 17.4 / 11.8; fp8 9.5 / 10.9, 4 queries of 131072 12.8 / 9.0).  Together a workgroup takes 1024 keys for
+  // fp8 as well: the sums of the queries bound it, not the wavefronts in flight.
+  const bool together = (long long)p.n_q * p.n_seq * ((p.L + 1023) / 1024) > 256;
+  if (p.n_q > 1 && hc <= 16 && together) {
     if (hc <= 8) {
       if (p.n_q == 2) GO(1, 4, 2);
       if (p.n_q <= 4) GO(2, 4, 2);
