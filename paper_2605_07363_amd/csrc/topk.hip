@@ -35,23 +35,29 @@ constexpr int kAttempts = 4;         // further brackets tried on a row
 __host__ __device__ constexpr int held_hard(int nt) { return nt == 256 ? 16 : 8; }
 __host__ __device__ constexpr int held_short(int nt) { return nt == 256 ? 16 : 8; }
 
+template <int NT>
+__device__ __forceinline__ void clear_hist(int* hist) {
+  for (int i = this_thread(); i < kBins; i += NT) hist[i] = 0;
+  __syncthreads();
+}
+
 // Visits elements lo..hi-1 of a row with all threads of the block.  Eight
 // coalesced loads per thread are in flight before the first one is used.  f is
 // called by every thread of every wavefront in each round (in == false past
 // the end), so it may contain wavefront-wide operations.
-template <int NT, typename F>
+template <int NT, int U = 8, typename F>
 __device__ __forceinline__ void scan_row(const float* __restrict__ s, int lo, int hi, F f) {
-  constexpr int U = 8;
+  const int tid = this_thread();
   for (int base = lo; base < hi; base += NT * U) {
     float v[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = base + u * NT + (int)threadIdx.x;
+      const int i = base + u * NT + tid;
       v[u] = i < hi ? s[i] : 0.f;
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int i = base + u * NT + (int)threadIdx.x;
+      const int i = base + u * NT + tid;
       f(i, v[u], i < hi);
     }
   }
@@ -100,7 +106,7 @@ __host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 3
 // The histograms share their LDS with the bitmap, which is cleared once the last of them has been read.
 //
 // Measured: 4096 rows of 65536, k = 2048: 212 us = 5.1 TB/s (two passes over each row: 402 us; sample and
-// stream alone, nothing selected: 190 us); 64 rows of 32768: 13.8 us (17.3 us in two launches).  Few rows
+// stream alone, nothing selected: 190 us); 64 rows of 32768: 14.4 us (17.3 us in two launches).  Few rows
 // are a chain of barrier-separated phases of one workgroup.
 struct Bracket {
   float lo, hi;
@@ -146,7 +152,7 @@ __device__ __forceinline__ void count_bins(int* hist, F bin_of) {
       same += __popcll(__builtin_amdgcn_ballot_w64(bin == first));
       if (bin >= 0 && bin != first) atomicAdd(&hist[bin], 1);
     }
-    if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], same);
+    if ((this_thread() & 63) == 0) atomicAdd(&hist[first], same);
   } else {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -270,7 +276,7 @@ __device__ __forceinline__ Found key_bracket(int cap, const Sample& sm, const fl
   // samples past the r_lo-th that the list has room for
   const int spare = sm.ls == 1 ? max(cap - sm.r_lo, 0) : (int)(3.f * sqrtf((float)sm.r_lo));
   __syncthreads();
-  zero_hist_n<NT>(hist);
+  clear_hist<NT>(hist);
   uint32_t key_lo = order_key(-FLT_MAX), key_hi = kKeyPosInf;   // key range of the r_lo-th sample
   br.hi = br.edge = INFINITY;
 #pragma unroll 1
@@ -343,22 +349,23 @@ typedef float f32x4_u __attribute__((ext_vector_type(4), aligned(4)));   // (16-
 template <int NT, int AHEAD>
 struct Stream {
   const float* s;
-  int n, blocks;
+  int n, blocks, tid;
   f32x4_u v[AHEAD];
 
   __device__ __forceinline__ f32x4_u request(int block) const {
-    return reinterpret_cast<const f32x4_u*>(s + min(block, blocks - 1) * 4 * NT)[threadIdx.x];
+    return reinterpret_cast<const f32x4_u*>(s + min(block, blocks - 1) * 4 * NT)[tid];
   }
-  __device__ __forceinline__ void begin(const float* s_, int n_) {
+  __device__ __forceinline__ void begin(const float* s_, int n_, int tid_) {
     s = s_;
     n = n_;
+    tid = tid_;
     blocks = n / (4 * NT);
     if (blocks == 0) return;
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u) v[u] = request(u);
   }
   __device__ __forceinline__ void filter(float lo, int first, uint2* list, int cap, int* fill) {
-    const int tid = threadIdx.x, rest0 = blocks * 4 * NT;
+    const int rest0 = blocks * 4 * NT;
     float rest[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) rest[u] = s[min(rest0 + u * NT + tid, n - 1)];
@@ -396,8 +403,8 @@ struct Stream {
 // LDS is hist, cleared, before).  false: see above.
 template <int NT>
 __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int cap, int n, int k, const Bracket& br,
-                                              uint32_t* sel, TopkLds<NT>& L) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+                                              uint32_t* sel, TopkLds<NT>& L, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
   int* hist = reinterpret_cast<int*>(sel);
   auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
   const float fine = fminf(fmaxf((float)kBins / (br.edge - br.lo), 1e-35f), 3e38f);   // entries above share the last bin
@@ -436,7 +443,7 @@ __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int
   if (few > kFew) {
     need = L.thr[1];
     __syncthreads();
-    zero_hist_n<NT>(hist);
+    clear_hist<NT>(hist);
     for (int j = tid; j < listed; j += NT) {
       const float x = __uint_as_float(list[j].x);
       if (side(x) == 1) atomicAdd(&hist[linear_bin(x, from2, fine2)], 1);
@@ -457,7 +464,7 @@ __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int
     for (int shift = 41; shift >= -3; shift -= 11) {     // 52 bits: 11 at 41, 30, 19, 8 and the last 8
       const int low = max(shift, 0), bits = shift < 0 ? 11 + shift : 11;
       __syncthreads();
-      zero_hist_n<NT>(hist);
+      clear_hist<NT>(hist);
       for (int j = tid; j < listed; j += NT) {
         const uint64_t r = rank_of(list[j]);
         if (side(__uint_as_float(list[j].x)) != 1) continue;
@@ -515,8 +522,8 @@ __device__ __forceinline__ bool select_listed(const uint2* list, int listed, int
 template <int NT>
 __device__ __forceinline__ void write_listed(const uint2* list, int listed, int n, int k, const uint32_t* sel,
                                              uint16_t* before, int* scan_scratch, const int* __restrict__ map,
-                                             int* __restrict__ out_idx, float* __restrict__ out_val) {
-  const int tid = threadIdx.x, nwords = (n + 31) / 32;
+                                             int* __restrict__ out_idx, float* __restrict__ out_val, int tid) {
+  const int nwords = (n + 31) / 32;
   const int wpt = (nwords + NT - 1) / NT;
   const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
   int cnt = 0;
@@ -544,8 +551,7 @@ __device__ __forceinline__ void write_listed(const uint2* list, int listed, int 
 // row than the rest of the work takes.  Workgroup (range, t, seq) of this
 // kernel finds the row's bracket from the sample, as every workgroup of the row does, and lists the
 // elements of its key range that reach it in the range's segment of the workspace; topk_kernel<LISTED>
-// selects from the segments of a row.  Two launches: rows up to 65536 elements are faster in one (32768:
-// 13.8 us against 17.3 us; 131072: 24.0 us against 21.2 us).
+// selects from the segments of a row.
 constexpr int kMaxRanges = 16;      // key ranges (workgroups) per row
 constexpr int kSegCap = 6936;       // entries of a segment, behind them 64 of slack
 constexpr int kSegInts = 64 + 2 * (kSegCap + 64);   // header (fill, or -1: no bracket; bracket at 8 .. 10), then entries
@@ -571,7 +577,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_prefilter_kernel(Prob p, co
   float held[kHeldLong];
   Bracket br = {0.f, 0.f, 0.f};
   Stream<NT, 2> st;
-  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, held, hist, L, br, [&] { st.begin(s + lo, hi - lo); });
+  const bool ok = sample_bracket<NT, false>(s, n, p.L, k, held, hist, L, br, [&] { st.begin(s + lo, hi - lo, threadIdx.x); });
   if (ok) st.filter(br.lo, lo, reinterpret_cast<uint2*>(seg + 64), kSegCap, &L.list_fill);
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -618,7 +624,7 @@ enum { kRowShort, kRowLong, kRowListed, kRowPlain };   // held in registers / st
 // The `need` lowest-index elements of the bitmap eq into sel (words are owned by one thread here).
 template <int NT>
 __device__ __forceinline__ void mark_lowest(const uint32_t* eq, uint32_t* sel, int nwords, int need, int* scan_scratch) {
-  const int tid = threadIdx.x;
+  const int tid = this_thread();
   const int wpt = (nwords + NT - 1) / NT;
   const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
   int cnt = 0;
@@ -647,7 +653,7 @@ __device__ __forceinline__ void mark_lowest(const uint32_t* eq, uint32_t* sel, i
 template <int NT>
 __device__ __forceinline__ void write_marked(const float* __restrict__ s, int n, int k, const uint32_t* sel, int* scan_scratch,
                                              const int* __restrict__ map, int* __restrict__ out_idx, float* __restrict__ out_val) {
-  const int tid = threadIdx.x, nwords = (n + 31) / 32;
+  const int tid = this_thread(), nwords = (n + 31) / 32;
   const int wpt = (nwords + NT - 1) / NT;
   const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
   int cnt = 0;
@@ -676,7 +682,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
   // dyn: sel bitmap, histogram, then eq bitmap OR list (keys, idx)
   int* const scan_scratch = L.scan_scratch;
   int* const thr = L.thr;
-  const int tid = threadIdx.x;
+  const int tid = this_thread();
   uint32_t* sel = dyn;
   uint32_t* region = dyn + sel_words(row_len);
   int* hist = reinterpret_cast<int*>(region);
@@ -686,7 +692,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
   const int nwords = (n + 31) / 32;
   for (int i = tid; i < nwords; i += NT) sel[i] = 0;
   if (tid == 0) { L.list_fill = 0; L.few_len = 0; }
-  zero_hist_n<NT>(hist);
+  clear_hist<NT>(hist);
   if (k < n || skip_lowest) {   // otherwise every element is selected
     // ---- pass 1: histogram of the top 11 bits
     scan_row<NT>(s, 0, n, [&](int, float v, bool in) {
@@ -718,7 +724,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
     int need = thr[1];
     const bool listed = thr[2] <= list_cap;
     __syncthreads();
-    zero_hist_n<NT>(hist);
+    clear_hist<NT>(hist);
 
     if (listed) {
       // ---- pass 2: mark digit1 > d1, compact digit1 == d1 into the LDS list
@@ -759,7 +765,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
         }
       } else {
       __syncthreads();
-      zero_hist_n<NT>(hist);
+      clear_hist<NT>(hist);
       for (int i = tid; i < len; i += NT) {
         const uint32_t key = lkey[i], kp = key >> 10;
         if (kp > p22) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
@@ -771,7 +777,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
       need = thr[1];
       const int ties = thr[2];
       __syncthreads();
-      zero_hist_n<NT>(hist);
+      clear_hist<NT>(hist);
       if (ties == need) {
         for (int i = tid; i < len; i += NT)
           if (lkey[i] >= tkey) atomicOr(&sel[lidx[i] >> 5], 1u << (lidx[i] & 31));
@@ -789,7 +795,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
         const int hi_digit = kBins - 1 - thr[0];
         need = thr[1];
         __syncthreads();
-        zero_hist_n<NT>(hist);
+        clear_hist<NT>(hist);
         for (int i = tid; i < len; i += NT) {
           if (lkey[i] != tkey) continue;
           const int e = lidx[i];
@@ -822,7 +828,7 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
       const uint32_t d2 = thr[0];
       need = thr[1];
       __syncthreads();
-      zero_hist_n<NT>(hist);
+      clear_hist<NT>(hist);
       const uint32_t pre22 = (d1 << 11) | d2;
       scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
         const uint32_t key = order_key(v);
@@ -849,62 +855,94 @@ __device__ __forceinline__ void two_pass_row(const float* __restrict__ s, int n,
   write_marked<NT>(s, n, k, sel, scan_scratch, map, out_idx, out_val);
 }
 
-// Wavefront-uniform copies of a function's arguments (they arrive in vector registers).
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-template <typename T>
-__device__ __forceinline__ T* uniform(T* p) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  const uint64_t u = (uint64_t)(uint32_t)uniform((int)(a >> 32)) << 32 | (uint32_t)uniform((int)a);
-  return (T*)(__attribute__((address_space(1))) T*)u;   // (in global memory)
+struct TopkArgs {
+  Prob p;
+  const float* S;
+  int row_len, k;
+  const int* map;
+  int* idx;
+  float* val;
+  const int* pre;
+  int cap, list_cap;
+  bool all_slots;
+};
+struct TopkRow {   // a workgroup's row
+  const float* s;
+  int n;
+  const int* map;
+  int* idx;
+  float* val;
+};
+__device__ __forceinline__ TopkRow topk_row_of(const TopkArgs& a) {
+  // queries in descending order: under a causal mask the late ones have the longest rows, and
+  // the workgroups with the most work should start first
+  const int t = gridDim.x - 1 - blockIdx.x, seq = blockIdx.y;
+  const size_t row = (size_t)seq * a.p.n_q + t;
+  return {a.S + row * a.row_len, a.map || a.all_slots ? a.row_len : visible(a.p, seq, t),
+          a.map ? a.map + row * a.row_len : nullptr, a.idx + row * a.k, a.val ? a.val + row * a.k : nullptr};
 }
-using LdsWord = __attribute__((address_space(3))) uint32_t;
 
-// A row that the linear bracket did not do.  A function of its own: inlined, its registers cost the others 0.8 us
-// (8192 scores) to 2 us (32768), and 1000 rows of 131072 129 us instead of 110.  s: the row, n of row_len elements;
-// map: its candidates or null; skip_lowest: -inf is never selected.  passed: elements that reached the lower end of
-// the first bracket, -1: it had none, -2: not worth another.
+// The kernel's arguments once more, through an address that the compiler knows nothing of: kept in registers for
+// hard_row, they cost the rows that do not need it, and between its stages they cost spills.
+__device__ __forceinline__ const TopkArgs& kernel_args() {
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const TopkArgs*)p;
+}
+
+// A row that the linear bracket did not do (a stage of topk_kernel, whose arguments it reads).  passed: elements that
+// reached the lower end of the first bracket, -1: it had none, -2: not worth another.
 template <int NT>
-__device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int row_len, int k, const int* __restrict__ map,
-                                         int* __restrict__ out_idx, float* __restrict__ out_val, int cap, int list_cap,
-                                         int passed, int skip_lowest, uint32_t* dyn, TopkLds<NT>& L) {
-  int* const scan_scratch = L.scan_scratch;
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void hard_row(int passed, uint32_t* dyn, TopkLds<NT>& L) {
   uint32_t* sel = dyn;
-  uint32_t* region = dyn + sel_words(row_len);
-  uint32_t* eq = region + kBins;
-  const int nwords = (n + 31) / 32;
-
-  if (k < n && passed >= -1) {
-    Found found = kNoBracket;
-    uint2* list = reinterpret_cast<uint2*>(region);
-    uint16_t* before = reinterpret_cast<uint16_t*>(list + cap + 64);
-    int* sample_hist = reinterpret_cast<int*>(sel);
-    Bracket br;
+  int* sample_hist = reinterpret_cast<int*>(sel);
+  Found found = kNoBracket;
+  Bracket br;
+  auto write = [&](int listed) {
+    const TopkArgs& a = kernel_args();
+    const TopkRow r = topk_row_of(a);
+    const uint2* list = reinterpret_cast<uint2*>(dyn + sel_words(a.row_len));
+    uint16_t* before = reinterpret_cast<uint16_t*>(dyn + sel_words(a.row_len) + 2 * (a.cap + 64));
+    write_listed<NT>(list, listed, r.n, a.k, sel, before, L.scan_scratch, r.map, r.idx, r.val, this_thread());
+  };
+  if (passed >= -1 && kernel_args().k < topk_row_of(kernel_args()).n) {
     // where a list was not usable: the rank that would have listed a number between k and the capacity
-    const float aim = 0.5f * (float)(k + cap);
-    float adjust = passed < 0 ? 0.f : aim / (float)max(passed, 1);
+    auto aim = [&](int passed) {
+      const TopkArgs& a = kernel_args();
+      return 0.5f * (float)(a.k + a.cap) / (float)max(passed, 1);
+    };
+    float adjust = passed < 0 ? 0.f : aim(passed);
 #pragma unroll 1
     for (int attempt = 0; attempt < kAttempts; ++attempt) {
-      // adjust > 0: the lower end is the sample of adjust times the rank, the upper end is open
-      float held[held_hard(NT)];
       __syncthreads();
-      Sample sm = take_sample<NT, false>(s, n, row_len, k, this_thread(), held, [] {});
-      if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
-      if (tid < kFew) L.frank[tid] = 0;
-      if (adjust > 0.f) {
-        sm.r_lo = (int)ceilf(fminf((float)sm.r_lo * adjust, 1e6f));
-        sm.r_hi = 0;
-        sm.rank_up = max(sm.r_lo / 16, 1);
+      {
+        // adjust > 0: the lower end is the sample of adjust times the rank, the upper end is open
+        const TopkArgs& a = kernel_args();
+        const TopkRow r = topk_row_of(a);
+        const int tid = this_thread();
+        float held[held_hard(NT)];
+        Sample sm = take_sample<NT, false>(r.s, r.n, a.row_len, a.k, tid, held, [] {});
+        if (tid == 0) { L.few_len = 0; L.nan_seen = 0; L.list_fill = 0; }
+        if (tid < kFew) L.frank[tid] = 0;
+        if (adjust > 0.f) {
+          sm.r_lo = (int)ceilf(fminf((float)sm.r_lo * adjust, 1e6f));
+          sm.r_hi = 0;
+          sm.rank_up = max(sm.r_lo / 16, 1);
+        }
+        found = key_bracket<NT>(a.cap, sm, held, sample_hist, L, br);
       }
-      found = key_bracket<NT>(cap, sm, held, sample_hist, L, br);
       if (found != kBracket) break;
+      const TopkArgs& a = kernel_args();
+      const TopkRow r = topk_row_of(a);
+      const int k = a.k, cap = a.cap;
+      uint2* list = reinterpret_cast<uint2*>(dyn + sel_words(a.row_len));
       Stream<NT, 2> st;
-      st.begin(s, n);
+      st.begin(r.s, r.n, this_thread());
       st.filter(br.lo, 0, list, cap, &L.list_fill);
       __syncthreads();
       const int listed = L.list_fill;
-      if (select_listed<NT>(list, listed, cap, n, k, br, sel, L)) {
-        write_listed<NT>(list, listed, n, k, sel, before, scan_scratch, map, out_idx, out_val);
+      if (select_listed<NT>(list, listed, cap, r.n, k, br, sel, L, this_thread())) {
+        write(listed);
         return;
       }
       if (listed >= k && listed <= cap) {
@@ -912,103 +950,95 @@ __device__ __forceinline__ void hard_row(const float* __restrict__ s, int n, int
         adjust = 1.f;
         continue;
       }
-      adjust = (adjust > 0.f ? adjust : 1.f) * aim / (float)max(listed, 1);
+      adjust = (adjust > 0.f ? adjust : 1.f) * aim(listed);
     }
-    // ---- the k-th largest is one of many equal values: marked from the ballots of one more pass, the counts prove it
-    // (2048 rows of 65536, 99.5 % zeros: 1960 us when they were left to the two-pass path)
-    if (found == kPlateau) {
-      const uint32_t level = order_key(br.lo);
-      int above = 0, equal = 0;
-      __syncthreads();
-      scan_row<NT>(s, 0, n, [&](int i, float v, bool in) {
-        const uint32_t key = order_key(v);
-        const unsigned long long a = __builtin_amdgcn_ballot_w64(in && key > level), e = __builtin_amdgcn_ballot_w64(in && key == level);
-        const int lane = tid & 63, w = ((i - lane) >> 5) + lane;
-        if (lane < 2 && w < nwords) {
-          sel[w] = (uint32_t)(lane ? a >> 32 : a);
-          eq[w] = (uint32_t)(lane ? e >> 32 : e);
+  }
+  // ---- the k-th largest is one of many equal values: marked from the ballots of one more pass, the counts prove it
+  // (2048 rows of 65536, 99.5 % zeros: 1960 us when they were left to the two-pass path)
+  if (found == kPlateau) {
+    const TopkArgs& a = kernel_args();
+    const TopkRow r = topk_row_of(a);
+    const float* s = r.s;
+    const int n = r.n, k = a.k, nwords = (n + 31) / 32, tid = this_thread();
+    uint32_t* region = dyn + sel_words(a.row_len);
+    uint32_t* eq = region + kBins;
+    const uint32_t level = order_key(br.lo);
+    int above = 0, equal = 0;
+    __syncthreads();
+    scan_row<NT, 4>(s, 0, n, [&](int i, float v, bool in) {
+      const uint32_t key = order_key(v);
+      const unsigned long long more = __builtin_amdgcn_ballot_w64(in && key > level), same = __builtin_amdgcn_ballot_w64(in && key == level);
+      const int lane = tid & 63, w = ((i - lane) >> 5) + lane;
+      if (lane < 2 && w < nwords) {
+        sel[w] = (uint32_t)(lane ? more >> 32 : more);
+        eq[w] = (uint32_t)(lane ? same >> 32 : same);
+      }
+      above += __popcll(more);
+      equal += __popcll(same);
+    });
+    if ((tid & 63) == 0) { L.wave_sure[tid >> 6] = above; L.wave_more[tid >> 6] = equal; }
+    __syncthreads();
+    waves_before(L.wave_sure, NT / 64, &above);
+    waves_before(L.wave_more, NT / 64, &equal);
+    if (above < k && above + equal >= k) {
+      mark_lowest<NT>(eq, sel, nwords, k - above, L.scan_scratch);
+      write_marked<NT>(s, n, k, sel, L.scan_scratch, r.map, r.idx, r.val);
+      return;
+    }
+    if (above >= k && above <= a.cap) {
+      // the plateau ends above the k-th largest: what lies above it is the list
+      uint2* list = reinterpret_cast<uint2*>(region);
+      const int wpt = (nwords + NT - 1) / NT;
+      const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
+      int cnt = 0, total;
+      for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
+      int pos = block_exclusive_scan(cnt, L.scan_scratch, &total);
+      for (int w = w_lo; w < w_hi; ++w)
+        for (uint32_t bits = sel[w]; bits; bits &= bits - 1) {
+          const int i = w * 32 + __ffs(bits) - 1;
+          list[pos++] = make_uint2(__float_as_uint(s[i]), (uint32_t)i);
         }
-        above += __popcll(a);
-        equal += __popcll(e);
-      });
-      if ((tid & 63) == 0) { L.wave_sure[tid >> 6] = above; L.wave_more[tid >> 6] = equal; }
       __syncthreads();
-      waves_before(L.wave_sure, NT / 64, &above);
-      waves_before(L.wave_more, NT / 64, &equal);
-      if (above < k && above + equal >= k) {
-        mark_lowest<NT>(eq, sel, nwords, k - above, scan_scratch);
-        write_marked<NT>(s, n, k, sel, scan_scratch, map, out_idx, out_val);
+      clear_hist<NT>(sample_hist);
+      br.lo = key_value(level + 1);
+      br.hi = INFINITY;
+      br.edge = fmaxf(br.edge, key_value(level + 2));
+      if (select_listed<NT>(list, above, a.cap, n, k, br, sel, L, this_thread())) {
+        write(above);
         return;
       }
-      if (above >= k && above <= cap) {
-        // the plateau ends above the k-th largest: what lies above it is the list
-        const int wpt = (nwords + NT - 1) / NT;
-        const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
-        int cnt = 0, total;
-        for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
-        int pos = block_exclusive_scan(cnt, scan_scratch, &total);
-        for (int w = w_lo; w < w_hi; ++w)
-          for (uint32_t bits = sel[w]; bits; bits &= bits - 1) {
-            const int i = w * 32 + __ffs(bits) - 1;
-            list[pos++] = make_uint2(__float_as_uint(s[i]), (uint32_t)i);
-          }
-        __syncthreads();
-        zero_hist_n<NT>(sample_hist);
-        br.lo = key_value(level + 1);
-        br.hi = INFINITY;
-        br.edge = fmaxf(br.edge, key_value(level + 2));
-        if (select_listed<NT>(list, above, cap, n, k, br, sel, L)) {
-          write_listed<NT>(list, above, n, k, sel, before, scan_scratch, map, out_idx, out_val);
-          return;
-        }
-      }
-      __syncthreads();
     }
   }
   __syncthreads();
-
-  two_pass_row<NT>(s, n, row_len, k, map, out_idx, out_val, list_cap, skip_lowest != 0, dyn, L);
-}
-
-template <int NT>
-__device__ __attribute__((noinline)) void call_hard_row(const float* s, int n, int row_len, int k, const int* map, int* out_idx,
-                                                        float* out_val, int cap, int list_cap, int passed, int skip_lowest,
-                                                        LdsWord* dyn, LdsWord* lds) {
-  auto words = [](LdsWord* p) { return (uint32_t*)(LdsWord*)(uintptr_t)(uint32_t)uniform((int)(uintptr_t)p); };
-  hard_row<NT>(uniform(s), uniform(n), uniform(row_len), uniform(k), uniform(map), uniform(out_idx), uniform(out_val),
-               uniform(cap), uniform(list_cap), uniform(passed), uniform(skip_lowest), words(dyn),
-               *reinterpret_cast<TopkLds<NT>*>(words(lds)));
+  const TopkArgs& a = kernel_args();
+  const TopkRow r = topk_row_of(a);
+  two_pass_row<NT>(r.s, r.n, a.row_len, a.k, r.map, r.idx, r.val, a.list_cap, a.map || a.all_slots, dyn, L);
 }
 
 template <int NT, int KIND>
-__device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict__ S, int row_len,
-                                         int k, const int* __restrict__ map, int* __restrict__ idx,
-                                         float* __restrict__ val, const int* __restrict__ pre, int cap,
-                                         int list_cap, int t, int seq, uint32_t* dyn, bool all_slots = false) {
+__device__ __forceinline__ void topk_row(const TopkArgs& a, uint32_t* dyn) {
   // dyn: sel bitmap (sampled path: and its histograms), then the list of the sampled path, or the two-pass
   // path's histogram and its eq bitmap OR list (keys, idx)
   __shared__ TopkLds<NT> L;
 
   const int tid = threadIdx.x;
-  const size_t row = (size_t)seq * p.n_q + t;
-  const float* s = S + row * row_len;
-  const int n = (map || all_slots) ? row_len : visible(p, seq, t);
+  const TopkRow r = topk_row_of(a);
+  const float* s = r.s;
+  const int n = r.n, row_len = a.row_len, k = a.k, cap = a.cap;
+  const bool all = !a.map && !a.all_slots;   // -inf may be selected
   uint32_t* sel = dyn;
   uint2* list = reinterpret_cast<uint2*>(dyn + sel_words(row_len));
-  int* out_idx = idx + row * k;
-  float* out_val = val ? val + row * k : nullptr;
-  const int* map_row = map ? map + row * row_len : nullptr;
   int passed = -1;
 
-  if (k >= n && !map && !all_slots) {   // every element
+  if (k >= n && all) {   // every element
     for (int i = tid; i < k; i += NT) {
-      out_idx[i] = i < n ? i : -1;
-      if (out_val) out_val[i] = i < n ? s[i] : -INFINITY;
+      r.idx[i] = i < n ? i : -1;
+      if (r.val) r.val[i] = i < n ? s[i] : -INFINITY;
     }
     return;
   }
   if constexpr (KIND == kRowPlain) {
-    two_pass_row<NT>(s, n, row_len, k, map_row, out_idx, out_val, list_cap, map || all_slots, dyn, L);
+    two_pass_row<NT>(s, n, row_len, k, r.map, r.idx, r.val, a.list_cap, !all, dyn, L);
     return;
   } else if (k < n) {
     bool done = false;
@@ -1021,9 +1051,9 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
       if (tid == 0) { L.few_len = 0; L.nan_seen = 0; }
       if (tid < kFew) L.frank[tid] = 0;
       bool whole;
-      passed = gather_segments(pre + row * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br, whole);
+      passed = gather_segments(a.pre + ((size_t)blockIdx.y * a.p.n_q + (gridDim.x - 1 - blockIdx.x)) * ranges_row * kSegInts, (n + rlen - 1) / rlen, list, cap, br, whole);
       __syncthreads();
-      if (whole) done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+      if (whole) done = select_listed<NT>(list, passed, cap, n, k, br, sel, L, tid);
       // (a segment overflowed that the list will hold, or sure > k: the same lower end once more, the upper end open)
       if (!done && passed >= k && passed <= cap) passed = whole && L.nan_seen ? -2 : (k + cap) / 2;
     } else if constexpr (KIND == kRowShort) {
@@ -1038,39 +1068,35 @@ __device__ __forceinline__ void topk_row(const Prob& p, const float* __restrict_
         }
         __syncthreads();
         passed = L.list_fill;
-        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L, tid);
         if (!done && passed >= k && passed <= cap) passed = L.nan_seen ? -2 : (k + cap) / 2;
       }
     } else {
       float held[kHeldLong];
       Stream<NT, NT == kTopkThreads ? 4 : 6> st;         // (64 registers: 32 wavefronts per CU; 80: 24)
-      if (sample_bracket<NT, false>(s, n, row_len, k, held, sample_hist, L, br, [&] { st.begin(s, n); })) {
+      if (sample_bracket<NT, false>(s, n, row_len, k, held, sample_hist, L, br, [&] { st.begin(s, n, tid); })) {
         st.filter(br.lo, 0, list, cap, &L.list_fill);
         __syncthreads();
         passed = L.list_fill;
-        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L);
+        done = select_listed<NT>(list, passed, cap, n, k, br, sel, L, tid);
         if (!done && passed >= k && passed <= cap) passed = L.nan_seen ? -2 : (k + cap) / 2;
       }
     }
     if (done) {
-      write_listed<NT>(list, passed, n, k, sel, before, L.scan_scratch, map_row, out_idx, out_val);
+      const TopkArgs& b = kernel_args();
+      const TopkRow w = topk_row_of(b);
+      write_listed<NT>(list, passed, n, k, sel, before, L.scan_scratch, w.map, w.idx, w.val, tid);
       return;
     }
   }
-  call_hard_row<NT>(s, n, row_len, k, map_row, out_idx, out_val, cap, list_cap, passed, map || all_slots ? 1 : 0,
-                    (LdsWord*)dyn, (LdsWord*)reinterpret_cast<uint32_t*>(&L));
+  if constexpr (KIND != kRowPlain) hard_row<NT>(passed, dyn, L);
 }
 
 // Registers: 1024 threads leave room for two workgroups per CU, the smaller ones for 24 wavefronts.
 template <int NT, int KIND>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kTopkThreads ? 8 : 6, 8))) void topk_kernel(
-    Prob p, const float* __restrict__ S, int row_len, int k, const int* __restrict__ map,
-    int* __restrict__ idx, float* __restrict__ val, const int* __restrict__ pre, int cap, int list_cap, bool all_slots) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == kTopkThreads ? 8 : 6, 8))) void topk_kernel(TopkArgs a) {
   extern __shared__ __align__(16) uint32_t dyn[];
-  // queries in descending order: under a causal mask the late ones have the longest rows, and
-  // the workgroups with the most work should start first
-  topk_row<NT, KIND>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, gridDim.x - 1 - blockIdx.x, blockIdx.y,
-                     dyn, all_slots);
+  topk_row<NT, KIND>(a, dyn);
 }
 
 // Only the rows r with only[r] != 0 (rows another path could not finish).  Normally
@@ -1091,7 +1117,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_only_kernel(Prob p, const f
   }
 }
 
-// Rows are cut into ranges where there are fewer rows than CUs and the rows are long.
+// Rows are cut into ranges where there are fewer rows than CUs and the rows are long, whatever k is (us, one launch /
+// two: 65536 elements, k = 2048 17.0 / 15.8, k = 8192 21.1 / 22.0 and 128 rows of it 22.9 / 39.9; 100003, k = 2048
+// 20.9 / 17.0; 131072, k = 8192 28.0 / 23.4).
 static bool use_split(const Prob& p) {
   return (long long)p.n_seq * p.n_q < 256 && p.L > 65536;
 }
@@ -1155,7 +1183,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
       const dim3 ranges((p.L + rlen - 1) / rlen, p.n_q, p.n_seq);                                  \
       topk_prefilter_kernel<<<ranges, kTopkThreads, 0, st>>>(p, S, k, rlen, pre);                 \
     }                                                                                              \
-    topk_kernel<NT, KIND><<<grid, NT, lds, st>>>(p, S, row_len, k, map, idx, val, pre, cap, list_cap, all_slots); \
+    topk_kernel<NT, KIND><<<grid, NT, lds, st>>>(TopkArgs{p, S, row_len, k, map, idx, val, pre, cap, list_cap, all_slots}); \
   } while (0)
   if (only) {
     static LdsSeen seen;
