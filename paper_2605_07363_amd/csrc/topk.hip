@@ -106,7 +106,7 @@ __host__ __device__ inline int sel_words(int row_len) { return (max((row_len + 3
 // The histograms share their LDS with the bitmap, which is cleared once the last of them has been read.
 //
 // Measured: 4096 rows of 65536, k = 2048: 212 us = 5.1 TB/s (two passes over each row: 402 us; sample and
-// stream alone, nothing selected: 190 us); 64 rows of 32768: 14.4 us (17.3 us in two launches).  Few rows
+// stream alone, nothing selected: 190 us); 64 rows of 32768: 14.6 us (17.3 us in two launches).  Few rows
 // are a chain of barrier-separated phases of one workgroup.
 struct Bracket {
   float lo, hi;
