@@ -108,6 +108,7 @@ __device__ __forceinline__ void fp8x4_to_bf16x4(uint32_t w, uint32_t& lo, uint32
 union Frag {
   bf16x8 v;
   uint4 u;
+  u32x4 x;
   uint32_t w[4];
 };
 
@@ -115,6 +116,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(int)))) int i32x8;
 union Frag8 {   // 32 fp8 codes: one operand of the fp8 matrix instruction
   i32x8 v;
   uint4 u[2];
+  u32x4 x[2];
 };
 
 __device__ __forceinline__ uint4 buffer_load16(BufferRsrc r, uint32_t lane_off, uint32_t wave_off = 0) {
@@ -136,6 +138,11 @@ __device__ __forceinline__ T select_by_mask(unsigned long long mask, T a, T b) {
 }
 __device__ __forceinline__ void buffer_store4(BufferRsrc r, uint32_t lane_off, uint32_t wave_off, float x) {
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, (int)lane_off, (int)wave_off, 0);
+}
+
+// In the lower 32 lanes the value of lane + 32.
+__device__ __forceinline__ float upper_half(float x) {
+  return __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false)[1]);
 }
 
 // NT = 16-row head tiles; a wavefront takes STEPS pipeline steps of G 64-key groups each.
@@ -925,13 +932,12 @@ __global__ __launch_bounds__(256) void score_tile_repair_kernel(
 }
 
 // ------------------------------------------------------------------ candidate re-scoring
-// score_gather_kernel (bf16 queries, bf16 or fp8 keys, candidate lists): the
+// score_gather_kernel (bf16 queries, bf16 or fp8 keys, or fp8 codes on both sides; candidate lists): the
 // fine stage of MISA-dagger scores k' gathered keys of one query with ALL heads
 // (Eq. dsa_score on the candidate set).  The query's H head rows are the
-// stationary operand (RT 32-row tiles in registers); each wavefront gathers 32
-// candidate keys per step straight from the (cache-resident) key cache into
-// MFMA fragments - a lane reads one contiguous half row - and the head sum is
-// in-lane over its accumulator registers plus one exchange between half-waves.
+// stationary operand (RT 32-row tiles in registers); a wavefront takes 32 candidates per step, one
+// column of the matrix instruction each, and the head sum is in-lane over its accumulator registers plus one
+// exchange between half-waves.
 // Candidates per workgroup: at most kGatherChunk.  The set-up of a workgroup (head rows, gates,
 // candidate indices) costs about a fifth of the kernel with 2048 candidates each, so many-query
 // problems take 4096 (0.37 ms against 0.39 ms on the 2048 x 8192 re-rank); few-query problems
@@ -941,62 +947,35 @@ __global__ __launch_bounds__(256) void score_tile_repair_kernel(
 // produced (a slot's index has been consumed by then) and the row's top-k is taken from there by
 // small_row_topk - no dense score matrix, no second launch.
 //
-// Loads: a load instruction costs the cache lines that its quads of lanes touch.  With bf16 keys, and with
-// fp8 keys that need no widening, the four lanes of a quad read 64 contiguous bytes of one row (row i of
-// the quad's four with load i) and the 16-byte pieces are exchanged inside the quad (quad_transpose),
-// which leaves every lane with its own candidate's bytes: 245 us against 282 us for 1024 x 8192 bf16
-// candidates, 313 us against 335 us for 2 x 1024 x 8192 fp8 ones with their top-k.  Where the codes are
-// widened the vector instructions are the bound, the 32 of the exchange cost more than the lines they
-// save (427 us against 390 us for 2048 x 8192), and a lane reads its half row by itself.
+// Loads: a load instruction costs the texture addresser a clock per quad of lanes and cache line, so the rows are read
+// whole, by 8 (fp8) or 16 (bf16) consecutive lanes, and go through LDS that only this wavefront uses (rows padded by
+// one 16-byte slot: the 16 lanes that read together hit 16 bank groups) to the lanes whose columns they are.
+// (Fragments loaded straight by the lane that needs them touch 64 lines per instruction: 70 % of the kernel's time with
+// widened fp8 keys.)  The head sums of a row tile stand beside the matrix instructions of the next one, so that a
+// wavefront feeds both pipes, and the rows of two steps are in flight in registers.
+// Bound by matrix and vector instructions at the clock that the chip holds; 2048 queries x 8192 candidates with
+// their top-k: widened fp8 keys 388 -> 343 us, bf16 keys 495 -> 361 us, fp8 on both sides 313 -> 240 us (rows of one step
+// in flight 342, 362, 250 us; row tiles with two sets of accumulators: spills for bf16 keys).
 constexpr int kGatherChunk = 4096;
 
-// The 4 x 4 transpose of 16-byte pieces over the four lanes of a quad: piece r of lane j becomes piece j of
-// lane r.  Two stages of selects between a lane's own and a neighbour's register; 32 vector instructions.
-__device__ __forceinline__ void quad_transpose_2(uint32_t& a0, uint32_t& a1, uint32_t& a2, uint32_t& a3,
-                                                 uint32_t& b0, uint32_t& b1, uint32_t& b2, uint32_t& b3) {
-  uint32_t s0, s1, s2, s3, t0, t1, t2, t3;
-  // (two wait states between a vector write and its quad-permuted read, and before a matrix read: the
-  // operands may come from vector instructions, inside the block the order keeps them apart)
-#define MISA_X1 " quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-#define MISA_X2 " quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-  asm("s_mov_b32 vcc_lo, 0x55555555\n\ts_mov_b32 vcc_hi, 0x55555555\n\t"    // even lanes keep their own
-      "v_cndmask_b32_dpp %8, %1, %0, vcc" MISA_X1 "v_cndmask_b32_dpp %10, %3, %2, vcc" MISA_X1
-      "v_cndmask_b32_dpp %12, %5, %4, vcc" MISA_X1 "v_cndmask_b32_dpp %14, %7, %6, vcc" MISA_X1
-      "s_mov_b32 vcc_lo, 0xaaaaaaaa\n\ts_mov_b32 vcc_hi, 0xaaaaaaaa\n\t"    // odd lanes
-      "v_cndmask_b32_dpp %9, %0, %1, vcc" MISA_X1 "v_cndmask_b32_dpp %11, %2, %3, vcc" MISA_X1
-      "v_cndmask_b32_dpp %13, %4, %5, vcc" MISA_X1 "v_cndmask_b32_dpp %15, %6, %7, vcc" MISA_X1
-      "s_mov_b32 vcc_lo, 0x33333333\n\ts_mov_b32 vcc_hi, 0x33333333\n\t"    // lanes 0, 1 of a quad
-      "v_cndmask_b32_dpp %0, %10, %8, vcc" MISA_X2 "v_cndmask_b32_dpp %4, %14, %12, vcc" MISA_X2
-      "v_cndmask_b32_dpp %1, %11, %9, vcc" MISA_X2 "v_cndmask_b32_dpp %5, %15, %13, vcc" MISA_X2
-      "s_mov_b32 vcc_lo, 0xcccccccc\n\ts_mov_b32 vcc_hi, 0xcccccccc\n\t"    // lanes 2, 3
-      "v_cndmask_b32_dpp %2, %8, %10, vcc" MISA_X2 "v_cndmask_b32_dpp %6, %12, %14, vcc" MISA_X2
-      "v_cndmask_b32_dpp %3, %9, %11, vcc" MISA_X2 "v_cndmask_b32_dpp %7, %13, %15, vcc" MISA_X2
-      "s_nop 1"
-      : "+v"(a0), "+v"(a1), "+v"(a2), "+v"(a3), "+v"(b0), "+v"(b1), "+v"(b2), "+v"(b3),
-        "=&v"(s0), "=&v"(s1), "=&v"(s2), "=&v"(s3), "=&v"(t0), "=&v"(t1), "=&v"(t2), "=&v"(t3)
-      :
-      : "vcc");
-#undef MISA_X1
-#undef MISA_X2
-}
-__device__ __forceinline__ void quad_transpose(uint4& v0, uint4& v1, uint4& v2, uint4& v3) {
-  quad_transpose_2(v0.x, v1.x, v2.x, v3.x, v0.y, v1.y, v2.y, v3.y);
-  quad_transpose_2(v0.z, v1.z, v2.z, v3.z, v0.w, v1.w, v2.w, v3.w);
-}
-
-template <int KDT, int RT, bool Q8, bool FUSED>
-__global__ __launch_bounds__(256) void score_gather_kernel(
+template <int KDT, int RT, bool Q8, bool PAGED, bool FUSED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void score_gather_kernel(
     Prob p, const uint16_t* __restrict__ Q, const float* __restrict__ W,
     const void* __restrict__ K, const float* __restrict__ kscale, const int* __restrict__ cand,
     int k_cand, int chunk, float* __restrict__ out, int k, int* __restrict__ idx,
     float* __restrict__ val) {
   constexpr int ROW_BYTES = KDT == MISA_BF16 ? 256 : 128;
-  constexpr int NLD = KDT == MISA_BF16 ? 8 : 4;  // 16-byte loads per lane and key (half a row)
-  constexpr bool QUAD = Q8 || KDT == MISA_BF16;  // a quad of lanes reads 64 bytes of one row
+  constexpr int PPR = ROW_BYTES / 16;            // 16-byte pieces of a row = consecutive lanes that read it
+  constexpr int NLD = 32 * PPR / 64;             // 16-byte loads per lane and step
+  constexpr int RPL = 64 / PPR;                  // rows per load instruction
+  constexpr int PITCH = PPR + 1;                 // LDS slots per row
+  constexpr bool WIDEN = KDT == MISA_FP8_E4M3 && !Q8;
   const int t = blockIdx.y, seq = blockIdx.z;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int col = lane & 31, hf = lane >> 5;
   const int n = visible(p, seq, t);
+  const uint32_t n_last = (uint32_t)(max(n, 1) - 1);
   const size_t qrow = (size_t)seq * p.n_q + t;
   const int c_begin = blockIdx.x * chunk;            // chunk: a multiple of 128, at most kGatherChunk
   const int c_end = min(c_begin + chunk, k_cand);
@@ -1006,16 +985,27 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
   // The candidate indices of this workgroup go through LDS, so that reading them
   // in the loop does not wait on the key loads in flight.
   __shared__ __align__(16) int s_cand[FUSED ? kSmallTopkMax : kGatherChunk];
-  for (int i = threadIdx.x; i < chunk; i += 256) s_cand[i] = c_begin + i < c_end ? crow[c_begin + i] : -1;
+  __shared__ u32x4 s_rows[4][32 * PITCH];            // (later the scratch of the top-k)
+  for (int i0 = threadIdx.x; i0 < chunk; i0 += 4096) {   // (16 loads in flight)
+    int v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = crow[min(c_begin + i0 + 256 * u, k_cand - 1)];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const int i = i0 + 256 * u;
+      if (i < chunk) s_cand[i] = c_begin + i < c_end ? v[u] : -1;
+    }
+  }
 
   // Row m of tile rt is head rt*32 + m; half-wave hf holds components 64 hf .. 64 hf + 63,
   // k-step ks the eight from 64 hf + 8 ks (the key fragments use the same mapping).
   // Q8 (fp8 query codes and fp8 keys, fp8 matrix instruction): k-step ks of 64 components,
   // half-wave hf the 32 from 64 ks + 32 hf.
   static_assert(!Q8 || KDT == MISA_FP8_E4M3, "fp8 queries contract with fp8 keys only");
+  constexpr int KS = Q8 ? 2 : 8;
   Frag a[RT][Q8 ? 1 : 8];
   Frag8 a8[RT][Q8 ? 2 : 1];
-  __shared__ float s_gate[2][RT * 16];   // [half-wave][accumulator register]: gates of the rows a lane holds
+  float gate[RT * 16];                               // of the rows this lane holds
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     const int head = rt * 32 + col;
@@ -1036,131 +1026,201 @@ __global__ __launch_bounds__(256) void score_gather_kernel(
         a[rt][ks].u = head < p.H ? v : make_uint4(0, 0, 0, 0);
       }
     }
-  }
-  if (threadIdx.x < 2 * RT * 16) {
-    const int h2 = threadIdx.x / (RT * 16), e = threadIdx.x % (RT * 16), rt = e / 16, r = e % 16;
-    const int hd = rt * 32 + 8 * (r >> 2) + 4 * h2 + (r & 3);
-    s_gate[h2][e] = hd < p.H ? W[qrow * p.H + hd] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int hd = rt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
+      const float w = W[qrow * p.H + min(hd, p.H - 1)];
+      gate[rt * 16 + r] = hd < p.H ? w : 0.f;
+    }
   }
 
-  // Loads are unconditional and branch-free (slot and row clamped), so the number
-  // of loads in flight is the same on every path and waits stay exact.  QUAD: load i (of every four) of a
-  // lane reads, of the row of candidate i of its quad, the lane's own piece of the half row (64 bytes;
-  // bf16 keys: two such pieces).  Q8: pieces 0, 1 and 4, 5 from 2 hf on, the fp8 instruction's operand.
-  struct Raw { uint4 v[NLD]; float scale; int s; };
-  const int piece = !QUAD ? hf * (ROW_BYTES / 32) : Q8 ? 4 * ((lane & 3) >> 1) + 2 * hf + (lane & 1)
-                                                       : hf * (ROW_BYTES / 32) + (lane & 3);
-  const uint32_t piece_off = (uint32_t)piece * 16u;
-  const char* kseq = static_cast<const char*>(K) + (p.page_table ? 0 : (size_t)seq * p.L * ROW_BYTES);
-  auto issue = [&](Raw& r, int c0) {
-    const int base = min(c0 - c_begin, chunk - 32);      // (past the end: any slots, nothing of them is kept)
-    int s = s_cand[base + col];
-    if (c0 + col >= c_end || s >= n) s = -1;
-    r.s = s;
-    const size_t own = key_slot(p, seq, max(s, 0));
-    if constexpr (QUAD) {
-      const int4 four = *reinterpret_cast<const int4*>(&s_cand[base + (col & ~3)]);
-      auto visible_row = [&](int s) { return s >= 0 && s < n ? s : 0; };
-      const int rows[4] = {visible_row(four.x), visible_row(four.y), visible_row(four.z), visible_row(four.w)};
-      const char* src[4];
-      if (p.page_table) {
+  const char* kseq = static_cast<const char*>(K) + (PAGED ? 0 : (size_t)seq * p.L * ROW_BYTES);
+  const float* sseq = kscale + (PAGED ? 0 : (size_t)seq * p.L);
+  u32x4* const rows = s_rows[wave];
+  u32x4* const put_at = rows + (lane / PPR) * PITCH + lane % PPR;
+  const u32x4* const get_at = rows + col * PITCH + (Q8 ? 2 * hf : (PPR / 2) * hf);
+  // Any candidate value gives the address of a visible key (the last one where it is none); steps past the end
+  // read the last slots, of which nothing is kept.
+  struct Stage { u32x4 v[NLD]; };
+  struct Slots { int s[NLD]; };
+  auto slots_at = [&](int c0) __attribute__((always_inline)) { return &s_cand[min(c0 - c_begin, chunk - 32)]; };
+  auto read_slots = [&](Slots& sl, int c0) __attribute__((always_inline)) {   // candidates of the rows a lane helps to load
 #pragma unroll
-        for (int i = 0; i < 4; ++i) src[i] = kseq + key_slot<true>(p, seq, rows[i]) * ROW_BYTES + piece_off;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) src[i] = kseq + ((uint32_t)rows[i] * (uint32_t)ROW_BYTES + piece_off);
-      }
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) r.v[i] = *reinterpret_cast<const uint4*>(src[i & 3] + (i >> 2) * 64);
-    } else {
-      const uint4* src = reinterpret_cast<const uint4*>(static_cast<const char*>(K) + own * ROW_BYTES + piece_off);
-#pragma unroll
-      for (int i = 0; i < NLD; ++i) r.v[i] = src[i];
-    }
-    r.scale = 1.f;
-    if (KDT == MISA_FP8_E4M3) r.scale = kscale[own];
+    for (int i = 0; i < NLD; ++i) sl.s[i] = slots_at(c0)[lane / PPR + i * RPL];
   };
-  auto finish = [&](Raw& r, int c0) {
-    if (c0 >= c_end) return;
+  auto issue = [&](Stage& st, const Slots& sl) __attribute__((always_inline)) {
+    const uint32_t piece_off = (uint32_t)(lane % PPR) * 16u;
 #pragma unroll
-    for (int i = 0; i < (QUAD ? NLD : 0); i += 4) quad_transpose(r.v[i], r.v[i + 1], r.v[i + 2], r.v[i + 3]);
-    f32x16 acc[RT];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[rt][q] = 0.f;
-    if constexpr (Q8) {
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        Frag8 b;
-        b.u[0] = r.v[(2 * ks) % NLD];
-        b.u[1] = r.v[(2 * ks + 1) % NLD];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          acc[rt] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8[rt][ks].v, b.v, acc[rt], 0, 0, 0, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int ks = 0; ks < 8; ++ks) {
-        Frag b;
-        if (KDT == MISA_BF16) {
-          b.u = r.v[ks % NLD];
-        } else {
-          const uint4 w = r.v[(ks >> 1) % NLD];
-          fp8x4_to_bf16x4((ks & 1) ? w.z : w.x, b.w[0], b.w[1]);
-          fp8x4_to_bf16x4((ks & 1) ? w.w : w.y, b.w[2], b.w[3]);
-        }
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-          acc[rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt][ks].v, b.v, acc[rt], 0, 0, 0);
-      }
+    for (int i = 0; i < NLD; ++i) {
+      const uint32_t row = min((uint32_t)sl.s[i], n_last);
+      if (PAGED) st.v[i] = *reinterpret_cast<const u32x4*>(kseq + key_slot<true>(p, seq, (int)row) * ROW_BYTES + piece_off);
+      else st.v[i] = *reinterpret_cast<const u32x4*>(kseq + (row * (uint32_t)ROW_BYTES + piece_off));
     }
-    // (bf16 keys: sums of eight heads, then those: as exact as 16-row head tiles would give)
-    constexpr int PER = KDT == MISA_BF16 ? 8 : RT * 16;
-    float part[RT * 16 / PER];
+  };
+  auto put = [&](const Stage& st) __attribute__((always_inline)) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // (the fragments before have been read: LDS keeps a wavefront's order)
 #pragma unroll
-    for (int i = 0; i < RT * 16; ++i) {
-      if (i % PER == 0) part[i / PER] = 0.f;
-      part[i / PER] = fmaf(s_gate[hf][i], relu(acc[i / 16][i % 16]), part[i / PER]);
+    for (int i = 0; i < NLD; ++i) put_at[i * RPL * PITCH] = st.v[i];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  };
+  // A step's key fragments: pieces of the lane's own column.
+  struct Pieces { u32x4 v[Q8 ? 4 : KDT == MISA_BF16 ? 8 : 4]; };
+  auto get = [&](Pieces& f, int j) __attribute__((always_inline)) { f.v[j] = get_at[Q8 ? 4 * (j >> 1) + (j & 1) : j]; };
+  auto widen = [&](Frag& b, const Pieces& f, int ks) __attribute__((always_inline)) {
+    const u32x4 w = f.v[ks >> 1];
+    fp8x4_to_bf16x4(w[2 * (ks & 1)], b.w[0], b.w[1]);
+    fp8x4_to_bf16x4(w[2 * (ks & 1) + 1], b.w[2], b.w[3]);
+  };
+  struct Own { int s; float scale; };                // this lane's candidate of a step
+  auto own_scale = [&](Own& o) __attribute__((always_inline)) {
+    o.scale = 1.f;
+    if (KDT == MISA_FP8_E4M3) {
+      const int row = (int)min((uint32_t)o.s, n_last);
+      o.scale = PAGED ? sseq[key_slot<true>(p, seq, row)] : sseq[(uint32_t)row];
     }
+  };
+  // (bf16 keys: sums of eight heads, then those: as exact as 16-row head tiles would give)
+  constexpr int PER = KDT == MISA_BF16 ? 8 : RT * 16;
+  constexpr int NPART = RT * 16 / PER;
+  float part[NPART];                                 // running head sums of the step that is being finished
+  auto head_term = [&](const f32x16& acc, int i) __attribute__((always_inline)) {
+    const float x = relu(acc[i % 16]);
+    part[i / PER] = i % PER == 0 ? gate[i] * x : fmaf(gate[i], x, part[i / PER]);
+  };
+  auto finish = [&](const Own& o, int c0) __attribute__((always_inline)) {
     float sum = part[0];
 #pragma unroll
-    for (int i = 1; i < RT * 16 / PER; ++i) sum += part[i];
-    sum += __shfl_xor(sum, 32);
+    for (int i = 1; i < NPART; ++i) sum += part[i];
+    sum += upper_half(sum);
     const int slot = c0 + col;
     if (hf == 0 && slot < c_end) {
-      const float score = r.s >= 0 ? sum * r.scale : -INFINITY;
-      if (FUSED) s_cand[slot] = __float_as_int(score);   // (c_begin = 0; this slot's index was read at issue)
+      const float score = (uint32_t)o.s < (uint32_t)n ? sum * o.scale : -INFINITY;
+      if (FUSED) s_cand[slot] = __float_as_int(score);   // (c_begin = 0; this slot's index has been read)
       else orow[slot] = score;
     }
   };
-
-  // kDepth register buffers: the loads of a step are issued kDepth - 1 steps before they are
-  // used (a step of one wavefront is far shorter than the latency of a gathered row).
-  constexpr int kDepth = 2;
-  __builtin_amdgcn_s_waitcnt(0);  // the query operand has landed; in-loop waits concern only loop loads
-  __syncthreads();                // candidate indices are in LDS
-  auto stream_candidates = [&]() {
-    Raw buf[kDepth];
-    int c0 = c_begin + wave * 32;
+  // One pass: the matrix instructions of row tile rt of the step at c0, into acc_new, beside the
+  // head sums of the pass before (acc_old, row tile old_rt; HEADS false: there is none), so that one set of
+  // accumulators serves both.  The step's first pass puts the rows of the next step from registers into LDS (this step's
+  // pieces have all been read), issues the loads of the step after the next two and finishes the step before; its last
+  // pass reads the next step's pieces as this step's are used up.  (The order between the matrix instructions is left to
+  // the compiler: pinned with scheduling barriers the same code took 3 to 5 % longer.)
+  Stage odd, even;                                   // rows of the next two steps
+  Slots sl;
+  Frag b[WIDEN ? 8 : 1];
+  Pieces f;
+  Own own;
+  auto pass = [&](auto heads_tag, auto rt_tag, f32x16& acc_new, const f32x16& acc_old, Stage& st, int c0) __attribute__((always_inline)) {
+    constexpr bool HEADS = decltype(heads_tag)::value;
+    constexpr int rt = decltype(rt_tag)::value, old_rt = RT - 1 - rt;
+    constexpr bool FIRST = rt == 0, LAST = rt == RT - 1;
+    constexpr int TPM = 16 / KS;
+    constexpr int PUT = Q8 ? 0 : RT == 1 ? 1 : 2;    // k-step after which the rows go to LDS
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int s_new = 0;
 #pragma unroll
-    for (int d = 0; d < kDepth - 1; ++d) issue(buf[d], c0 + 128 * d);
-    while (true) {
-#pragma unroll
-      for (int d = 0; d < kDepth; ++d) {
-        issue(buf[(d + kDepth - 1) % kDepth], c0 + 128 * (kDepth - 1));
-        __builtin_amdgcn_sched_barrier(0);
-        finish(buf[d], c0);
-        c0 += 128;
-        if (c0 >= c_end) return;
+    for (int ks = 0; ks < KS; ++ks) {
+      if constexpr (Q8) {
+        Frag8 k8;
+        k8.x[0] = f.v[(2 * ks) & 3];
+        k8.x[1] = f.v[(2 * ks + 1) & 3];
+        acc_new = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8[rt][ks & 1].v, k8.v, ks == 0 ? zero : acc_new, 0, 0, 0, 0, 0, 0);
+      } else {
+        Frag kb;
+        if (WIDEN) kb = b[ks & 7];
+        else kb.x = f.v[ks % (sizeof(f.v) / 16)];
+        acc_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt][ks & 7].v, kb.v, ks == 0 ? zero : acc_new, 0, 0, 0);
       }
+#pragma unroll
+      for (int u = 0; u < (HEADS ? TPM : 0); ++u) head_term(acc_old, old_rt * 16 + ks * TPM + u);
+      if (FIRST && ks == PUT) {
+        put(st);
+        issue(st, sl);
+        s_new = slots_at(c0)[col];
+      }
+      if (LAST) {
+        auto next = [&](int j) __attribute__((always_inline)) {   // piece j (8 of them: bf16 fragments) of the next step
+          if (WIDEN) {
+            widen(b[j & 7], f, j);
+          } else {
+            get(f, j % (sizeof(f.v) / 16));
+          }
+        };
+        if (Q8) {
+          next(2 * ks);
+          next(2 * ks + 1);
+        } else if (RT == 2) {
+          next(ks);
+        } else if (ks >= 3) {                        // (one pass: after the rows have been put)
+          if (ks == 4) next(2);
+          if (ks == 5) next(4);
+          if (ks == 7) next(6);
+          next(ks == 3 ? 0 : ks == 4 ? 1 : ks == 5 ? 3 : ks == 6 ? 5 : 7);
+        }
+      }
+      if (WIDEN && FIRST && ks == (RT == 2 ? 5 : 2)) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) get(f, j);
+      }
+      if (LAST && ks == KS - 1) read_slots(sl, c0 + 512);
+    }
+    if (FIRST) {
+      if (HEADS) finish(own, c0 - 128);
+      own.s = s_new;
+      own_scale(own);
     }
   };
-  stream_candidates();
+  using Yes = std::true_type;
+  using No = std::false_type;
+  using Tile0 = std::integral_constant<int, 0>;
+  using Tile1 = std::integral_constant<int, RT - 1>;
+
+  const int c_first = c_begin + wave * 32;
+  const int steps = (c_end - c_first + 127) / 128;   // of this wavefront (none: <= 0)
+  __syncthreads();                                   // candidate indices are in LDS
+  if (steps > 0) {
+    f32x16 acc0, acc1;
+    {
+      Stage first;
+      read_slots(sl, c_first);
+      issue(first, sl);
+      read_slots(sl, c_first + 128);
+      issue(odd, sl);
+      read_slots(sl, c_first + 256);
+      issue(even, sl);
+      put(first);
+    }
+    read_slots(sl, c_first + 384);
+#pragma unroll
+    for (int j = 0; j < (int)(sizeof(f.v) / 16); ++j) get(f, j);
+#pragma unroll
+    for (int j = 0; j < (WIDEN ? 8 : 0); ++j) widen(b[j], f, j);
+    auto rest = [&](const f32x16& acc, int c) __attribute__((always_inline)) {   // the head sums of the last pass
+#pragma unroll
+      for (int e = 0; e < 16; ++e) head_term(acc, (RT - 1) * 16 + e);
+      finish(own, c);
+    };
+    pass(No{}, Tile0{}, acc0, acc1, odd, c_first);
+    if (RT == 2) pass(Yes{}, Tile1{}, acc1, acc0, odd, c_first);
+    int c0 = c_first + 128;
+    for (int i = 1;; i += 2, c0 += 256) {
+      if (i >= steps) { rest(RT == 2 ? acc1 : acc0, c0 - 128); break; }
+      if constexpr (RT == 2) {
+        pass(Yes{}, Tile0{}, acc0, acc1, even, c0);
+        pass(Yes{}, Tile1{}, acc1, acc0, even, c0);
+      } else {
+        pass(Yes{}, Tile0{}, acc1, acc0, even, c0);
+      }
+      if (i + 1 >= steps) { rest(acc1, c0); break; }
+      pass(Yes{}, Tile0{}, acc0, acc1, odd, c0 + 128);
+      if constexpr (RT == 2) pass(Yes{}, Tile1{}, acc1, acc0, odd, c0 + 128);
+    }
+  }
   if constexpr (FUSED) {
-    __shared__ SmallTopkLds topk_lds;
-    __syncthreads();                // all scores of the row are in LDS
-    small_row_topk(s_cand, k_cand, k, crow, idx + qrow * k, val ? val + qrow * k : nullptr, topk_lds);
+    static_assert(sizeof(SmallRowLds) <= sizeof(s_rows), "the top-k works in the rows' LDS");
+    __syncthreads();                // all scores of the row are in LDS, the rows' LDS is free
+    small_row_topk(s_cand, k_cand, k, crow, idx + qrow * k, val ? val + qrow * k : nullptr,
+                   *reinterpret_cast<SmallRowLds*>(&s_rows[0][0]));
   }
 }
 
@@ -1320,11 +1380,13 @@ static hipError_t launch_gather(const Prob& p, const void* Q, const float* W, co
   while (chunk > 512 && rows * ((k_cand + chunk - 1) / chunk) < 1024) chunk /= 2;
   const dim3 grid((k_cand + chunk - 1) / chunk, p.n_q, p.n_seq);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
+#define GO(RT, PAGED) score_gather_kernel<KDT, RT, Q8, PAGED, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr)
   if (p.H <= 32) {
-    score_gather_kernel<KDT, 1, Q8, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr);
+    if (p.page_table) GO(1, true); else GO(1, false);
   } else {
-    score_gather_kernel<KDT, 2, Q8, false><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, out, 0, nullptr, nullptr);
+    if (p.page_table) GO(2, true); else GO(2, false);
   }
+#undef GO
   return hipGetLastError();
 }
 
@@ -1344,11 +1406,13 @@ static hipError_t launch_gather_topk(const Prob& p, const void* Q, const float* 
   const int chunk = (k_cand + 255) / 256 * 256;
   const dim3 grid(1, p.n_q, p.n_seq);
   const uint16_t* q = static_cast<const uint16_t*>(Q);
+#define GO(RT, PAGED) score_gather_kernel<KDT, RT, Q8, PAGED, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val)
   if (p.H <= 32) {
-    score_gather_kernel<KDT, 1, Q8, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val);
+    if (p.page_table) GO(1, true); else GO(1, false);
   } else {
-    score_gather_kernel<KDT, 2, Q8, true><<<grid, 256, 0, st>>>(p, q, W, K, kscale, cand, k_cand, chunk, nullptr, k, idx, val);
+    if (p.page_table) GO(2, true); else GO(2, false);
   }
+#undef GO
   return hipGetLastError();
 }
 

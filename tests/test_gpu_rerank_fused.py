@@ -244,3 +244,40 @@ def test_many_query_rerank_writes_only_its_outputs(misa):
     assert torch.all(vbuf[:pad] == 3.25) and torch.all(vbuf[pad + ROWS * k:] == 3.25)
     assert torch.equal(cand, before)
     assert torch.all(idx >= -1) and torch.all(idx < L)
+
+
+@pytest.mark.parametrize("kc,k,H,k_dtype", [
+    (2047, 512, 64, "bf16"),      # the longest list that is not sampled
+    (2048, 512, 64, "e4m3"),      # the shortest that is, exactly eight scores per thread
+    (2049, 2040, 32, "bf16"),     # one score in the last walk; more wanted than the sample can bracket
+    (2303, 1, 64, "e4m3"),        # no upper end
+    (5000, 1250, 64, "bf16"),
+    (8192, 6000, 33, "e4m3"),     # more listed than a wavefront's segment holds
+    (8191, 2048, 64, "bf16"),
+])
+def test_many_query_rerank_sampled_selection(misa, kc, k, H, k_dtype):
+    """Lists from which the kernel takes a sampled bracket, against the two-kernel path bit for bit: ordinary scores,
+    the k-th largest on a plateau, more than 64 equal scores, infinite and NaN scores, few valid candidates."""
+    seed, L = 9960 + kc % 97, 9000
+    rng = np.random.default_rng(seed)
+    wl, inp = _problem(seed, k_dtype, "bf16", H, L)
+    K = inp["K"]
+    if k_dtype == "bf16":
+        K[0, 100:400] = K[0, 100]                          # 300 equal scores
+        K[0, 7000, 5] = 0x7F80                             # an infinite component: +-inf or NaN scores
+        K[0, 7500, 9] = 0x7FC0                             # NaN
+    else:
+        K[0, 100:400] = K[0, 100]
+        K[0, 7500, 9] = 0x7F
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    cand = _candidates(rng, ROWS, L, kc, full=True)
+    cand[0, :50, min(kc, 300):] = -1                       # few valid candidates
+    cand[0, 50:100, ::2] = -1
+    cand[0, 100:800][cand[0, 100:800] == 7000] = 6999      # rows without the odd keys
+    cand[0, 100:800][cand[0, 100:800] == 7500] = 7499
+    dcand = torch.from_numpy(cand).cuda()
+    idx, val = _rerank(misa, p, dv, dcand, kc, k)
+    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k)
+    assert torch.equal(idx, idx2)
+    assert torch.equal(val.view(torch.int32), val2.view(torch.int32))
