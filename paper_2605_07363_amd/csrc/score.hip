@@ -1298,6 +1298,10 @@ int tile_key_ranges(const Prob& p, bool routed, bool q8, int mode, int* keys_per
   // the chip several times, at least 1024 keys each.
   int splits = 8;
   while (splits < 64 && (long long)splits * q_tiles * p.n_seq < 2048 && lt / (splits * 2) >= 1024) splits *= 2;
+  // Where that leaves CUs without a workgroup, ranges of down to four tiles, while all of them run at once (two per
+  // CU; us, 1024 keys / this: 333 queries x 10007 keys 26.3 / 16.1, 32 x 10007 20.5 / 9.9, 8 x 4096 13.0 / 9.6,
+  // 1000 x 10007 30.2 / 27.8; past two per CU, 400 x 20000 in ranges of 313 keys 31.9, of 625 25.5).
+  while (splits < 64 && 2ll * splits * q_tiles * p.n_seq <= 512 && lt / (splits * 2) >= 256) splits *= 2;
   *keys_per_wg = ((lt + splits - 1) / splits + kKT - 1) / kKT * kKT;
   return (lt + *keys_per_wg - 1) / *keys_per_wg;
 }
