@@ -16,6 +16,7 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
 // Device-side view of misa_problem (host fills it after validation).
 struct Prob {
@@ -61,6 +62,10 @@ template <>
 struct Vec16<MISA_F32> {
   static constexpr int N = 4;
   static constexpr int ROW_BYTES = kD * 4;
+  __device__ static __forceinline__ void unpack(const u32x4& v, float* out) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = __uint_as_float(v[i]);
+  }
   __device__ static __forceinline__ void load(const void* p, float* out) {
     const float4 v = *reinterpret_cast<const float4*>(p);
     out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
@@ -70,6 +75,13 @@ template <>
 struct Vec16<MISA_BF16> {
   static constexpr int N = 8;
   static constexpr int ROW_BYTES = kD * 2;
+  __device__ static __forceinline__ void unpack(const u32x4& v, float* out) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      out[2 * i] = __uint_as_float(v[i] << 16);
+      out[2 * i + 1] = __uint_as_float(v[i] & 0xFFFF0000u);
+    }
+  }
   __device__ static __forceinline__ void load(const void* p, float* out) {
     const uint4 v = *reinterpret_cast<const uint4*>(p);
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -177,7 +189,6 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* scratch, int* to
 // Buffer descriptors (raw, unstrided): accesses at byte offsets >= num_bytes read zeros and
 // drop stores.  Addresses are descriptor base + per-lane byte offset + wave-uniform byte offset.
 using BufferRsrc = __amdgpu_buffer_rsrc_t;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 // base and num_bytes must be the same in every lane: they are moved to scalar registers here,
 // so that the compiler keeps the descriptor there instead of looping over "distinct" lanes.
 __device__ __forceinline__ BufferRsrc make_rsrc(const void* base, uint32_t num_bytes) {

@@ -6,8 +6,11 @@
 // bf16 nearest to each value and the bf16 nearest to the exact remainder, and
 // both are multiplied, so the products carry the pooled key to 2^-17 relative.  ReLU, the causal
 // block mask and the sum over blocks stay in accumulator lanes until the end
-// of the block range, when one wavefront reduction per row writes the partial
-// sum to the workspace.
+// of the block range, when they are added by lane shifts and go through LDS to one
+// lane per row, which writes the partial sum to the workspace.  (333 queries of 64
+// heads, 157 blocks, with the finalisation: 26.9 us with 160 lane exchanges and a
+// division per row and lane, tiles requested after the causal limits were known, and a
+// finalisation of dependent rounds; 14.5 us now.)
 // route_partial_kernel (fp32 queries): lane = head.  Each lane keeps its query head in
 // registers; the pooled key of the block being visited is the same for the
 // whole wavefront, so it is fetched with wave-uniform (scalar) loads and every
@@ -110,6 +113,12 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v;
 }
 
+// Sum over each half of the wavefront, in its last lane (all lanes active).
+__device__ __forceinline__ float half_sum(float v) {
+  v = row16_sum(v);
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x142, 0xa, 0xf, false));   // row_bcast:15
+}
+
 union RFrag {
   bf16x8 v;
   uint4 u;
@@ -134,6 +143,23 @@ __global__ __launch_bounds__(256) void route_tile_kernel(Prob p, int splits,
 
   const int per = (p.M + splits - 1) / splits;
   const int b_lo = split * per, b_hi = min(b_lo + per, p.M);
+
+  // (the first tiles are requested before anything else: with a few tiles per workgroup the kernel is their latency)
+  const float* kp_seq = Kp + (size_t)seq * p.M * kD;
+  float4 stage[2][4];  // two sets: with CP == 1 tiles are requested two iterations ahead
+  auto load_tile = [&](int b0, auto set_tag) {
+    constexpr int SET = decltype(set_tag)::value;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int e = tid + 256 * i;               // float4 index inside the 32 x 128 tile
+      const int row = e >> 5;
+      stage[SET][i] = *reinterpret_cast<const float4*>(kp_seq + (size_t)min(b0 + row, p.M - 1) * kD + (e & 31) * 4);
+    }
+  };
+  using Set0 = std::integral_constant<int, 0>;
+  using Set1 = std::integral_constant<int, 1>;
+  load_tile(b_lo, Set1{});
+  if (CP == 1) load_tile(b_lo + kRouteKT, Set0{});  // staged during the first iteration
 
   // stationary operand
   RFrag a[2][8];
@@ -172,17 +198,6 @@ __global__ __launch_bounds__(256) void route_tile_kernel(Prob p, int splits,
   __syncthreads();
   const int b_stop = s_stop;
 
-  const float* kp_seq = Kp + (size_t)seq * p.M * kD;
-  float4 stage[2][4];  // two sets: with CP == 1 tiles are requested two iterations ahead
-  auto load_tile = [&](int b0, auto set_tag) {
-    constexpr int SET = decltype(set_tag)::value;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = tid + 256 * i;               // float4 index inside the 32 x 128 tile
-      const int row = e >> 5;
-      stage[SET][i] = *reinterpret_cast<const float4*>(kp_seq + (size_t)min(b0 + row, p.M - 1) * kD + (e & 31) * 4);
-    }
-  };
   auto store_tile = [&](int buf, auto set_tag) {
     constexpr int SET = decltype(set_tag)::value;
 #pragma unroll
@@ -206,14 +221,8 @@ __global__ __launch_bounds__(256) void route_tile_kernel(Prob p, int splits,
 #pragma unroll
     for (int r = 0; r < 16; ++r) sum[rt][r] = 0.f;
 
-  using Set0 = std::integral_constant<int, 0>;
-  using Set1 = std::integral_constant<int, 1>;
   int buf = 0;
-  if (b_lo < b_stop) {
-    load_tile(b_lo, Set1{});
-    store_tile(0, Set1{});
-    if (CP == 1) load_tile(b_lo + kRouteKT, Set0{});  // staged during the first iteration
-  }
+  if (b_lo < b_stop) store_tile(0, Set1{});
   __builtin_amdgcn_s_waitcnt(0);  // prologue loads have landed; in-loop waits concern only loop loads
   __syncthreads();
   int it = 0;
@@ -284,20 +293,23 @@ __global__ __launch_bounds__(256) void route_tile_kernel(Prob p, int splits,
     b0 += kRouteKT;
   }
 
-  // sum over the 32 block columns of each half-wave, then one lane per row writes
+  // sum over the 32 block columns of each half-wave; the sums go through LDS of the wavefront to one lane per row
+  __shared__ __align__(16) float s_sum[4][64];
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      float v = sum[rt][r];
-#pragma unroll
-      for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o);
-      const int rr = row0 + rt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-      if (col == 0 && rr < rows_per_seq) {
-        const int t = rr / p.H, j = rr % p.H;
-        part[(((size_t)seq * p.n_q + t) * (splits * CP) + split * CP + phase) * kWave + j] = v;
-      }
+    for (int g = 0; g < 4; ++g) {
+      const float4 v = make_float4(half_sum(sum[rt][4 * g]), half_sum(sum[rt][4 * g + 1]), half_sum(sum[rt][4 * g + 2]),
+                                   half_sum(sum[rt][4 * g + 3]));
+      if (col == 31) *reinterpret_cast<float4*>(&s_sum[wave][rt * 32 + 8 * g + 4 * hf]) = v;
     }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  const int rr = row0 + lane;
+  if (rr < rows_per_seq) {
+    const int t = rr / p.H, j = rr - t * p.H;
+    part[(((size_t)seq * p.n_q + t) * (splits * CP) + split * CP + phase) * kWave + j] = s_sum[wave][lane];
+  }
 }
 
 // Few query-head rows (decode: n_q * H <= 64 in one workgroup; up to 7 queries of any head count: blockIdx.z
@@ -396,12 +408,15 @@ __global__ __launch_bounds__(256) void route_few_kernel(Prob p, int tiles_per_wa
   }
 }
 
+// Bound by latency for few queries (a chain of a few rounds of loads: what does not depend on another is requested
+// first) and by reading the queries again for many: 4096 of 64 heads 23.6 -> 16.9 us, 333 of them 11.2 -> 5.9 us.
 template <int KDT, int QDT>
 __global__ __launch_bounds__(128) void route_finalize_kernel(
     Prob p, int splits, const void* __restrict__ Q, const float* __restrict__ W,
     const void* __restrict__ K, const float* __restrict__ kscale, const float* __restrict__ part,
     int* __restrict__ heads, float* __restrict__ E) {
-  __shared__ float tailk[kD];
+  __shared__ __align__(16) float tailk[kD];
+  __shared__ __align__(16) float tsum[128 / (kD / Vec16<KDT>::N)][kD];
   __shared__ __align__(16) float Es[kMaxH];
   __shared__ float sred[4][kMaxH];
   __shared__ float sdot[kMaxH];
@@ -414,27 +429,49 @@ __global__ __launch_bounds__(128) void route_finalize_kernel(
   const size_t q_head = ((size_t)seq * p.n_q + t) * p.H + min(tid, p.H - 1);
   const float gate = W[q_head];   // (requested before the chain of round trips that it ends)
 
-  if (tail) {  // mean of keys nfull*B .. n-1, component tid
-    const char* base = static_cast<const char*>(K);
-    auto key_component = [&](int row) {
-      const size_t slot = key_slot(p, seq, row);
-      const char* src = base + slot * KV::ROW_BYTES;
-      if (KDT == MISA_F32) return reinterpret_cast<const float*>(src)[tid];
-      if (KDT == MISA_BF16) return bf16_bits_to_float(reinterpret_cast<const uint16_t*>(src)[tid]);
-      const uint32_t w = reinterpret_cast<const uint32_t*>(src)[tid >> 2];
-      const f32x2 pr = __builtin_amdgcn_cvt_pk_f32_fp8(w >> ((tid & 2) * 8), false);
-      return pr[tid & 1] * kscale[slot];
-    };
-    // rows are added in order; 32 loads are in flight at a time (the workgroup's run time is the
-    // latency of these rounds, and a block of 64 has at most two of them)
-    float s = 0.f;
-    for (int row = nfull * p.B; row < n; row += 32) {
-      float v[32];
+  // The query's H rows are one contiguous piece, read in 16-byte chunks in thread order; the first eight of a thread are
+  // requested before the tail block, whose mean they wait for.
+  using QV = Vec16<QDT>;
+  constexpr int CPH = kD / QV::N;  // chunks per head row: 32 (fp32) or 16 (bf16)
+  constexpr int QU = 8;
+  const char* qrow = static_cast<const char*>(Q) + ((size_t)seq * p.n_q + t) * p.H * QV::ROW_BYTES;
+  const int q_chunks = p.H * CPH;
+  u32x4 qraw[QU];
+  auto request_queries = [&](int base) {
 #pragma unroll
-      for (int u = 0; u < 32; ++u) v[u] = key_component(min(row + u, n - 1));
+    for (int u = 0; u < QU; ++u)
+      qraw[u] = *reinterpret_cast<const u32x4*>(qrow + (size_t)min(base + 128 * u + tid, q_chunks - 1) * 16);
+  };
+  if (tail) {  // mean of keys nfull*B .. n-1
+    // LPR consecutive lanes read a row, the workgroup RPI rows with one load each; eight loads in flight (the
+    // workgroup's run time is the latency of these rounds)
+    constexpr int LPR = kD / KV::N, RPI = 128 / LPR, U = 8;
+    const int lr = tid / LPR, lp = tid % LPR;
+    request_queries(0);
+    float acc[KV::N];
 #pragma unroll
-      for (int u = 0; u < 32; ++u) s += row + u < n ? v[u] : 0.f;
+    for (int e = 0; e < KV::N; ++e) acc[e] = 0.f;
+    for (int row = nfull * p.B + lr; row < n; row += RPI * U) {
+      float v[U][KV::N], scale[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const size_t slot = key_slot(p, seq, min(row + RPI * u, n - 1));
+        KV::load(static_cast<const char*>(K) + slot * KV::ROW_BYTES + lp * 16, v[u]);
+        scale[u] = KDT == MISA_FP8_E4M3 ? kscale[slot] : 1.f;
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (row + RPI * u < n) {
+#pragma unroll
+          for (int e = 0; e < KV::N; ++e) acc[e] = KDT == MISA_FP8_E4M3 ? fmaf(v[u][e], scale[u], acc[e]) : acc[e] + v[u][e];
+        }
     }
+#pragma unroll
+    for (int e = 0; e < KV::N; ++e) tsum[lr][lp * KV::N + e] = acc[e];
+    __syncthreads();
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < RPI; ++i) s += tsum[i][tid];
     tailk[tid] = s / (float)r;
   }
   // Partial sums of the block tiles: the 128 threads form 4 (H <= 32) or 2 groups of one thread
@@ -458,24 +495,24 @@ __global__ __launch_bounds__(128) void route_finalize_kernel(
   __syncthreads();
 
   if (tail) {
-    // q_j . (tail mean) for all heads: the query's H rows are one contiguous piece, read in
-    // 16-byte chunks in thread order; the CPH consecutive lanes that hold a head's chunks add
-    // their partial products with a butterfly, and the first of them keeps the sum.
-    using QV = Vec16<QDT>;
-    constexpr int CPH = kD / QV::N;  // chunks per head row: 32 (fp32) or 16 (bf16)
-    const char* qrow = static_cast<const char*>(Q) + ((size_t)seq * p.n_q + t) * p.H * QV::ROW_BYTES;
-    const int total = p.H * CPH, part_of = tid % CPH;
-    for (int base = 0; base < total; base += 128) {
-      const int c = base + tid;
-      float v[QV::N], d = 0.f;
-      if (c < total) {
-        QV::load(qrow + (size_t)c * 16, v);
+    // q_j . (tail mean) for all heads: the CPH consecutive lanes that hold a head's chunks add
+    // their partial products, and the last of them keeps the sum.
+    const int part_of = tid % CPH;
+    float tk[QV::N];
 #pragma unroll
-        for (int e = 0; e < QV::N; ++e) d = fmaf(v[e], tailk[part_of * QV::N + e], d);
+    for (int e = 0; e < QV::N; ++e) tk[e] = tailk[part_of * QV::N + e];
+    for (int base = 0; base < q_chunks; base += 128 * QU) {
+      if (base > 0) request_queries(base);
+#pragma unroll
+      for (int u = 0; u < QU; ++u) {
+        const int c = base + 128 * u + tid;
+        float v[QV::N], d = 0.f;
+        QV::unpack(qraw[u], v);
+#pragma unroll
+        for (int e = 0; e < QV::N; ++e) d = fmaf(v[e], tk[e], d);
+        d = CPH == 32 ? half_sum(d) : row16_sum(d);
+        if (part_of == CPH - 1 && c < q_chunks) sdot[c / CPH] = d;
       }
-#pragma unroll
-      for (int o = CPH / 2; o >= 1; o >>= 1) d += __shfl_xor(d, o);
-      if (part_of == 0 && c < total) sdot[c / CPH] = d;
     }
     __syncthreads();
   }
@@ -623,12 +660,17 @@ hipError_t launch_route(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
     else route_few_kernel<4><<<g1, 256, 0, st>>>(p, tpw, parts, q, Kp, part);
   } else if (q_dtype == MISA_BF16) {
     const int rg = route_row_groups(p);
-    total_splits = splits * (4 / rg);
-    const int rows = p.n_q * p.H;
-    const dim3 g1(splits, (rows + 64 * rg - 1) / (64 * rg), p.n_seq);
+    const int rows = p.n_q * p.H, groups = (rows + 64 * rg - 1) / (64 * rg);
+    // where CUs are left without a workgroup, down to one tile of 32 blocks per split, as far as there is room for the
+    // partial sums (us, 128 blocks / this: 8 queries of 64 x 64 blocks 13.4 / 12.7, 100 of 32 x 512 15.5 / 12.8; not past one
+    // workgroup per CU: 700 of 64 x 64 blocks 14.5 / 16.2 in two)
+    const long long most = std::min<long long>(std::min((p.M + kRouteKT - 1) / kRouteKT, splits * rg), 256 / ((long long)groups * p.n_seq));
+    const int s = std::max<int>(splits, (int)most);
+    total_splits = s * (4 / rg);
+    const dim3 g1(s, groups, p.n_seq);
     const uint16_t* q = static_cast<const uint16_t*>(Q);
-    if (rg == 4) route_tile_kernel<4><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);
-    else route_tile_kernel<2><<<g1, 256, 0, st>>>(p, splits, q, Kp, part);   // (one group: few rows)
+    if (rg == 4) route_tile_kernel<4><<<g1, 256, 0, st>>>(p, s, q, Kp, part);
+    else route_tile_kernel<2><<<g1, 256, 0, st>>>(p, s, q, Kp, part);   // (one group: few rows)
   } else {
     // few rows: a block per wavefront while that makes at most 64 partial sums (64 blocks: 6.8 us; 25 us in
     // one workgroup, whose wavefronts then take 16 blocks each one after the other), and no more workgroups

@@ -72,3 +72,30 @@ def test_head_scores_of_many_sequences(misa, n_seq, n_q, H, L, B, q_dtype):
             _, ref = O.route_heads(q, w, Ks, B, p.h, n)
             assert_scores_close(E[s, t].cpu().numpy(), ref, f"E {s} {t}")
             check_index_set(heads[s, t].cpu().numpy(), ref, p.h, f"heads {s} {t}")
+
+
+@pytest.mark.parametrize("k_dtype,q_dtype", [("bf16", "bf16"), ("e4m3", "bf16"), ("f32", "bf16"), ("bf16", "f32"), ("e4m3", "f32")])
+@pytest.mark.parametrize("H,L,B", [(64, 1400, 300), (37, 32 * 16 * 3 + 17, 16), (64, 32 * 40, 8), (20, 5000, 1024)])
+def test_head_scores_of_a_chunk_with_tails(misa, k_dtype, q_dtype, H, L, B):
+    """A prefill chunk whose workgroups do not fill the chip (block tiles split down to one each), and tail blocks of
+    every length at which the rounds of their loads end."""
+    tails = [1, 2, 3, 4, 5, 8, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257, B - 1, B]
+    tails = [t for t in tails if t <= B]
+    wl = WL.scaled(WL.WORKLOADS["c1"], n_seq=1, L=L, n_q=2 * len(tails), H=H, h=8, B=B, decode=False, k_dtype=k_dtype,
+                   q_dtype=q_dtype, needles=0)
+    inp = WL.make_inputs(wl, seed=L + H)
+    full = L // B - 1
+    inp["q_pos"] = np.array([full * B + t - 1 for t in tails] + [t - 1 for t in tails], dtype=np.int32)
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    Kp = torch.empty(1, p.M, 128, device="cuda")
+    misa.pool_keys(p, dv["K"], dv["kscale"], Kp, misa.alloc_workspace(p, misa.OP_POOL))
+    heads = torch.empty(1, p.n_q, p.h, dtype=torch.int32, device="cuda")
+    E = torch.empty(1, p.n_q, H, device="cuda")
+    misa.route_heads(p, dv["Q"], dv["W"], Kp, dv["K"], dv["kscale"], heads, E, misa.alloc_workspace(p, misa.OP_ROUTE))
+    torch.cuda.synchronize()
+    for t in range(p.n_q):
+        K, q, w, n = oracle_view(inp, 0, t)
+        _, ref = O.route_heads(q, w, K, B, p.h, n)
+        assert_scores_close(E[0, t].cpu().numpy(), ref, f"E {t}")
+        check_index_set(heads[0, t].cpu().numpy(), ref, p.h, f"heads {t}")
