@@ -1144,9 +1144,11 @@ static int pass_capacity(int row_len, int k, int nt, bool is_short, double sd) {
 hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const int* map, int* idx,
                        float* val, void* ws, hipStream_t st, const int* only, bool all_slots) {
   // Short rows: as many threads as hold the row; few rows of up to 4096 take 512 threads (7.3 us for one
-  // row against 9.3 us with 256).  Long rows: 1024 threads where there are few rows or the lists are
-  // long (a CU then holds one or two rows); many rows with short lists take 512, of which a CU holds
-  // three at different phases, so that memory is never idle (4096 x 65536: 212 us against 244 us).
+  // row against 9.3 us with 256).  Long rows: 1024 threads where there is at most one row per CU or the lists are
+  // long; more rows with shorter lists take 512, of which a CU holds
+  // three at different phases, so that memory is never idle (4096 x 65536: 212 us against 244 us), and two where there
+  // are less than two rows per CU (333 x 10007: 14.6 us against 17.8, 400 x 20000: 17.1 against 19.2; 200 x 65536: 21.6
+  // against 18.6).
   constexpr size_t kLdsMost = 156 * 1024;
   const bool is_short = !only && row_len <= 8192;
   const bool split = !map && !all_slots && !only && use_split(p);
@@ -1161,7 +1163,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
   int nt = row_len > 4096 ? kTopkThreads : few_rows ? 512 : 256;
   if (is_short) fits(nt, kLdsMost);
   else if (only) nt = kTopkThreads;
-  else if (split || (long long)p.n_q * p.n_seq < 512 || !fits(nt = 512, 53 * 1024)) {
+  else if (split || few_rows || !fits(nt = 512, (long long)p.n_q * p.n_seq < 512 ? 76 * 1024 : 53 * 1024)) {
     nt = kTopkThreads;
     // the longest rows have room for half the reserve; k well above 8192: the two-pass path
     if (!fits(nt, kLdsMost) && !fits(nt, kLdsMost, 3.0)) cap = 0;
