@@ -201,19 +201,232 @@ __global__ __launch_bounds__(kThrThreads) void select_threshold_kernel(
 }
 
 // ---------------------------------------------------------------- select
+// The usual row: one entry per thread brackets the k-th largest between two thresholds, a walk over the registers marks what lies above
+// the bracket and lists what lies inside, a histogram of the list finds the bin of the k-th, whose few entries are ranked
+// directly.  The entries are in index order, so the output place of one is the number of selected ones
+// before it, from the ballots.  The counts prove the bracket right or wrong; false (for all threads; nothing
+// written) where it is wrong or does not fit.
+constexpr int kRowSeg = 288;        // list entries of a wavefront, behind them 64 of slack
+template <int NT, int EPT>
+struct EntryLds {
+  uint2 word[EPT * (NT / 64)];      // selected entries: word u NW + wave holds u NT + 64 wave ..
+  int before[EPT * (NT / 64)];      // selected entries of the words before a word
+  uint2 few[64];                    // (key, entry)
+  int few_rank[64];
+  int sure[16], listed[16], valid[16];
+  int at_lo[3], at_hi[3];
+  float low[16], high[16];
+  int few_len, unlike;
+  uint32_t same;
+};
+template <int NT>
+constexpr size_t row_list_bytes() { return (size_t)(NT / 64) * (kRowSeg + 64) * 8; }
+
+template <int NT, int EPT>
+__device__ __forceinline__ bool select_sampled(const int (&ei)[EPT], const float (&ev)[EPT], int c, int chunks, int k, float tau, float top,
+                                               int* hist, int* scan_scratch, uint32_t* dyn, EntryLds<NT, EPT>& L,
+                                               int* __restrict__ out_idx, float* __restrict__ out_val) {
+  constexpr int NW = NT / 64;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  uint2* const list = reinterpret_cast<uint2*>(dyn) + wave * (kRowSeg + 64);
+  auto bin_of = [](float v, float from, float scale) {
+    return (int)__builtin_amdgcn_fmed3f((v - from) * scale, 0.f, (float)(kBins - 1));
+  };
+
+  // ---- sample: one entry of every thread (hist is cleared, a barrier passed)
+  float width;
+  {
+    const int slabs = (chunks + NW - 1) / NW;
+    const int us = (int)((((uint32_t)tid * 2654435761u >> 16) * (uint32_t)slabs) >> 16);
+    uint32_t bits = 0;          // (a chain of selects would become an indexed load, and the entries scratch memory)
+    bool valid = false;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u) {
+      bits |= us == u ? __float_as_uint(ev[u]) : 0u;
+      valid |= us == u && ei[u] >= 0;
+    }
+    const float smp = __uint_as_float(bits);
+    if (!(fabsf(tau) < 1e30f) || !(fabsf(top) < 1e30f)) {   // (the list is the whole row: the sample's own range)
+      const bool finite = valid && fabsf(smp) < 1e30f;
+      const float low = -wave_max_f32(finite ? -smp : -INFINITY), high = wave_max_f32(finite ? smp : -INFINITY);
+      if (lane == 0) { L.low[wave] = low; L.high[wave] = high; }
+      __syncthreads();
+      tau = -wave_max_f32(-L.low[lane & (NW - 1)]);
+      top = wave_max_f32(L.high[lane & (NW - 1)]);
+    }
+    width = (top - tau) * (1.f / kBins);
+    const float per = (float)kBins / (top - tau);
+    if (!(width > 0.f) || !(per < 3e38f)) return false;
+    if (valid && smp >= tau) atomicAdd(&hist[bin_of(smp, tau, per)], 1);
+    const int n_valid = __popcll(__builtin_amdgcn_ballot_w64(valid));
+    if (lane == 0) L.valid[wave] = n_valid;
+  }
+  if (tid < 64) {
+    L.few[tid] = make_uint2(0u, 0u);      // (key 0 ranks below every entry)
+    L.few_rank[tid] = 0;
+  }
+  if (tid == 0) { L.few_len = 0; L.at_lo[2] = 0; L.at_hi[2] = 0; L.unlike = 0; }
+  __syncthreads();
+  int m;
+  waves_before(L.valid, NW, &m);
+  const float part = (float)k / (float)c, kf = part * (float)m, margin = 5.f * sqrtf(kf * (1.f - part)) + 8.f;
+  const int r_lo = min((int)ceilf(kf + margin), m), r_hi = (int)floorf(kf - margin);
+  find_threshold_bin_n<NT>(hist, r_lo, scan_scratch, L.at_lo, max(r_hi, 1), L.at_hi);
+  if (L.at_lo[2] == 0) return false;
+  // the bracket's ends, rounded outwards: of the bins 2048 x 2^-22 of one, and what the values have lost by their size
+  const float slack = 0.001f * width + 2.5e-7f * fmaxf(fabsf(tau), fabsf(top));
+  const float from = kf + margin > (float)m ? tau : tau + (float)L.at_lo[0] * width - slack;   // (no lower end in the sample: all)
+  const float edge = tau + (float)(L.at_hi[0] + 1) * width + slack;
+  const float upto = r_hi >= 1 && L.at_hi[0] < kBins - 1 ? edge : INFINITY;
+  const float fine = fminf((float)kBins / (edge - from), 3e38f);
+
+  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+
+  // ---- walk
+  int sure = 0, fill = 0;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const bool live = ei[u] >= 0;
+    const unsigned long long above = __builtin_amdgcn_ballot_w64(live && ev[u] >= upto);
+    const unsigned long long in = __builtin_amdgcn_ballot_w64(live && ev[u] >= from) & ~above;
+    if (lane == 0) L.word[u * NW + wave] = make_uint2((uint32_t)above, (uint32_t)(above >> 32));
+    sure += __popcll(above);
+    const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(in >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)in, 0));
+    if (__builtin_amdgcn_inverse_ballot_w64(in)) list[min(fill, kRowSeg) + at] = make_uint2(__float_as_uint(ev[u]), (uint32_t)(u * NT + tid));
+    fill += __popcll(in);
+  }
+  __syncthreads();     // (the histogram is clear)
+  for (int j = lane; j < min(fill, kRowSeg); j += 64) atomicAdd(&hist[bin_of(__uint_as_float(list[j].x), from, fine)], 1);
+  if (lane == 0) { L.sure[wave] = sure; L.listed[wave] = fill; }
+  __syncthreads();
+  int all_sure, all_listed;
+  waves_before(L.sure, NW, &all_sure);
+  waves_before(L.listed, NW, &all_listed);
+  const bool over = lane < NW && L.listed[lane & (NW - 1)] > kRowSeg;
+  int need = k - all_sure;
+  if (__builtin_amdgcn_ballot_w64(over) != 0 || need < 0 || all_listed < need) return false;
+  auto mark = [&](uint32_t e) {
+    atomicOr(reinterpret_cast<uint32_t*>(&L.word[e >> 6]) + ((e >> 5) & 1), 1u << (e & 31));   // (entry u NT + 64 wave + lane)
+  };
+  if (need > 0) {
+    find_threshold_bin_n<NT>(hist, need, scan_scratch, L.at_lo);
+    const int b = L.at_lo[0];
+    int few = L.at_lo[2], b2 = -1;
+    need = L.at_lo[1];
+    const float from2 = from + (float)b / fine, fine2 = fminf(fine * (float)kBins, 3e38f);
+    if (few > 64) {             // a crowded bin (scores that pile up: a query whose gates are all negative) is cut once more
+      for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+      __syncthreads();
+      for (int j = lane; j < fill; j += 64) {
+        const float v = __uint_as_float(list[j].x);
+        if (bin_of(v, from, fine) == b) atomicAdd(&hist[bin_of(v, from2, fine2)], 1);
+      }
+      __syncthreads();
+      find_threshold_bin_n<NT>(hist, need, scan_scratch, L.at_lo);
+      b2 = L.at_lo[0];
+      few = L.at_lo[2];
+      need = L.at_lo[1];
+    }
+    for (int j = lane; j < fill; j += 64) {
+      const uint2 e = list[j];
+      int d = bin_of(__uint_as_float(e.x), from, fine) - b;
+      if (d == 0 && b2 >= 0) d = bin_of(__uint_as_float(e.x), from2, fine2) - b2;
+      if (d > 0) mark(e.y);
+      if (d == 0) {
+        if (few <= 64) L.few[atomicAdd(&L.few_len, 1)] = make_uint2(order_key(__uint_as_float(e.x)), e.y);
+        else L.same = e.x;
+      }
+    }
+    __syncthreads();
+    if (few > 64) {
+      // as a rule equal scores (the zeros of keys that no active head likes): the first of them
+      const float same = __uint_as_float(L.same);
+      bool unlike = false;
+      for (int j = lane; j < fill; j += 64) {
+        const float v = __uint_as_float(list[j].x);
+        unlike |= bin_of(v, from, fine) == b && bin_of(v, from2, fine2) == b2 && v != same;
+      }
+      if (unlike) L.unlike = 1;
+      uint2* const eq = reinterpret_cast<uint2*>(hist);      // (searched before the last barrier)
+#pragma unroll
+      for (int u = 0; u < EPT; ++u) {
+        const unsigned long long m_eq = __builtin_amdgcn_ballot_w64(ei[u] >= 0 && ev[u] == same);
+        if (lane == 0) eq[u * NW + wave] = make_uint2((uint32_t)m_eq, (uint32_t)(m_eq >> 32));
+      }
+      __syncthreads();
+      if (L.unlike) return false;
+      const uint2 w = tid < EPT * NW ? eq[tid] : make_uint2(0u, 0u);
+      const int n_w = __popc(w.x) + __popc(w.y);
+      int total;
+      int left = need - block_exclusive_scan(n_w, scan_scratch, &total);
+      if (tid < EPT * NW && left > 0) {
+        unsigned long long bits = (unsigned long long)w.y << 32 | w.x, kept = bits;
+        if (left < n_w) {
+          kept = 0;
+          for (; left > 0; --left) {
+            kept |= bits & (0ull - bits);
+            bits &= bits - 1;
+          }
+        }
+        L.word[tid].x |= (uint32_t)kept;
+        L.word[tid].y |= (uint32_t)(kept >> 32);
+      }
+      __syncthreads();
+    } else {
+    {
+      // ranked by score, then index: all pairs, a wavefront comparing each entry with its share of the others
+      constexpr int JP = 64 / NW;
+      const uint2 own = L.few[lane];
+      int rank = 0;
+#pragma unroll
+      for (int j = 0; j < JP; ++j) {
+        const uint2 o = L.few[wave * JP + j];
+        rank += (o.x > own.x || (o.x == own.x && o.y < own.y)) ? 1 : 0;
+      }
+      if (rank) atomicAdd(&L.few_rank[lane], rank);
+    }
+    __syncthreads();
+    if (tid < few && L.few_rank[tid] < need) mark(L.few[tid].y);
+    __syncthreads();
+    }
+  }
+
+  // ---- output in entry order, which is index order
+  {
+    const uint2 w = tid < EPT * NW ? L.word[tid] : make_uint2(0u, 0u);
+    int total;
+    const int before = block_exclusive_scan(__popc(w.x) + __popc(w.y), scan_scratch, &total);
+    if (tid < EPT * NW) L.before[tid] = before;
+  }
+  __syncthreads();
+  const uint2 word = lane < EPT ? L.word[lane * NW + wave] : make_uint2(0u, 0u);
+  const int before = lane < EPT ? L.before[lane * NW + wave] : 0;
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
+    const uint32_t m_lo = __builtin_amdgcn_readlane(word.x, u), m_hi = __builtin_amdgcn_readlane(word.y, u);
+    const int pos = __builtin_amdgcn_mbcnt_hi(m_hi, __builtin_amdgcn_mbcnt_lo(m_lo, (uint32_t)__builtin_amdgcn_readlane(before, u)));
+    if (__builtin_amdgcn_inverse_ballot_w64((unsigned long long)m_hi << 32 | m_lo) && pos < k) {   // pos < k: always true when the selection is consistent
+      out_idx[pos] = ei[u];
+      if (out_val) out_val[pos] = ev[u];
+    }
+  }
+  return true;
+}
+
 // One workgroup of NT threads per row: exact top-k of the row's candidate list.
-// Thread t owns list entries t, t + NT, ... (at most EPT of them) and keeps them in
-// registers for all passes, so LDS only holds the histogram and the row bitmaps and
-// several rows share a compute unit.  The chain of barriers of one row is the bound, so the second row
-// on a CU counts: index and score of 13 entries, without their keys, leave 46 registers (2048 rows of
-// about 10500 entries: 95 us; 127 us with the keys kept, 83 registers and one workgroup of 1024 per CU).
+// A thread keeps its (at most EPT) list entries in registers for all passes; index and score without their keys fit 64
+// registers, so that two workgroups of 1024 threads share a CU.  Bound by the chain of barriers and loads of a row, which
+// all workgroups go through in step, then by reading the lists (2048 rows of about 10500 entries: 95 us with the place of
+// every entry searched by its thread and all of them counted, 82 now, 48 at the rate of a large copy; chunks found by
+// ballots of every wavefront: 92).
 template <int NT, int EPT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void select_rows_kernel(
     Prob p, const int2* __restrict__ cand, const int* __restrict__ seg, const int* __restrict__ seg_count,
     int ranges, const float* __restrict__ tau, const uint32_t* __restrict__ upper, int cap, int k, int qwg,
     int q_tiles, int* __restrict__ idx, float* __restrict__ val, int* __restrict__ row_flag,
     int* __restrict__ tile_flag) {
-  extern __shared__ uint32_t dyn[];  // selection bitmap, then the prefix count of every bitmap word
+  extern __shared__ __align__(16) uint32_t dyn[];  // the sampled selection's lists; or the selection bitmap, then the prefix count of every bitmap word
   __shared__ int hist[kBins];
   __shared__ int scan_scratch[32];
   __shared__ int thr[3];
@@ -221,9 +434,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   __shared__ int bidx[64];
   __shared__ int b_len;
   __shared__ int brank[64];       // entries of the boundary list that rank before an entry
-  __shared__ int seg_first[65];   // offset of a range's segment in the row's list
-  __shared__ int seg_pre[65];     // entries of the ranges before it (compact numbering of the row's entries)
-  __shared__ int seg_bad;
+  constexpr int NW = NT / 64;
   const int t = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x;
   const size_t row = (size_t)seq * p.n_q + t;
   const int n = visible(p, seq, t);
@@ -235,24 +446,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     if (out_val) out_val[i] = -INFINITY;
   }
   if (k_eff == 0) return;
-  // the row's entries: range r holds seg_count[r] of them from seg[r] on; a count above the
-  // segment's length means that hits were dropped
-  if (tid < 64) {
-    int cnt = 0, len = 0, first = 0;
-    if (tid < ranges) {
-      first = seg[row * (ranges + 1) + tid];
-      len = seg[row * (ranges + 1) + tid + 1] - first;
-      cnt = seg_count[row * ranges + tid];
-    }
-    const unsigned long long bad = __ballot(cnt > len);
-    const int end = wave_inclusive_scan(cnt);
-    seg_first[tid] = first;
-    seg_pre[tid] = end - cnt;
-    if (tid == 63) { seg_pre[64] = end; seg_bad = bad != 0; }
+  // The row's entries: range r holds seg_count[r] of them from seg[r] on; a count above the segment's length means that
+  // hits were dropped.  They are taken in chunks of 64 of one range, chunk u NW + wave of the row by this wavefront; lane r
+  // of every wavefront looks after range r, and the wavefronts together write down where the chunks are.
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int cnt = 0, len = 0, first_entry = 0;
+  if (lane < ranges) {
+    first_entry = seg[row * (ranges + 1) + lane];
+    len = seg[row * (ranges + 1) + lane + 1] - first_entry;
+    cnt = seg_count[row * ranges + lane];
   }
-  __syncthreads();
-  const int c = seg_pre[64];
-  if (seg_bad || c > NT * EPT || c < k_eff) {  // a segment overflowed, more entries than this kernel holds, or threshold too high: leave the row to the repair pass
+  const bool dropped = __builtin_amdgcn_ballot_w64(cnt > len) != 0;
+  const int chunk_end = wave_inclusive_scan((cnt + 63) >> 6), chunks = __builtin_amdgcn_readlane(chunk_end, 63);
+  const int entry_end = wave_inclusive_scan(cnt), c = __builtin_amdgcn_readlane(entry_end, 63);
+  if (dropped || chunks > NW * EPT || c < k_eff) {  // a segment overflowed, more entries than this kernel holds, or threshold too high: leave the row to the repair pass
     if (tid == 0) {
       row_flag[row] = 1;
       tile_flag[seq * q_tiles + t / qwg] = 1;
@@ -267,27 +474,42 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   int ei[EPT];
   float ev[EPT];
   const int2* src = cand + row * (size_t)cap;
-  int rg = 0, rg_begin = 0, rg_end = seg_pre[1];   // the range whose entries [rg_begin, rg_end) hold entry i
+  __shared__ int4 s_chunk[NW * EPT];      // place in the row's list, entries, number in the row of a chunk's first entry
+  {
+    const int mine = (cnt + 63) >> 6;
+    for (int q = wave; __builtin_amdgcn_ballot_w64(q < mine) != 0; q += NW)
+      if (q < mine) s_chunk[chunk_end - mine + q] = make_int4(first_entry + 64 * q, min(cnt - 64 * q, 64), entry_end - cnt + 64 * q, 0);
+    for (int j = chunks + tid; j < NW * EPT; j += NT) s_chunk[j] = make_int4(0, 0, 0, 0);
+  }
+  for (int i = tid; i < kBins; i += NT) hist[i] = 0;
+  __syncthreads();
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int i = tid + u * NT;                    // (increasing with u: the range only moves forward)
-    int2 e = make_int2(-1, 0);
-    if (i < c) {
-      while (rg_end <= i) {                        // ends at the latest at range 63: seg_pre[64] = c > i
-        ++rg;
-        rg_begin = rg_end;
-        rg_end = seg_pre[rg + 1];
-      }
-      e = src[seg_first[rg] + (i - rg_begin)];
-    }
-    ei[u] = e.x;
+    const int2 chunk = *reinterpret_cast<const int2*>(&s_chunk[u * NW + wave]);
+    const bool live = lane < chunk.y;
+    const int2 e = src[live ? chunk.x + lane : 0];
+    ei[u] = live ? e.x : -1;
     ev[u] = __int_as_float(e.y);
   }
+  if (c == k_eff) {       // every entry, in index order
+#pragma unroll
+    for (int u = 0; u < EPT; ++u)
+      if (ei[u] >= 0) {
+        const int at = s_chunk[u * NW + wave].z + lane;
+        out_idx[at] = ei[u];
+        if (out_val) out_val[at] = ev[u];
+      }
+    return;
+  }
+  __shared__ EntryLds<NT, EPT> entry_lds;
+  if (select_sampled<NT, EPT>(ei, ev, c, chunks, k_eff, tau[row], key_to_float(upper[row]), hist, scan_scratch, dyn, entry_lds, out_idx, out_val)) return;
+  // the digits of the keys instead
+  __syncthreads();
   auto key_of = [&](int u) { return order_key(ev[u]); };
   for (int i = tid; i < nwords; i += NT) sel[i] = 0;
   if (tid == 0) b_len = 0;
   if (tid < 64) brank[tid] = 0;
-  zero_hist_n<NT>(hist);  // ends with a barrier
+  zero_hist_n<NT>(hist);
   auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
 
   // Short way: one digit of key - key(tau), scaled so that [tau, upper] fills the 2047 lower
@@ -297,7 +519,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   // (score descending, index ascending).  More than 64 entries in that digit, or the catch-all
   // digit: the three raw key digits below decide instead.
   bool done = false;
-  if (c != k_eff) {
+  {
     const uint32_t klo = order_key(tau[row]);
     const uint32_t up = upper[row];
     const uint32_t span = up > klo ? up - klo : 1u;
@@ -352,11 +574,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     }
   }
 
-  if (c == k_eff) {
-#pragma unroll
-    for (int u = 0; u < EPT; ++u)
-      if (ei[u] >= 0) mark(ei[u]);
-  } else if (!done) {
+  if (!done) {
     // most significant digit first: 11 + 11 + 10 bits of the key
 #pragma unroll
     for (int u = 0; u < EPT; ++u)
@@ -434,10 +652,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   // Output slot of a selected index = number of selected indices below it.
   const int wpt = (nwords + NT - 1) / NT;
   const int w_lo = min(tid * wpt, nwords), w_hi = min(w_lo + wpt, nwords);
-  int cnt = 0;
-  for (int w = w_lo; w < w_hi; ++w) cnt += __popc(sel[w]);
+  int selected = 0;
+  for (int w = w_lo; w < w_hi; ++w) selected += __popc(sel[w]);
   int total;
-  int pos = block_exclusive_scan(cnt, scan_scratch, &total);
+  int pos = block_exclusive_scan(selected, scan_scratch, &total);
   for (int w = w_lo; w < w_hi; ++w) {
     wpre[w] = pos;
     pos += __popc(sel[w]);
@@ -556,13 +774,14 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
 #define GO(NT, EPT)                                                                                 \
   do {                                                                                              \
     static LdsSeen seen;                                                                            \
-    e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_rows_kernel<NT, EPT>), lds, seen);  \
+    const size_t dyn = std::max(lds, row_list_bytes<NT>());                                         \
+    e = ensure_dynamic_lds(reinterpret_cast<const void*>(select_rows_kernel<NT, EPT>), dyn, seen);  \
     if (e != hipSuccess) return e;                                                                  \
-    select_rows_kernel<NT, EPT><<<rows, NT, lds, st>>>(p, cand, seg, seg_count, l.ranges, tau, upper, l.cap, k, \
+    select_rows_kernel<NT, EPT><<<rows, NT, dyn, st>>>(p, cand, seg, seg_count, l.ranges, tau, upper, l.cap, k, \
                                                        l.qwg, l.q_tiles, idx, val, row_flag, tile_flag); \
   } while (0)
-  if (small_rows) GO(512, 10);
-  else GO(1024, 13);
+  if (small_rows) GO(512, 14);
+  else GO(1024, 14);
 #undef GO
   if ((e = hipGetLastError()) != hipSuccess) return e;
 

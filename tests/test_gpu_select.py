@@ -283,3 +283,25 @@ def test_select_workspace_is_checked(misa):
     small_ws = torch.empty(1024, dtype=torch.uint8, device="cuda")
     with pytest.raises(misa.MisaError):
         misa.select_tokens(p, dv["Q"], dv["W"], None, dv["K"], dv["kscale"], 100, idx, None, small_ws)
+
+
+@pytest.mark.parametrize("L,k,n_q,h", [
+    (9000, 700, 24, 3),        # negative gates: the k-th largest score is one of the zeros
+    (70000, 8192, 12, 3),      # the same with the longest lists
+    (20000, 2048, 40, 8),      # negative gates, the k-th largest below the zeros
+    (4500, 4000, 24, 8),       # every visible key is listed, most are taken
+    (5120, 5119, 9, 8),        # all but one of the last row, all of the others
+    (13312, 8000, 9, 8),       # the most keys that are all listed
+])
+def test_select_plateaus_and_whole_rows(misa, L, k, n_q, h):
+    wl = small("c2", L=L, n_q=n_q, h=h, k=k)
+    inp = WL.make_inputs(wl, seed=L % 1000)
+    inp["W"][:, ::2] = -np.abs(inp["W"][:, ::2])
+    inp["W"][:, 1] = 0.0                                   # every score equal
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    heads = random_heads(wl)
+    idx, val = one_call(misa, p, dv, heads, k)
+    ref_idx, ref_val = two_call(misa, p, dv, heads, k)
+    assert torch.equal(idx, ref_idx)
+    assert torch.equal(val, ref_val)
