@@ -34,7 +34,9 @@ hipError_t launch_score(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
 // top-k, Eq. misa_final_topk) in one workgroup, no score matrix: taken when rerank_fused_path says
 // so (at least kRerankFusedMinRows queries, k_cand <= 8192, matrix-core types); the results equal
 // launch_score + launch_topk(map = cand) bit for bit.
-constexpr int kRerankFusedMinRows = 1024;
+// (512 rows run at once, two per CU; us, two kernels / one, 64 heads, 8192 candidates, widened fp8 keys: 1023 rows 167 / 162,
+// 768 rows 142 / 135, 600 rows 110 / 119.)
+constexpr int kRerankFusedMinRows = 704;
 bool rerank_fused_path(const Prob& p, int k_dtype, int q_dtype, int k_cand);
 hipError_t launch_rerank_fused(const Prob& p, int k_dtype, int q_dtype, const void* Q, const float* W,
                                const void* K, const float* kscale, const int* cand, int k_cand, int k,

@@ -967,11 +967,13 @@ __global__ __launch_bounds__(256) void score_tile_repair_kernel(
 // wavefront feeds both pipes, and the rows of two steps are in flight in registers.
 // Bound by matrix and vector instructions at the clock that the chip holds; 2048 queries x 8192 candidates with
 // their top-k: widened fp8 keys 388 -> 343 us, bf16 keys 495 -> 361 us, fp8 on both sides 313 -> 240 us (rows of one step
-// in flight 342, 362, 250 us; row tiles with two sets of accumulators: spills for bf16 keys).
+// in flight 342, 362, 250 us; row tiles with two sets of accumulators: spills for bf16 keys); with the query rows read
+// whole as well 337, 353, 236 us, and 1023 rows of 2048 candidates 66 -> 59, 79 -> 75, 55 -> 49 us.  Two wavefronts per
+// SIMD; three with one row tile of fp8 queries (1100 x 8192: 128 -> 108 us), where the others would spill.
 constexpr int kGatherChunk = 4096;
 
 template <int KDT, int RT, bool Q8, bool PAGED, bool FUSED>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void score_gather_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT == 1 && Q8 ? 3 : 2, RT == 1 && Q8 ? 3 : 2))) void score_gather_kernel(
     Prob p, const uint16_t* __restrict__ Q, const float* __restrict__ W,
     const void* __restrict__ K, const float* __restrict__ kscale, const int* __restrict__ cand,
     int k_cand, int chunk, float* __restrict__ out, int k, int* __restrict__ idx,
@@ -998,53 +1000,44 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // in the loop does not wait on the key loads in flight.
   __shared__ __align__(16) int s_cand[FUSED ? kSmallTopkMax : kGatherChunk];
   __shared__ u32x4 s_rows[4][32 * PITCH];            // (later the scratch of the top-k)
-  for (int i0 = threadIdx.x; i0 < chunk; i0 += 4096) {   // (16 loads in flight)
-    int v[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) v[u] = crow[min(c_begin + i0 + 256 * u, k_cand - 1)];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int i = i0 + 256 * u;
-      if (i < chunk) s_cand[i] = c_begin + i < c_end ? v[u] : -1;
-    }
-  }
-
+  __shared__ __align__(16) float s_gate[RT * 32];
   // Row m of tile rt is head rt*32 + m; half-wave hf holds components 64 hf .. 64 hf + 63,
   // k-step ks the eight from 64 hf + 8 ks (the key fragments use the same mapping).
   // Q8 (fp8 query codes and fp8 keys, fp8 matrix instruction): k-step ks of 64 components,
   // half-wave hf the 32 from 64 ks + 32 hf.
+  // The rows are read whole and go through LDS, like the keys' (each wavefront by itself, fragment by fragment: 4096 clocks
+  // of the texture addresser per workgroup, as much as 512 candidates take).
   static_assert(!Q8 || KDT == MISA_FP8_E4M3, "fp8 queries contract with fp8 keys only");
   constexpr int KS = Q8 ? 2 : 8;
-  Frag a[RT][Q8 ? 1 : 8];
-  Frag8 a8[RT][Q8 ? 2 : 1];
-  float gate[RT * 16];                               // of the rows this lane holds
+  constexpr int QPR = Q8 ? 8 : 16, QPITCH = QPR + 1, QLD = RT * 32 * QPR / 256;   // 16-byte pieces per head row, per thread
+  static_assert(RT * 32 * QPITCH * 16 <= (int)sizeof(s_rows), "the query rows pass through the keys' LDS");
+  u32x4* const s_q = &s_rows[0][0];
+  {
+    const u32x4* src = reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(Q) + qrow * p.H * (QPR * 16));
+    u32x4 q[QLD];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    const int head = rt * 32 + col;
-    if (Q8) {
-      const uint8_t* src = reinterpret_cast<const uint8_t*>(Q) + (qrow * p.H + min(head, p.H - 1)) * kD + 32 * hf;
+    for (int i = 0; i < QLD; ++i) q[i] = src[min((int)threadIdx.x + 256 * i, p.H * QPR - 1)];
+    const float w = threadIdx.x < RT * 32 ? W[qrow * p.H + min((int)threadIdx.x, p.H - 1)] : 0.f;
+    for (int i0 = threadIdx.x; i0 < chunk; i0 += 4096) {   // (16 loads in flight)
+      int v[16];
 #pragma unroll
-      for (int ks = 0; ks < (Q8 ? 2 : 0); ++ks)
+      for (int u = 0; u < 16; ++u) v[u] = crow[min(c_begin + i0 + 256 * u, k_cand - 1)];
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const uint4 v = *reinterpret_cast<const uint4*>(src + 64 * ks + 16 * u);
-          a8[rt][ks].u[u] = head < p.H ? v : make_uint4(0, 0, 0, 0);
-        }
-    } else {
-      const uint16_t* src = Q + (qrow * p.H + min(head, p.H - 1)) * kD + 64 * hf;
-#pragma unroll
-      for (int ks = 0; ks < (Q8 ? 0 : 8); ++ks) {
-        const uint4 v = *reinterpret_cast<const uint4*>(src + 8 * ks);
-        a[rt][ks].u = head < p.H ? v : make_uint4(0, 0, 0, 0);
+      for (int u = 0; u < 16; ++u) {
+        const int i = i0 + 256 * u;
+        if (i < chunk) s_cand[i] = c_begin + i < c_end ? v[u] : -1;
       }
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int hd = rt * 32 + 8 * (r >> 2) + 4 * hf + (r & 3);
-      const float w = W[qrow * p.H + min(hd, p.H - 1)];
-      gate[rt * 16 + r] = hd < p.H ? w : 0.f;
+    for (int i = 0; i < QLD; ++i) {
+      const int e = threadIdx.x + 256 * i, head = e / QPR;
+      s_q[head * QPITCH + e % QPR] = head < p.H ? q[i] : u32x4{0, 0, 0, 0};
     }
+    if (threadIdx.x < RT * 32) s_gate[threadIdx.x] = threadIdx.x < p.H ? w : 0.f;
   }
+  Frag a[RT][Q8 ? 1 : 8];
+  Frag8 a8[RT][Q8 ? 2 : 1];
+  float gate[RT * 16];                               // of the rows this lane holds
 
   const char* kseq = static_cast<const char*>(K) + (PAGED ? 0 : (size_t)seq * p.L * ROW_BYTES);
   const float* sseq = kscale + (PAGED ? 0 : (size_t)seq * p.L);
@@ -1189,7 +1182,27 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
   const int c_first = c_begin + wave * 32;
   const int steps = (c_end - c_first + 127) / 128;   // of this wavefront (none: <= 0)
-  __syncthreads();                                   // candidate indices are in LDS
+  __syncthreads();                                   // candidate indices, query rows and gates are in LDS
+#pragma unroll
+  for (int rt = 0; rt < RT; ++rt) {
+    const u32x4* row = s_q + (rt * 32 + col) * QPITCH;
+    if (Q8) {
+#pragma unroll
+      for (int i = 0; i < (Q8 ? 4 : 0); ++i) a8[rt][i >> 1].x[i & 1] = row[4 * (i >> 1) + 2 * hf + (i & 1)];
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < (Q8 ? 0 : 8); ++ks) a[rt][ks].x = row[8 * hf + ks];
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const float4 w = *reinterpret_cast<const float4*>(&s_gate[rt * 32 + 8 * g + 4 * hf]);
+      gate[rt * 16 + 4 * g] = w.x;
+      gate[rt * 16 + 4 * g + 1] = w.y;
+      gate[rt * 16 + 4 * g + 2] = w.z;
+      gate[rt * 16 + 4 * g + 3] = w.w;
+    }
+  }
+  __syncthreads();                                   // the rows' LDS is free for the keys
   if (steps > 0) {
     f32x16 acc0, acc1;
     {

@@ -281,3 +281,21 @@ def test_many_query_rerank_sampled_selection(misa, kc, k, H, k_dtype):
     idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k)
     assert torch.equal(idx, idx2)
     assert torch.equal(val.view(torch.int32), val2.view(torch.int32))
+
+
+@pytest.mark.parametrize("rows", [703, 704, 1023])
+@pytest.mark.parametrize("k_dtype,q_dtype,H,kc,k", [("bf16", "bf16", 64, 2048, 512), ("e4m3", "e4m3", 32, 2100, 700), ("e4m3", "bf16", 20, 600, 64)])
+def test_rerank_around_the_one_kernel_threshold(misa, rows, k_dtype, q_dtype, H, kc, k):
+    seed, L = 9700 + rows + kc, 4000
+    rng = np.random.default_rng(seed)
+    wl = WL.scaled(WL.WORKLOADS["c2"], n_seq=1, L=L, n_q=rows, H=H, h=1, B=64, k=1, k_cand=0, k_dtype=k_dtype, q_dtype=q_dtype,
+                   needles=6, name=f"rrt{seed}")
+    dv = misa.to_device(WL.make_inputs(wl, seed=seed))
+    p = dv["problem"]
+    if q_dtype == "e4m3":
+        p = replace(p, q_dtype=misa.FP8_E4M3_MATRIX)
+    dcand = torch.from_numpy(_candidates(rng, rows, L, kc)).cuda()
+    idx, val = _rerank(misa, p, dv, dcand, kc, k)
+    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=300)
+    assert torch.equal(idx, idx2)
+    assert torch.equal(val, val2)
