@@ -351,19 +351,20 @@ __device__ __forceinline__ bool pick_row(int* sc, int n, int k, const int* __res
   const int most = max(max(L.listed[0], L.listed[1]), max(L.listed[2], L.listed[3]));
   if (sure > k || sure + listed < k || most > kPickSeg) return false;
 
-  // ---- the listed ones: a wavefront looks at those that it has listed
+  // ---- the listed ones: a wavefront looks at those that it has listed (also where none of them is wanted: a NaN ranks by its
+  // sign, above or below all others)
   int need = k - sure;
+  const float fine = fminf(fmaxf((float)kPickBins / (edge - b_lo), 1e-35f), 3e38f);
+  bool nan = false;
+  for (int j = lane; j < fill; j += 64) {
+    const float x = scf[L.list[wave][j]];
+    nan |= x != x;
+    atomicAdd(&L.hist[bin_of(x, b_lo, fine)], 1);
+  }
+  if (nan) L.nan_seen = 1;
+  __syncthreads();
+  if (L.nan_seen) return false;
   if (need > 0) {
-    const float fine = fminf(fmaxf((float)kPickBins / (edge - b_lo), 1e-35f), 3e38f);
-    bool nan = false;
-    for (int j = lane; j < fill; j += 64) {
-      const float x = scf[L.list[wave][j]];
-      nan |= x != x;
-      atomicAdd(&L.hist[bin_of(x, b_lo, fine)], 1);
-    }
-    if (nan) L.nan_seen = 1;
-    __syncthreads();
-    if (L.nan_seen) return false;
     pick_bin(L.hist, L.scan, need, L.at_lo, need, L.at_hi);
     const int b = L.at_lo[0], few = L.at_lo[2];
     need = L.at_lo[1];

@@ -283,6 +283,30 @@ def test_many_query_rerank_sampled_selection(misa, kc, k, H, k_dtype):
     assert torch.equal(val.view(torch.int32), val2.view(torch.int32))
 
 
+def test_many_query_rerank_nan_beside_exactly_k_infinite_scores(misa):
+    """k scores of +inf fill the answer of the sampled selection without a look at what it has listed below them; a NaN
+    ranks above them all the same, as in the two-kernel path."""
+    kc, L, H = 2048, 9000, 64
+    wl, inp = _problem(9977, "e4m3", "bf16", H, L)
+    inp["W"][:] = np.abs(inp["W"]) + 0.1                   # (every score is positive)
+    inp["kscale"][0, 7000] = np.inf                        # +inf
+    inp["kscale"][0, 7500] = np.nan
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    rng = np.random.default_rng(9977)
+    cand = np.stack([np.sort(rng.choice(6900, size=kc, replace=False)) for _ in range(ROWS)])[None].astype(np.int32)
+    cand[0, :, -2] = 7000
+    cand[0, ::2, -1] = 7500                                # (every other row has no NaN)
+    dcand = torch.from_numpy(cand).cuda()
+    for k in (1, 2):
+        idx, val = _rerank(misa, p, dv, dcand, kc, k)
+        idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k)
+        assert torch.equal(idx, idx2)
+        assert torch.equal(val.view(torch.int32), val2.view(torch.int32))
+        if k == 1:
+            assert torch.all(idx[0, ::2] == 7500) and torch.all(idx[0, 1::2] == 7000)
+
+
 @pytest.mark.parametrize("rows", [703, 704, 1023])
 @pytest.mark.parametrize("k_dtype,q_dtype,H,kc,k", [("bf16", "bf16", 64, 2048, 512), ("e4m3", "e4m3", 32, 2100, 700), ("e4m3", "bf16", 20, 600, 64)])
 def test_rerank_around_the_one_kernel_threshold(misa, rows, k_dtype, q_dtype, H, kc, k):
