@@ -32,11 +32,14 @@ hipError_t launch_score(const Prob& p, int k_dtype, int q_dtype, const void* Q, 
 
 // The whole re-rank of a query (dense scores of its k_cand candidates, Eq. dsa_score, and their
 // top-k, Eq. misa_final_topk) in one workgroup, no score matrix: taken when rerank_fused_path says
-// so (at least kRerankFusedMinRows queries, k_cand <= 8192, matrix-core types); the results equal
+// so (kRerankFusedMinRows queries or more, kRerankFusedMinList .. 8192 candidates, matrix-core types); the results equal
 // launch_score + launch_topk(map = cand) bit for bit.
-// (512 rows run at once, two per CU; us, two kernels / one, 64 heads, 8192 candidates, widened fp8 keys: 1023 rows 167 / 162,
-// 768 rows 142 / 135, 600 rows 110 / 119.)
+// Rows: one kernel over two, two head counts, lists of 2048 to 8192: 704 rows bf16 0.92 - 0.96, widened fp8 0.95 - 1.00, fp8
+// on both sides 0.85 - 1.01; 800 rows 0.98 - 1.04; 1023 rows 0.91 - 0.98 (below, 512 rows run at once: 600 rows 1.08).
+// Lists: shorter ones have no sampled selection (small_topk.h) and share a CU with one other row only; us, two kernels /
+// one: 730 rows of 1024 candidates 33 / 53, 1024 of 256 25 / 49, 1536 of 1500 80 / 108, 8192 of 2047 and less 0.4 - 0.9.
 constexpr int kRerankFusedMinRows = 704;
+constexpr int kRerankFusedMinList = 2048;
 bool rerank_fused_path(const Prob& p, int k_dtype, int q_dtype, int k_cand);
 hipError_t launch_rerank_fused(const Prob& p, int k_dtype, int q_dtype, const void* Q, const float* W,
                                const void* K, const float* kscale, const int* cand, int k_cand, int k,

@@ -1421,13 +1421,14 @@ static hipError_t launch_gather(const Prob& p, const void* Q, const float* W, co
   return hipGetLastError();
 }
 
-// Re-rank with the top-k inside the gather kernel: for many queries with short candidate lists
-// (one workgroup per query fills the chip, the list fits LDS) and the types the gather kernel
-// takes.
+// Re-rank with the top-k inside the gather kernel: for many queries with candidate lists from which
+// the top-k is sampled (one workgroup per query fills the chip, the list fits LDS) and the types the
+// gather kernel takes.
 bool rerank_fused_path(const Prob& p, int k_dtype, int q_dtype, int k_cand) {
   const bool types = (q_dtype == MISA_BF16 && k_dtype != MISA_F32) ||
                      (q_dtype == MISA_FP8_E4M3 && k_dtype == MISA_FP8_E4M3);
-  return types && k_cand <= kSmallTopkMax && (long long)p.n_q * p.n_seq >= kRerankFusedMinRows;
+  return types && k_cand >= kRerankFusedMinList && k_cand <= kSmallTopkMax &&
+         (long long)p.n_q * p.n_seq >= kRerankFusedMinRows;
 }
 
 template <int KDT, bool Q8>

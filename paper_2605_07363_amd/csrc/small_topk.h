@@ -10,6 +10,7 @@
 // for rows that the bracket does not fit.
 #pragma once
 
+#include "kernels.h"
 #include "radix.h"
 
 namespace misa {
@@ -238,6 +239,7 @@ __device__ __forceinline__ void small_row_by_digits(const int* sc, int n, int k,
 constexpr int kPickBins = 1024;
 constexpr int kPickSamples = 1024;
 constexpr int kPickSeg = 640;        // list entries of a wavefront, behind them 64 of slack
+static_assert(kRerankFusedMinList >= 2 * kPickSamples, "shorter lists are left to the two kernels");
 
 struct PickLds {
   int hist[kPickBins];

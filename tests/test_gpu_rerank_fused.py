@@ -323,3 +323,29 @@ def test_rerank_around_the_one_kernel_threshold(misa, rows, k_dtype, q_dtype, H,
     idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=300)
     assert torch.equal(idx, idx2)
     assert torch.equal(val, val2)
+
+
+@pytest.mark.parametrize("rows,kc,one_kernel", [
+    (704, 2048, True), (703, 2048, False), (704, 2047, False), (1023, 256, False), (1100, 1024, False), (2048, 2047, False),
+    (720, 8192, True),
+])
+@pytest.mark.parametrize("k_dtype,q_dtype", [("bf16", "bf16"), ("e4m3", "e4m3_matrix")])
+def test_rerank_short_lists_take_two_kernels(misa, rows, kc, one_kernel, k_dtype, q_dtype):
+    """Only the two-kernel path writes the scores of the candidates to the workspace; the results are the same."""
+    seed, L, k, H = 9500 + rows + kc, 9000, 200, 32
+    matrix = q_dtype == "e4m3_matrix"
+    wl = WL.scaled(WL.WORKLOADS["c2"], n_seq=1, L=L, n_q=rows, H=H, h=1, B=64, k=1, k_cand=0, k_dtype=k_dtype,
+                   q_dtype="e4m3" if matrix else q_dtype, needles=6, name=f"rrl{seed}")
+    dv = misa.to_device(WL.make_inputs(wl, seed=seed))
+    p = replace(dv["problem"], q_dtype=misa.FP8_E4M3_MATRIX) if matrix else dv["problem"]
+    dcand = torch.from_numpy(_candidates(np.random.default_rng(seed), rows, L, kc)).cuda()
+    ws = misa.alloc_workspace(p, misa.OP_RERANK, kc)
+    ws.fill_(0xA5)
+    idx = torch.empty(1, rows, k, dtype=torch.int32, device="cuda")
+    val = torch.empty(1, rows, k, device="cuda")
+    misa.rerank(p, dv["Q"], dv["W"], dv["K"], dv["kscale"], dcand, kc, k, idx, val, ws)
+    torch.cuda.synchronize()
+    assert bool(torch.all(ws == 0xA5)) == one_kernel
+    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=300)
+    assert torch.equal(idx, idx2)
+    assert torch.equal(val, val2)
