@@ -1146,9 +1146,10 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
   // Short rows: as many threads as hold the row; few rows of up to 4096 take 512 threads (7.3 us for one
   // row against 9.3 us with 256).  Long rows: 1024 threads where there is at most one row per CU or the lists are
   // long; more rows with shorter lists take 512, of which a CU holds
-  // three at different phases, so that memory is never idle (4096 x 65536: 212 us against 244 us), and two where there
-  // are less than two rows per CU (333 x 10007: 14.6 us against 17.8, 400 x 20000: 17.1 against 19.2; 200 x 65536: 21.6
-  // against 18.6).
+  // three at different phases, so that memory is never idle (4096 x 65536: 212 us against 244 us).  Less than two rows
+  // per CU: 512 threads, two rows per CU, up to 45056 elements (us, 1024 / 512: 333 x 10007 17.8 / 14.6, 400 x 20000
+  // 19.2 / 17.1, 428 x 42624 24.7 / 23.0, 433 x 43590 23.7 / 23.9); beyond, a row that needs a second look takes too long
+  // (490 x 118413 with scores alike in runs 63 / 74, 263 x 100783 on a plateau 101 / 114, 286 x 115232 Gaussian 40.5 / 41.8).
   constexpr size_t kLdsMost = 156 * 1024;
   const bool is_short = !only && row_len <= 8192;
   const bool split = !map && !all_slots && !only && use_split(p);
@@ -1159,11 +1160,12 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     lds = (size_t)sel_words(row_len) * 4 + (size_t)(cap + 64) * 8 + (size_t)((row_len + 31) / 32) * 2;
     return lds <= most;
   };
-  const bool few_rows = (long long)p.n_q * p.n_seq < 256;
+  const long long rows = (long long)p.n_q * p.n_seq;
+  const bool few_rows = rows < 256, one_set = rows < 512;
   int nt = row_len > 4096 ? kTopkThreads : few_rows ? 512 : 256;
   if (is_short) fits(nt, kLdsMost);
   else if (only) nt = kTopkThreads;
-  else if (split || few_rows || !fits(nt = 512, (long long)p.n_q * p.n_seq < 512 ? 76 * 1024 : 53 * 1024)) {
+  else if (split || few_rows || (one_set && row_len > 45056) || !fits(nt = 512, one_set ? 76 * 1024 : 53 * 1024)) {
     nt = kTopkThreads;
     // the longest rows have room for half the reserve; k well above 8192: the two-pass path
     if (!fits(nt, kLdsMost) && !fits(nt, kLdsMost, 3.0)) cap = 0;
@@ -1191,8 +1193,7 @@ hipError_t launch_topk(const Prob& p, const float* S, int row_len, int k, const 
     static LdsSeen seen;
     e = ensure_dynamic_lds(reinterpret_cast<const void*>(topk_only_kernel), lds, seen);
     if (e != hipSuccess) return e;
-    const int rows = p.n_seq * p.n_q;
-    topk_only_kernel<<<rows < 256 ? rows : 256, kTopkThreads, lds, st>>>(p, S, k, idx, val, list_cap, only);
+    topk_only_kernel<<<(unsigned)std::min<long long>(rows, 256), kTopkThreads, lds, st>>>(p, S, k, idx, val, list_cap, only);
   } else if (is_short && nt == 256) {
     GO(256, kRowShort);
   } else if (is_short && nt == 512) {

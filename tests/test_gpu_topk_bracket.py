@@ -157,3 +157,17 @@ def test_hard_values_match_a_sort(misa, kind, rows, L, k):
         assert np.array_equal(got[t], ref), t
         assert np.array_equal(v[t].view(np.int32), x[t, ref].view(np.int32)), t
         assert np.array_equal(got[t::distinct], np.broadcast_to(got[t], got[t::distinct].shape)), t
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("rows,L,k", [
+    (255, 45056, 4000),      # 1024 threads
+    (256, 8193, 2048),       # 512 threads, two rows per CU: the shortest row,
+    (300, 45056, 4000),      # the longest one with a list beyond 53 KB,
+    (511, 20011, 5000),      # and one between
+    (256, 45057, 4000),      # 1024 threads again
+    (511, 45056, 9000),      # a list that does not fit twice
+    (512, 45056, 4000),      # more rows: lists of up to 53 KB only
+])
+def test_hard_values_of_less_than_two_rows_per_cu(misa, kind, rows, L, k):
+    test_hard_values_match_a_sort(misa, kind, rows, L, k)
