@@ -72,6 +72,15 @@ static int list_capacity(int k, int ranges) {
   return (int)((c + 255) / 256 * 256);
 }
 
+// Chunks of 64 entries of one key range that the row selection has to have room for.  The entries of a row have mean 16 r
+// and variance 240 r (r hits among samples of one key in 16), and a range's last chunk lacks 31.5 entries on average, with
+// variance 341; the room covers 5.5 standard deviations of the sum, as sample_rank does at the other end.  (At the line
+// about 3 rows in 10^7 have more; entries alone would leave k = 2300 in 16 ranges 4.2 deviations, 4 rows in 10^5.)
+static int row_chunks(int k, int ranges) {
+  const double r = sample_rank(k);
+  return (int)std::ceil((kSampleStride * r + 31.5 * ranges + 5.5 * std::sqrt(240.0 * r + 341.0 * ranges)) / 64.0);
+}
+
 static size_t select_lds_bytes(const Prob& p) {
   const size_t nwords = ((size_t)p.L + 31) / 32;
   return nwords * 8;  // selection bitmap and per-word prefix counts
@@ -746,12 +755,12 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
   int2* cand = reinterpret_cast<int2*>(base + l.cand);
   const dim3 rows(p.n_q, p.n_seq);
 
-  // the row selection holds a row's entries in registers: 512 threads x 10 for up to 5120
-  // expected entries (16 r plus six standard deviations), 1024 x 13 above (measured on MI355X);
-  // rows with more entries go to the repair pass
+  // The row selection holds a row's entries in registers, in chunks of 64: 512 threads (8 chunks for every entry of a
+  // thread) for up to 5120 expected entries (16 r and six standard deviations of 16 sqrt(r)), 1024 above.  Rows all of
+  // whose visible keys are listed fill their chunks (a key range is whole tiles of 64 keys).
   const double rr = sample_rank(k);
   const bool small_rows = kSampleStride * rr * (1.0 + 6.0 / std::sqrt(rr)) <= 5120.0;
-  const int entry_limit = small_rows ? 512 * 10 : 1024 * 13;   // k = kFusedMaxK: 13056 expected
+  const int entry_limit = small_rows ? 512 * 10 : 1024 * 13;
 
   hipError_t e = launch_tile_mode(p, k_dtype, q_dtype, kTileSample, TileAux{}, Q, W, heads, K, kscale, Ss, st);
   if (e != hipSuccess) return e;
@@ -780,11 +789,19 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
     select_rows_kernel<NT, EPT><<<rows, NT, dyn, st>>>(p, cand, seg, seg_count, l.ranges, tau, upper, l.cap, k, \
                                                        l.qwg, l.q_tiles, idx, val, row_flag, tile_flag); \
   } while (0)
-  // chunks of 64 entries a thread has room for: the entries expected and half a chunk lost per key range, which many short
-  // ranges need more of (4096 rows of 3300 entries in 16 ranges: 10 chunks 59.4 us, 14 66.7)
-  if (small_rows && l.ranges <= 16) GO(512, 10);
-  else if (small_rows) GO(512, 14);
-  else GO(1024, 14);
+  // The smallest room that row_chunks asks for (us, entries per thread: 4096 rows of k = 2048, 16 ranges: 10 60.0, 11 61.6, 14
+  // 66.8; 1000 of k = 1024, 63 ranges: 10 22.5, 14 24.8; 2048 of k = 8192, 32 ranges, 1024 threads: 14 93.3, 15 94.2).  Without
+  // room a row goes to the repair pass, whatever the selection itself would take.
+  const int need = row_chunks(k, l.ranges);      // at most 113 for small rows, 232 for k = kFusedMaxK and 64 ranges
+  if (small_rows) {
+    if (need <= 8 * 10) GO(512, 10);
+    else if (need <= 8 * 11) GO(512, 11);
+    else if (need <= 8 * 14) GO(512, 14);
+    else GO(512, 15);
+  } else {
+    if (need <= 16 * 14) GO(1024, 14);
+    else GO(1024, 15);
+  }
 #undef GO
   if ((e = hipGetLastError()) != hipSuccess) return e;
 

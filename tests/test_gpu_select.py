@@ -196,6 +196,52 @@ def test_select_repairs_rows_with_misleading_samples(misa, sampled_are):
     check_against_oracle(inp, heads, idx, val, wl.k, [(0, 0), (0, 19)])
 
 
+@pytest.mark.parametrize("L,k,ranges,room", [
+    (8128, 2048, 16, 80),        # chunks of 64 entries of one key range that the row selection has room for:
+    (8128, 2300, 16, 88),        # the sizes of its kernels, each at a k and a number of ranges that takes it
+    (32768, 2048, 64, 112),
+    (32768, 2368, 64, 120),
+    (32768, 7000, 64, 224),
+    (32768, 8192, 64, 240),
+])
+@pytest.mark.parametrize("over", [0, 1])
+def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges, room, over):
+    # r sampled keys reach the threshold, as they always do, and so many others that the entries of the key ranges take
+    # `room` chunks (one more: the rows are repaired).  The last chunk of every range holds eight entries, so that the
+    # rows have no more entries than chance may give them (5.3 standard deviations of 15.5 sqrt(r) above 16 r).
+    wl = small("c2", L=L, n_q=16, k=k)
+    inp = WL.make_inputs(wl, seed=L % 1000 + k)
+    rng = np.random.default_rng(k)
+    mu = k / 16
+    r = int(np.ceil(mu + 6 * np.sqrt(mu) + 8))
+    per = -(-L // ranges // 64) * 64                       # keys of a range
+    chunks = np.full(ranges, (room + over) // ranges)
+    chunks[:(room + over) % ranges] += 1
+    count = 64 * chunks - 56
+    assert k <= count.sum() <= 16 * r + 5.3 * 15.5 * np.sqrt(r)
+    hits = np.full(ranges, r // ranges)
+    hits[:r % ranges] += 1
+    size = rng.uniform(0.25, 1.0, L)
+    for i in range(ranges):
+        keys = np.arange(i * per, min((i + 1) * per, L - 64))
+        sampled = np.array([sampled_position(j) for j in range(keys[0] // 16, (keys[-1] + 1) // 16)])
+        size[rng.choice(sampled, hits[i], replace=False)] = rng.uniform(2.0, 2.1, hits[i])
+        others = np.setdiff1d(keys, sampled)
+        size[rng.choice(others, count[i] - hits[i], replace=False)] = rng.uniform(2.2, 4.0, count[i] - hits[i])
+    direction = rng.uniform(0.5, 1.5, wl.d) * rng.choice([-1.0, 1.0], wl.d)
+    inp["K"] = WL.f32_to_bf16_bits((size[None, :, None] * direction).astype(np.float32))
+    inp["Q"] = WL.f32_to_bf16_bits((direction * rng.uniform(0.2, 1.0, inp["Q"].shape)).astype(np.float32))
+    inp["W"] = np.abs(inp["W"]) + 0.01
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    heads = random_heads(wl)
+    idx, val = one_call(misa, p, dv, heads, k)
+    ref_idx, ref_val = two_call(misa, p, dv, heads, k)
+    assert torch.equal(idx, ref_idx)
+    assert torch.equal(val, ref_val)
+    assert int(one_call.repaired.sum()) == (wl.n_q if over else 0)
+
+
 def test_select_longest_rows(misa):
     # the longest supported cache: bitmap and prefix arrays of the row kernel at their largest
     wl = small("c2", L=524288, n_q=8, k=1000, needles=8)
