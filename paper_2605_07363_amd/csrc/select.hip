@@ -436,7 +436,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     int q_tiles, int* __restrict__ idx, float* __restrict__ val, int* __restrict__ row_flag,
     int* __restrict__ tile_flag) {
   extern __shared__ __align__(16) uint32_t dyn[];  // the sampled selection's lists; or the selection bitmap, then the prefix count of every bitmap word
-  __shared__ int hist[kBins];
+  __shared__ __align__(16) int hist[kBins];   // (also the marks of equal scores, in words of 8 bytes: select_sampled)
   __shared__ int scan_scratch[32];
   __shared__ int thr[3];
   __shared__ uint32_t bkey[64];
