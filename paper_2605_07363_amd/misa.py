@@ -103,10 +103,13 @@ def _ptr(t: Optional[torch.Tensor]):
 # The handle of the current stream of the current device.  A call of the library is a few microseconds of host work, which
 # a chain of short kernels waits for: plain integers instead of ctypes objects and torch's own raw handle instead of a
 # Stream object save 2 to 3 us per call (five calls on one 4096-token sequence: 36 us, bound by the host, to 25 us).
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# The raw handle is not part of torch's public interface: where a torch does not have it, the Stream object is asked.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
     return _raw_stream(torch.cuda.current_device())
 
 

@@ -148,3 +148,19 @@ def test_route_heads_static_rejects_problems_beyond_its_scratch_array(misa):
     # argument validation comes first, as in misa_route_heads
     assert misa.lib.misa_route_heads_static(ctypes.byref(_prob(misa).c()), None, FAKE, FAKE, FAKE, None, FAKE,
                                             None, None) == 1
+
+
+def test_binding_without_the_raw_stream_handle_of_torch(misa, monkeypatch):
+    """torch's raw stream handle is not part of its public interface: a torch without it takes the public one."""
+    import importlib.util
+    import sys
+    import types
+
+    import torch
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=0x1230))
+    spec = importlib.util.spec_from_file_location("misa_without_raw_stream", misa.__file__)
+    m = importlib.util.module_from_spec(spec)
+    monkeypatch.setitem(sys.modules, spec.name, m)
+    spec.loader.exec_module(m)
+    assert m._stream() == 0x1230
