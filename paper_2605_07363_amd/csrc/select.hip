@@ -72,13 +72,15 @@ static int list_capacity(int k, int ranges) {
   return (int)((c + 255) / 256 * 256);
 }
 
-// Chunks of 64 entries of one key range that the row selection has to have room for.  The entries of a row have mean 16 r
-// and variance 240 r (r hits among samples of one key in 16), and a range's last chunk lacks 31.5 entries on average, with
-// variance 341; the room covers 5.5 standard deviations of the sum, as sample_rank does at the other end.  (At the line
-// about 3 rows in 10^7 have more; entries alone would leave k = 2300 in 16 ranges 4.2 deviations, 4 rows in 10^5.)
-static int row_chunks(int k, int ranges) {
+// Room for entries that the row selection has to have: a row's entries have mean 16 r and variance 240 r (r hits among
+// samples of one key in 16), of which 5.5 standard deviations are covered, as sample_rank does at the other end; and the
+// last chunk of every key range may hold a single entry.  (Chunks of 64 instead, a wavefront-wide load each,
+// lose up to 63 per range, and do where most ranges hold a few entries: 4 of 232 rows of k = 942 in 63 ranges needed more
+// than 5120 places for 2000 entries.)
+constexpr int kChunk = 16;                // entries of one key range that 16 lanes take together (128 bytes of the list)
+static int row_room(int k, int ranges) {
   const double r = sample_rank(k);
-  return (int)std::ceil((kSampleStride * r + 31.5 * ranges + 5.5 * std::sqrt(240.0 * r + 341.0 * ranges)) / 64.0);
+  return (int)std::ceil(kSampleStride * r + 5.5 * std::sqrt(240.0 * r)) + (kChunk - 1) * ranges;
 }
 
 static size_t select_lds_bytes(const Prob& p) {
@@ -232,7 +234,7 @@ template <int NT>
 constexpr size_t row_list_bytes() { return (size_t)(NT / 64) * (kRowSeg + 64) * 8; }
 
 template <int NT, int EPT>
-__device__ __forceinline__ bool select_sampled(const int (&ei)[EPT], const float (&ev)[EPT], int c, int chunks, int k, float tau, float top,
+__device__ __forceinline__ bool select_sampled(const int (&ei)[EPT], const float (&ev)[EPT], int c, int slabs, int k, float tau, float top,
                                                int* hist, int* scan_scratch, uint32_t* dyn, EntryLds<NT, EPT>& L,
                                                int* __restrict__ out_idx, float* __restrict__ out_val) {
   constexpr int NW = NT / 64;
@@ -246,7 +248,6 @@ __device__ __forceinline__ bool select_sampled(const int (&ei)[EPT], const float
   // ---- sample: one entry of every thread (hist is cleared, a barrier passed)
   float width;
   {
-    const int slabs = (chunks + NW - 1) / NW;
     const int us = (int)((((uint32_t)tid * 2654435761u >> 16) * (uint32_t)slabs) >> 16);
     uint32_t bits = 0;          // (a chain of selects would become an indexed load, and the entries scratch memory)
     bool valid = false;
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   __shared__ int bidx[64];
   __shared__ int b_len;
   __shared__ int brank[64];       // entries of the boundary list that rank before an entry
-  constexpr int NW = NT / 64;
+  constexpr int NW = NT / 64, kSlab = NT / kChunk;
   const int t = blockIdx.x, seq = blockIdx.y, tid = threadIdx.x;
   const size_t row = (size_t)seq * p.n_q + t;
   const int n = visible(p, seq, t);
@@ -456,8 +457,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   }
   if (k_eff == 0) return;
   // The row's entries: range r holds seg_count[r] of them from seg[r] on; a count above the segment's length means that
-  // hits were dropped.  They are taken in chunks of 64 of one range, chunk u NW + wave of the row by this wavefront; lane r
-  // of every wavefront looks after range r, and the wavefronts together write down where the chunks are.
+  // hits were dropped.  They are taken in chunks of kChunk of one range, one after another by 16 lanes each, in slabs of NT;
+  // lane r of every wavefront looks after range r, and the wavefronts together write down where the chunks are.
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int cnt = 0, len = 0, first_entry = 0;
   if (lane < ranges) {
@@ -466,9 +467,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
     cnt = seg_count[row * ranges + lane];
   }
   const bool dropped = __builtin_amdgcn_ballot_w64(cnt > len) != 0;
-  const int chunk_end = wave_inclusive_scan((cnt + 63) >> 6), chunks = __builtin_amdgcn_readlane(chunk_end, 63);
+  const int mine = (cnt + kChunk - 1) / kChunk;
+  const int chunk_end = wave_inclusive_scan(mine), chunks = __builtin_amdgcn_readlane(chunk_end, 63);
   const int entry_end = wave_inclusive_scan(cnt), c = __builtin_amdgcn_readlane(entry_end, 63);
-  if (dropped || chunks > NW * EPT || c < k_eff) {  // a segment overflowed, more entries than this kernel holds, or threshold too high: leave the row to the repair pass
+  if (dropped || chunks > kSlab * EPT || c < k_eff) {  // a segment overflowed, more entries than this kernel holds, or threshold too high: leave the row to the repair pass
     if (tid == 0) {
       row_flag[row] = 1;
       tile_flag[seq * q_tiles + t / qwg] = 1;
@@ -483,20 +485,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   int ei[EPT];
   float ev[EPT];
   const int2* src = cand + row * (size_t)cap;
-  __shared__ int4 s_chunk[NW * EPT];      // place in the row's list, entries, number in the row of a chunk's first entry
-  {
-    const int mine = (cnt + 63) >> 6;
-    for (int q = wave; __builtin_amdgcn_ballot_w64(q < mine) != 0; q += NW)
-      if (q < mine) s_chunk[chunk_end - mine + q] = make_int4(first_entry + 64 * q, min(cnt - 64 * q, 64), entry_end - cnt + 64 * q, 0);
-    for (int j = chunks + tid; j < NW * EPT; j += NT) s_chunk[j] = make_int4(0, 0, 0, 0);
-  }
+  __shared__ int2 s_chunk[kSlab * EPT];   // place of a chunk's first entry in the row's list; its number in the row and, in 8 bits, the chunk's entries
+  for (int q = wave; __builtin_amdgcn_ballot_w64(q < mine) != 0; q += NW)
+    if (q < mine)
+      s_chunk[chunk_end - mine + q] = make_int2(first_entry + kChunk * q, (entry_end - cnt + kChunk * q) << 8 | min(cnt - kChunk * q, kChunk));
+  for (int j = chunks + tid; j < kSlab * EPT; j += NT) s_chunk[j] = make_int2(0, 0);
   for (int i = tid; i < kBins; i += NT) hist[i] = 0;
   __syncthreads();
+  const int slabs = (chunks + kSlab - 1) / kSlab;
 #pragma unroll
   for (int u = 0; u < EPT; ++u) {
-    const int2 chunk = *reinterpret_cast<const int2*>(&s_chunk[u * NW + wave]);
-    const bool live = lane < chunk.y;
-    const int2 e = src[live ? chunk.x + lane : 0];
+    const int2 chunk = s_chunk[u * kSlab + tid / kChunk];
+    const int in_chunk = tid % kChunk;
+    const bool live = in_chunk < (chunk.y & 0xFF);
+    const int2 e = src[live ? chunk.x + in_chunk : 0];
     ei[u] = live ? e.x : -1;
     ev[u] = __int_as_float(e.y);
   }
@@ -504,14 +506,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 #pragma unroll
     for (int u = 0; u < EPT; ++u)
       if (ei[u] >= 0) {
-        const int at = s_chunk[u * NW + wave].z + lane;
+        const int at = (s_chunk[u * kSlab + tid / kChunk].y >> 8) + tid % kChunk;
         out_idx[at] = ei[u];
         if (out_val) out_val[at] = ev[u];
       }
     return;
   }
   __shared__ EntryLds<NT, EPT> entry_lds;
-  if (select_sampled<NT, EPT>(ei, ev, c, chunks, k_eff, tau[row], key_to_float(upper[row]), hist, scan_scratch, dyn, entry_lds, out_idx, out_val)) return;
+  if (select_sampled<NT, EPT>(ei, ev, c, slabs, k_eff, tau[row], key_to_float(upper[row]), hist, scan_scratch, dyn, entry_lds, out_idx, out_val)) return;
   // the digits of the keys instead
   __syncthreads();
   auto key_of = [&](int u) { return order_key(ev[u]); };
@@ -538,8 +540,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
       return x > span ? (uint32_t)(kBins - 1) : (x << sh) >> 21;
     };
 #pragma unroll
-    for (int u = 0; u < EPT; ++u)
+    for (int u = 0; u < EPT; ++u) {
       if (ei[u] >= 0) atomicAdd(&hist[digit(key_of(u))], 1);
+    }
     __syncthreads();
     find_threshold_bin_n<NT>(hist, k_eff, scan_scratch, thr);
     const uint32_t d1 = thr[0];
@@ -755,9 +758,9 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
   int2* cand = reinterpret_cast<int2*>(base + l.cand);
   const dim3 rows(p.n_q, p.n_seq);
 
-  // The row selection holds a row's entries in registers, in chunks of 64: 512 threads (8 chunks for every entry of a
-  // thread) for up to 5120 expected entries (16 r and six standard deviations of 16 sqrt(r)), 1024 above.  Rows all of
-  // whose visible keys are listed fill their chunks (a key range is whole tiles of 64 keys).
+  // The row selection holds a row's entries in registers: 512 threads x 10 or 12 for up to 5120 expected entries (16 r and
+  // six standard deviations of 16 sqrt(r)), 1024 x 13 or 14 above.  Rows all of whose visible keys are listed fill their
+  // chunks (a key range is whole tiles of 64 keys).
   const double rr = sample_rank(k);
   const bool small_rows = kSampleStride * rr * (1.0 + 6.0 / std::sqrt(rr)) <= 5120.0;
   const int entry_limit = small_rows ? 512 * 10 : 1024 * 13;
@@ -789,18 +792,14 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
     select_rows_kernel<NT, EPT><<<rows, NT, dyn, st>>>(p, cand, seg, seg_count, l.ranges, tau, upper, l.cap, k, \
                                                        l.qwg, l.q_tiles, idx, val, row_flag, tile_flag); \
   } while (0)
-  // The smallest room that row_chunks asks for (us, entries per thread: 4096 rows of k = 2048, 16 ranges: 10 60.0, 11 61.6, 14
-  // 66.8; 1000 of k = 1024, 63 ranges: 10 22.5, 14 24.8; 2048 of k = 8192, 32 ranges, 1024 threads: 14 93.3, 15 94.2).  Without
-  // room a row goes to the repair pass, whatever the selection itself would take.
-  const int need = row_chunks(k, l.ranges);      // at most 113 for small rows, 232 for k = kFusedMaxK and 64 ranges
+  // the smallest room that is enough: without it a row goes to the repair pass, whatever the selection itself would take
+  const int room = row_room(k, l.ranges);      // at most 5914 for small rows, 13639 for k = kFusedMaxK (64 ranges)
   if (small_rows) {
-    if (need <= 8 * 10) GO(512, 10);
-    else if (need <= 8 * 11) GO(512, 11);
-    else if (need <= 8 * 14) GO(512, 14);
-    else GO(512, 15);
+    if (room <= 512 * 10) GO(512, 10);
+    else GO(512, 12);
   } else {
-    if (need <= 16 * 14) GO(1024, 14);
-    else GO(1024, 15);
+    if (room <= 1024 * 13) GO(1024, 13);
+    else GO(1024, 14);
   }
 #undef GO
   if ((e = hipGetLastError()) != hipSuccess) return e;

@@ -196,29 +196,27 @@ def test_select_repairs_rows_with_misleading_samples(misa, sampled_are):
     check_against_oracle(inp, heads, idx, val, wl.k, [(0, 0), (0, 19)])
 
 
-@pytest.mark.parametrize("L,k,ranges,room", [
-    (8128, 2048, 16, 80),        # chunks of 64 entries of one key range that the row selection has room for:
-    (8128, 2300, 16, 88),        # the sizes of its kernels, each at a k and a number of ranges that takes it
-    (32768, 2048, 64, 112),
-    (32768, 2368, 64, 120),
-    (32768, 7000, 64, 224),
-    (32768, 8192, 64, 240),
+@pytest.mark.parametrize("L,k,ranges,room,repaired", [
+    (8128, 2300, 16, 5120, True),       # entries that each kernel of the row selection has room for, at a k and a number of
+    (32768, 2048, 64, 6144, True),      # key ranges that takes it
+    (32768, 7000, 64, 13312, True),
+    (32768, 8192, 64, 14336, True),
 ])
 @pytest.mark.parametrize("over", [0, 1])
-def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges, room, over):
-    # r sampled keys reach the threshold, as they always do, and so many others that the entries of the key ranges take
-    # `room` chunks (one more: the rows are repaired).  The last chunk of every range holds eight entries, so that the
-    # rows have no more entries than chance may give them (5.3 standard deviations of 15.5 sqrt(r) above 16 r).
+def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges, room, repaired, over):
+    # r sampled keys reach the threshold, as they always do, and so many others that the entries of the key ranges, in
+    # chunks of 16, take the whole room (one more: the rows are repaired).  The last chunk of every range
+    # holds one entry, which is the most room that a given number of entries may need.
     wl = small("c2", L=L, n_q=16, k=k)
     inp = WL.make_inputs(wl, seed=L % 1000 + k)
     rng = np.random.default_rng(k)
     mu = k / 16
     r = int(np.ceil(mu + 6 * np.sqrt(mu) + 8))
     per = -(-L // ranges // 64) * 64                       # keys of a range
-    chunks = np.full(ranges, (room + over) // ranges)
-    chunks[:(room + over) % ranges] += 1
-    count = 64 * chunks - 56
-    assert k <= count.sum() <= 16 * r + 5.3 * 15.5 * np.sqrt(r)
+    chunks = np.full(ranges, (room // 16 + over) // ranges)
+    chunks[:(room // 16 + over) % ranges] += 1
+    count = 16 * chunks - 15
+    assert count.sum() >= max(k, 16 * r)
     hits = np.full(ranges, r // ranges)
     hits[:r % ranges] += 1
     size = rng.uniform(0.25, 1.0, L)
@@ -239,7 +237,7 @@ def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges,
     ref_idx, ref_val = two_call(misa, p, dv, heads, k)
     assert torch.equal(idx, ref_idx)
     assert torch.equal(val, ref_val)
-    assert int(one_call.repaired.sum()) == (wl.n_q if over else 0)
+    assert int(one_call.repaired.sum()) == (wl.n_q if over and repaired else 0)
 
 
 def test_select_longest_rows(misa):
