@@ -197,15 +197,19 @@ def test_select_repairs_rows_with_misleading_samples(misa, sampled_are):
 
 
 @pytest.mark.parametrize("L,k,ranges,room,repaired", [
-    (8128, 2300, 16, 5120, True),       # entries that each kernel of the row selection has room for, at a k and a number of
-    (32768, 2048, 64, 6144, True),      # key ranges that takes it
+    (8128, 200, 16, 1536, False),       # entries that the parts of the 512-thread row selection end at,
+    (8128, 700, 16, 3072, False),
+    (32768, 2500, 64, 5120, False),     # of the 1024-thread one,
+    (32768, 4096, 64, 8192, False),
+    (8128, 2300, 16, 5120, True),       # and that each of its kernels has room for, at a k and a number of key ranges
+    (32768, 2048, 64, 6144, True),      # that takes it
     (32768, 7000, 64, 13312, True),
     (32768, 8192, 64, 14336, True),
 ])
 @pytest.mark.parametrize("over", [0, 1])
 def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges, room, repaired, over):
     # r sampled keys reach the threshold, as they always do, and so many others that the entries of the key ranges, in
-    # chunks of 16, take the whole room (one more: the rows are repaired).  The last chunk of every range
+    # chunks of 16, take the whole room (one more: the next part, or the rows are repaired).  The last chunk of every range
     # holds one entry, which is the most room that a given number of entries may need.
     wl = small("c2", L=L, n_q=16, k=k)
     inp = WL.make_inputs(wl, seed=L % 1000 + k)
@@ -238,6 +242,25 @@ def test_select_rows_that_fill_the_room_of_the_row_selection(misa, L, k, ranges,
     assert torch.equal(idx, ref_idx)
     assert torch.equal(val, ref_val)
     assert int(one_call.repaired.sum()) == (wl.n_q if over and repaired else 0)
+
+
+@pytest.mark.parametrize("k", [1, 127, 128, 2040])
+@pytest.mark.parametrize("gates", ["random", "negative", "zero"])
+def test_select_rows_around_the_shortest_sampled_list(misa, k, gates):
+    # Rows of 2044 to 2051 visible keys, all of them listed: from 2048 entries and k = 128 on the selection samples its bracket.
+    wl = small("c2", L=4500, n_q=8, k=k)
+    inp = WL.make_inputs(wl, seed=k)
+    inp["q_pos"] = np.arange(2043, 2051, dtype=np.int32)
+    if gates != "random":
+        inp["W"] = -np.abs(inp["W"]) if gates == "negative" else 0 * inp["W"]
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    heads = random_heads(wl)
+    idx, val = one_call(misa, p, dv, heads, k)
+    ref_idx, ref_val = two_call(misa, p, dv, heads, k)
+    assert torch.equal(idx, ref_idx)
+    assert torch.equal(val, ref_val)
+    assert int(one_call.repaired.sum()) == 0
 
 
 def test_select_longest_rows(misa):
