@@ -1327,8 +1327,12 @@ int tile_key_ranges(const Prob& p, bool routed, bool q8, int mode, int* keys_per
   while (splits < 64 && (long long)splits * q_tiles * p.n_seq < 2048 && lt / (splits * 2) >= 1024) splits *= 2;
   // Where that leaves CUs without a workgroup, ranges of down to four tiles, while all of them run at once (two per
   // CU; us, 1024 keys / this: 333 queries x 10007 keys 26.3 / 16.1, 32 x 10007 20.5 / 9.9, 8 x 4096 13.0 / 9.6,
-  // 1000 x 10007 30.2 / 27.8; past two per CU, 400 x 20000 in ranges of 313 keys 31.9, of 625 25.5).
-  while (splits < 64 && 2ll * splits * q_tiles * p.n_seq <= 512 && lt / (splits * 2) >= 256) splits *= 2;
+  // 1000 x 10007 30.2 / 27.8; past two per CU, 400 x 20000 in ranges of 313 keys 31.9, of 625 25.5).  One per CU where a
+  // workgroup has 512 head rows to prepare, or two of 256 run no faster (one / two per CU: 160 queries of 64 heads x 4200 keys
+  // 20.7 / 26.7, x 8300 33.6 / 39.2; 704 of 8 heads, fp8 codes, x 16500 38.0 / 42.0; 160 of 32 heads x 4200 13.6 / 14.3).
+  const int hc = routed ? p.h : p.H;
+  const int most = hc > 16 || (hc <= 8 && q8 && mode == kTileStore) ? 256 : 512;
+  while (splits < 64 && 2ll * splits * q_tiles * p.n_seq <= most && lt / (splits * 2) >= 256) splits *= 2;
   *keys_per_wg = ((lt + splits - 1) / splits + kKT - 1) / kKT * kKT;
   return (lt + *keys_per_wg - 1) / *keys_per_wg;
 }

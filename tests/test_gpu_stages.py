@@ -232,6 +232,34 @@ def test_score_with_all_heads_listed_equals_dense(misa):
     assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("base,n_q,L,h,dense,q_matrix", [
+    ("c2", 128, 8300, 8, True, False),      # 64 heads: 16 query tiles, two and one workgroups per CU
+    ("c2", 129, 4200, 8, True, False),
+    ("c4", 704, 16500, 8, False, True),     # fp8 codes on both sides, tiles of 64 queries
+    ("c2", 160, 4200, 32, False, False),
+    ("c2", 333, 10007, 8, False, False),
+])
+def test_scores_do_not_depend_on_the_key_ranges(misa, base, n_q, L, h, dense, q_matrix):
+    # the number of key ranges per query tile follows from the number of queries: a call for all of them against calls for 24
+    from dataclasses import replace
+    wl = small(base, L=L, n_q=n_q, h=h, k=64, k_cand=0, needles=8, **(dict(q_dtype="e4m3") if q_matrix else {}))
+    dv = misa.to_device(WL.make_inputs(wl, seed=n_q))
+    p = dv["problem"]
+    if q_matrix:
+        p = replace(p, q_dtype=misa.FP8_E4M3_MATRIX)
+    rng = np.random.default_rng(n_q)
+    heads = torch.from_numpy(np.stack([np.sort(rng.choice(wl.H, wl.h, replace=False)) for _ in range(n_q)])[None].astype(np.int32)).cuda()
+    S = torch.full((1, n_q, L), 7.0, dtype=torch.float32, device="cuda")
+    misa.score_tokens(p, dv["Q"], dv["W"], None if dense else heads, dv["K"], dv["kscale"], S, misa.alloc_workspace(p, misa.OP_SCORE))
+    for a in range(0, n_q, 24):
+        a = min(a, n_q - 24)
+        part = replace(p, n_q=24, q_pos=dv["q_pos"][a:a + 24].contiguous())
+        s = torch.full((1, 24, L), 7.0, dtype=torch.float32, device="cuda")
+        misa.score_tokens(part, dv["Q"][:, a:a + 24].contiguous(), dv["W"][:, a:a + 24].contiguous(), None if dense else heads[:, a:a + 24].contiguous(),
+                          dv["K"], dv["kscale"], s, misa.alloc_workspace(part, misa.OP_SCORE))
+        assert torch.equal(S[:, a:a + 24], s)
+
+
 # --------------------------------------------------------------------- top-k
 def _topk_case(misa, S, k, q_pos=None, seq_len=None):
     n_seq, n_q, L = S.shape
