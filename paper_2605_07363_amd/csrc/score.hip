@@ -27,21 +27,24 @@ namespace misa {
 
 // ------------------------------------------------------------------ generic
 // The four lanes of a quad read 64 contiguous bytes of their key's row per load, all loads at once, and add their sums.
-// Bound by latency for few keys (one query of 8 heads, 4096 fp32 keys: 7.0 us with a lane per key, whose 32 loads follow
-// one another on 16 CUs; 4.5 us now) and by the multiply-adds and the LDS reads of the query for many.
+// Bound by latency for few keys (one query of 8 heads, 4096 fp32 keys: 6.6 us with a lane per key, whose 32 loads follow
+// one another on 16 CUs; 3.8 us now) and by the multiply-adds and the LDS reads of the query for many.
 template <int KDT, int QDT>
 __global__ __launch_bounds__(256) void score_generic_kernel(
     Prob p, const void* __restrict__ Q, const float* __restrict__ W, const int* __restrict__ heads,
     const void* __restrict__ K, const float* __restrict__ kscale, const int* __restrict__ cand,
     int k_cand, int groups, float* __restrict__ out) {
-  __shared__ __align__(16) float qs[kMaxH][kD];
-  __shared__ float wsm[kMaxH];
+  // query heads, padded to a multiple of 8, then their gates: no more LDS than they need, so that eight heads leave
+  // room for the eight workgroups that a CU takes
+  extern __shared__ __align__(16) float generic_lds[];
   using KV = Vec16<KDT>;
   using QV = Vec16<QDT>;
   const int t = blockIdx.y, seq = blockIdx.z, tid = threadIdx.x;
   const int n = visible(p, seq, t);
   const int hc = heads ? p.h : p.H;
   const int hpad = (hc + 7) & ~7;
+  float (*const qs)[kD] = reinterpret_cast<float (*)[kD]>(generic_lds);
+  float* const wsm = generic_lds + hpad * kD;
   const size_t qrow = (size_t)seq * p.n_q + t;
 
   // Gather the active heads (zero rows for padding and for invalid indices).
@@ -1254,10 +1257,18 @@ static hipError_t launch_generic(const Prob& p, const void* Q, const float* W, c
                                  const void* K, const float* kscale, const int* cand, int k_cand,
                                  float* out, hipStream_t st) {
   const int row_len = cand ? k_cand : p.L;
-  // 64 keys per workgroup where that fills the chip no more than once (eight workgroups per CU), else 256 share the set-up
-  const int groups = (long long)((row_len + 63) / 64) * p.n_q * p.n_seq <= 2048 ? 1 : 4;
+  const int hpad = ((heads ? p.h : p.H) + 7) & ~7;
+  const int lds = hpad * (kD + 1) * (int)sizeof(float);
+  // 64 keys per workgroup where the chip takes all of those at once (eight per CU by registers, five with fp32 keys, four
+  // by LDS with 64 heads), else 128 share the set-up, and 256 where there are many turns of them
+  // (us, lane per key / this: one query of 8 heads x 4096 fp32 keys 6.6 / 3.8, 2 x 120 x 554 11.6 / 8.9,
+  // 500 x 890 bf16 keys 22.3 / 17.0, 96 x 2951 fp8 candidates of 64 heads 181 / 136; 256 keys and room for 64 heads in every
+  // workgroup: 14.2 for 2 x 120 x 554, 23.0 for 500 x 890, 175; 128 against 256 keys: 32 x 21 x 12143 fp32 keys 538 / 497)
+  const int at_once = 256 * std::min(KDT == MISA_F32 ? 5 : 8, 160 * 1024 / lds);
+  const long long most = (long long)((row_len + 63) / 64) * p.n_q * p.n_seq;
+  const int groups = most <= at_once ? 1 : most <= 16 * at_once ? 2 : 4;
   const dim3 grid((row_len + 64 * groups - 1) / (64 * groups), p.n_q, p.n_seq);
-  score_generic_kernel<KDT, QDT><<<grid, 256, 0, st>>>(p, Q, W, heads, K, kscale, cand, k_cand, groups, out);
+  score_generic_kernel<KDT, QDT><<<grid, 256, lds, st>>>(p, Q, W, heads, K, kscale, cand, k_cand, groups, out);
   return hipGetLastError();
 }
 

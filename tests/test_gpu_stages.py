@@ -260,6 +260,34 @@ def test_scores_do_not_depend_on_the_key_ranges(misa, base, n_q, L, h, dense, q_
         assert torch.equal(S[:, a:a + 24], s)
 
 
+@pytest.mark.parametrize("k_dtype", ["f32", "bf16", "e4m3"])
+@pytest.mark.parametrize("n_q,L,h", [(142, 519, 8), (143, 519, 8), (227, 519, 8), (228, 519, 8), (100, 1345, 3), (41, 4097, 64), (65, 2047, 17), (700, 3333, 5)])
+def test_fp32_query_scores_do_not_depend_on_the_keys_per_workgroup(misa, k_dtype, n_q, L, h):
+    # 64 keys per workgroup while the chip takes all of those at once (227 queries of 519 keys, 142 with fp32 keys), 128
+    # beyond and 256 from 16 times as many on: a call for all queries against calls for 20 of them, and some rows against the oracle
+    from dataclasses import replace
+    wl = small("c2", L=L, n_q=n_q, h=h, k=64, k_dtype=k_dtype, q_dtype="f32", needles=4)
+    inp = WL.make_inputs(wl, seed=n_q)
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    rng = np.random.default_rng(n_q)
+    heads = np.stack([np.sort(rng.choice(wl.H, wl.h, replace=False)) for _ in range(n_q)])[None].astype(np.int32)
+    dheads = torch.from_numpy(heads).cuda()
+    S = torch.full((1, n_q, L), 7.0, dtype=torch.float32, device="cuda")
+    misa.score_tokens(p, dv["Q"], dv["W"], dheads, dv["K"], dv["kscale"], S, misa.alloc_workspace(p, misa.OP_SCORE))
+    for a in range(0, n_q, 20):
+        a = min(a, n_q - 20)
+        part = replace(p, n_q=20, q_pos=dv["q_pos"][a:a + 20].contiguous())
+        s = torch.full((1, 20, L), 7.0, dtype=torch.float32, device="cuda")
+        misa.score_tokens(part, dv["Q"][:, a:a + 20].contiguous(), dv["W"][:, a:a + 20].contiguous(), dheads[:, a:a + 20].contiguous(),
+                          dv["K"], dv["kscale"], s, misa.alloc_workspace(part, misa.OP_SCORE))
+        assert torch.equal(S[:, a:a + 20], s)
+    for t in (0, n_q // 2, n_q - 1):
+        K, q, w, n = oracle_view(inp, 0, t)
+        assert_scores_close(S[0, t, :n].cpu().numpy(), O.score_tokens(q, w, heads[0, t], K, n), f"row {t}")
+        assert bool(torch.all(torch.isneginf(S[0, t, n:])))
+
+
 # --------------------------------------------------------------------- top-k
 def _topk_case(misa, S, k, q_pos=None, seq_len=None):
     n_seq, n_q, L = S.shape
