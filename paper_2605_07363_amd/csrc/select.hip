@@ -786,11 +786,15 @@ hipError_t launch_select(const Prob& p, int k_dtype, int q_dtype, const void* Q,
   const double rr = sample_rank(k);
   const bool small_rows = kSampleStride * rr * (1.0 + 6.0 / std::sqrt(rr)) <= 5120.0;
   const int entry_limit = small_rows ? 512 * 10 : 1024 * 13;
+  // Listed whole: rows of what a list in 8 key ranges has room for.  (A list in more ranges has more room, 450 entries per
+  // range for k = 2, but a threshold costs less than entries that it would have kept away: 313 rows of up to 5139 keys, k = 2, 16 ranges
+  // 48.8 us with rows of 5120 listed whole, 42.7 with 8 ranges.)
+  const int keep_all = std::min(std::min(l.cap, list_capacity(k, 8)), entry_limit);
 
   hipError_t e = launch_tile_mode(p, k_dtype, q_dtype, kTileSample, TileAux{}, Q, W, heads, K, kscale, Ss, st);
   if (e != hipSuccess) return e;
   select_threshold_kernel<<<p.n_seq * p.n_q, kThrThreads, 0, st>>>(
-      p, Ss, l.m, sample_rank(k), l.cap, std::min(l.cap, entry_limit), l.qwg, l.q_tiles, l.ranges, l.keys_per_range, max_sample_hits(k), tau,
+      p, Ss, l.m, sample_rank(k), l.cap, keep_all, l.qwg, l.q_tiles, l.ranges, l.keys_per_range, max_sample_hits(k), tau,
       upper, seg, row_flag, tile_flag);
   if ((e = hipGetLastError()) != hipSuccess) return e;
 

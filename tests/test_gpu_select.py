@@ -8,6 +8,8 @@ routes: the sampled-threshold route, rows short enough to keep every key, rows
 whose threshold comes out too high or too low (repaired inside the call), and
 problems it hands to the two-call path.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -261,6 +263,40 @@ def test_select_rows_around_the_shortest_sampled_list(misa, k, gates):
     assert torch.equal(idx, ref_idx)
     assert torch.equal(val, ref_val)
     assert int(one_call.repaired.sum()) == 0
+
+
+@pytest.mark.parametrize("L,n_q,h,k,whole", [
+    (5139, 313, 16, 2, 4608),      # 14 key ranges
+    (4990, 400, 16, 30, 4864),     # 16
+    (9000, 40, 8, 1, 4608),        # 29
+])
+def test_select_lists_rows_whole_up_to_the_room_of_eight_ranges(misa, L, n_q, h, k, whole):
+    """A small k in many key ranges has room for more entries than a threshold would let through: which rows are listed
+    whole must not follow that room.  The segments of a row that is listed whole add up to its visible keys."""
+    wl = small("c2", L=L, n_q=n_q, h=h, k=k)
+    inp = WL.make_inputs(wl, seed=L)
+    inp["q_pos"] = (L - 1 - np.arange(n_q) * 7 % 1100).astype(np.int32)
+    inp["q_pos"][:2] = whole - 1, min(whole, L - 1)
+    dv = misa.to_device(inp)
+    p = dv["problem"]
+    heads = random_heads(wl)
+    idx, val = one_call(misa, p, dv, heads, k)
+    ref_idx, ref_val = two_call(misa, p, dv, heads, k)
+    assert torch.equal(idx, ref_idx)
+    assert torch.equal(val, ref_val)
+    ws = misa.alloc_workspace(p, misa.OP_SELECT, k)
+    misa.select_tokens(p, dv["Q"], dv["W"], heads, dv["K"], dv["kscale"], k, idx, val, ws)
+    torch.cuda.synchronize()
+    up, up64 = (lambda x: (x + 255) // 256 * 256), (lambda x: (x + 63) // 64 * 64)
+    q_tiles = -(-n_q // (32 if h <= 8 else 16))
+    ranges = next(s for s in (8, 16, 32, 64) if 2 * s * q_tiles > 512 or L // (2 * s) < 256)
+    ranges = -(-L // up64(-(-L // ranges)))                # (of whole tiles of 64 keys)
+    at = misa.lib.misa_select_row_flags_offset(ctypes.byref(p.c()), 1, k) + up(4 * n_q) + up(4 * q_tiles)
+    seg = ws[at:at + 4 * n_q * (ranges + 1)].view(torch.int32).view(n_q, ranges + 1).cpu().numpy()
+    n = inp["q_pos"] + 1
+    assert np.all(seg[:, 0] == 0) and np.all(np.diff(seg, axis=1) >= 0)
+    assert np.array_equal(seg[n <= whole, -1], n[n <= whole])
+    assert np.all(seg[n > whole, -1] < n[n > whole])
 
 
 def test_select_longest_rows(misa):
