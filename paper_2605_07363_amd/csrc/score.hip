@@ -654,7 +654,8 @@ __device__ __forceinline__ void score_tile_body(
     }
   }
   // Stores the hits of accumulator slot j named by the ballot m (score sc, key key of this
-  // lane) into the segments of its two queries and advances their fills.
+  // lane) into the segments of its two queries and advances their fills.  Column tiles come here in key
+  // order and lanes are keys: a segment is in ascending key order, which the row selection relies on.
   const unsigned long long upper_half = 0xFFFFFFFF00000000ull;
   auto append_hits = [&](int j, unsigned long long m, int key, float sc) {
     const uint32_t m_lo = (uint32_t)m, m_hi = (uint32_t)(m >> 32);

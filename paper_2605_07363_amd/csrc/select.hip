@@ -14,12 +14,16 @@
 //                (key, score) pairs with score >= tau to per-row lists.  A row's
 //                list is cut into one segment per key range of that launch,
 //                sized in step 2 from the range's own sampled scores, so every
-//                segment has exactly one writer and needs no atomics.
+//                segment has exactly one writer and needs no atomics.  Segments
+//                are filled in ascending key order: step 4 takes an entry's place
+//                in the list for its rank by index.
 //   4. select    Per row, the exact top-k of the list (ties: lower index) is
-//                chosen by radix select in LDS and written in ascending index
-//                order.  Since every score >= tau is in the list, the result
-//                equals the top-k of the full row whenever the list holds at
-//                least k entries and did not overflow.
+//                written in ascending index order: from a bracket that a sample
+//                of the entries gives and the counts prove (select_sampled), or,
+//                where the list or k is short or the bracket wrong, from
+//                the digits of the keys.  Since every score >= tau is in the
+//                list, the result equals the top-k of the full row whenever the
+//                list holds at least k entries and did not overflow.
 //   5. repair    Rows for which that does not hold are flagged; the plain path
 //                (dense scores of their query tiles, then the row top-k) runs
 //                for them only.  Without flagged rows these two launches exit
@@ -548,8 +552,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   zero_hist_n<NT>(hist);
   auto mark = [&](int e) { atomicOr(&sel[e >> 5], 1u << (e & 31)); };
 
-  // Short way: one digit of key - key(tau), scaled so that [tau, upper] fills the 2047 lower
-  // values of the digit (larger keys share 2047).  The list entries then spread over the whole
+  // Lists below kSampledMin and k below kSampledMinK, as a rule: one digit of key - key(tau), scaled so that [tau, upper]
+  // fills the 2047 lower values of the digit (larger keys share 2047).  The list entries then spread over the whole
   // histogram instead of piling up in the few bins a raw key prefix gives them; entries above
   // the digit of the k-th largest are selected and the few inside it ranked against each other
   // (score descending, index ascending).  More than 64 entries in that digit, or the catch-all

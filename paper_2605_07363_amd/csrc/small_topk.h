@@ -6,8 +6,8 @@
 // selected, the k largest of the rest are, ties go to the lower position, positions come out in
 // ascending order and unused output slots hold -1 / -inf.
 //
-// Method: pick_row, from a sampled bracket, for rows of 2048 scores and more; small_row_by_digits for the others and
-// for rows that the bracket does not fit.
+// Method: pick_row, from a sampled bracket; small_row_by_digits for rows that the bracket does not fit.  (Rows below 2048
+// scores have no such bracket and do not come here.)
 #pragma once
 
 #include "kernels.h"
@@ -280,7 +280,6 @@ __device__ __forceinline__ bool pick_row(int* sc, int n, int k, const int* __res
                                          int* __restrict__ out_idx, float* __restrict__ out_val, PickLds& L) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (n < 2 * kPickSamples) return false;
   const float kf = (float)k * (float)kPickSamples / (float)n, margin = 4.f * sqrtf(kf) + 8.f;
   const int r_lo = (int)ceilf(kf + margin), r_hi = (int)floorf(kf - margin);
   if (r_lo > kPickSamples) return false;

@@ -254,11 +254,15 @@ def test_block_scores_of_infinite_components(misa, H, what):
 
 
 MANY = {
-    # from 1024 rows on the dense scores of up to 8192 candidates and their top-k are one kernel
+    # from 704 rows on the dense scores of 2048 to 8192 candidates (m blocks of B) and their top-k are one kernel
     "bf16": (small("c2", L=3001, n_q=1024, B=64, k=200, H=32, h=8), 9),
     "fp8_keys": (small("c4", L=2500, n_q=1100, B=32, k=128, k_cand=0, H=64, needles=16), 12),
     "two_sequences": (small("c2", n_seq=2, L=2777, n_q=513, B=100, k=300, H=40, h=8), 7),
     "fp8_queries": (small("c4", n_seq=2, L=2000, n_q=512, B=64, k=64, k_cand=0, H=17, h=8, q_dtype="e4m3", needles=4), 5),
+    "2560_candidates": (small("c2", L=3001, n_q=1024, B=64, k=200, H=32, h=8), 40),
+    "2048_candidates_fp8_keys": (small("c4", L=2500, n_q=1100, B=32, k=128, k_cand=0, H=64, needles=16), 64),
+    "2100_candidates_of_two": (small("c2", n_seq=2, L=2777, n_q=513, B=100, k=300, H=40, h=8), 21),
+    "2112_candidates_fp8_queries": (small("c4", n_seq=2, L=2500, n_q=512, B=64, k=64, k_cand=0, H=17, h=8, q_dtype="e4m3", needles=4), 33),
     "8192_candidates": (small("c2", L=9000, n_q=1030, B=128, k=2048, H=8, h=8), 64),
     "8256_candidates": (small("c2", L=9000, n_q=1030, B=129, k=2048, H=8, h=8), 64),
     "k_of_all": (small("c2", L=600, n_q=1024, B=50, k=250, H=16, h=8), 5),

@@ -1,7 +1,8 @@
-"""Re-rank of many queries with short candidate lists (Eq. misa_final_topk on Eq. dsa_score of
-the candidates): the library takes the dense scores and their top-k in one kernel there.  Checked
-against the oracle and, bit for bit, against the same rows re-ranked as sub-problems too small
-for that kernel (dense scores through the workspace, then the row top-k)."""
+"""Re-rank of many queries (Eq. misa_final_topk on Eq. dsa_score of the candidates): from 704 queries on
+the library takes the dense scores of lists of 2048 to 8192 candidates and their top-k in one kernel.
+Checked against the oracle and, bit for bit, against the same rows re-ranked as sub-problems too small
+for that kernel (dense scores through the workspace, then the row top-k); shorter and longer lists take
+the two kernels whatever the number of queries."""
 from dataclasses import replace
 
 import numpy as np
@@ -22,7 +23,7 @@ def misa():
     return m
 
 
-ROWS = 1100          # above the library's threshold for the one-kernel path (1024 rows)
+ROWS = 1100          # above the library's threshold for the one-kernel path (704 rows)
 
 
 def _problem(seed, k_dtype, q_dtype, H, L):
@@ -85,6 +86,9 @@ def _check_rows_against_oracle(inp, cand, idx, val, k, rows, what, abs_frac=ABS_
     ("e4m3", "bf16", 64, 1024, 1024),    # k = k': everything that is valid is kept
     ("e4m3", "bf16", 17, 333, 50),       # one row tile, odd head count
     ("bf16", "bf16", 32, 2500, 640),
+    ("bf16", "bf16", 64, 2100, 300),     # (from here on one kernel) not a multiple of the 128-candidate step
+    ("e4m3", "bf16", 64, 2048, 2048),    # k = k'
+    ("e4m3", "bf16", 17, 2333, 50),      # one row tile, odd head count
 ])
 def test_many_query_rerank_against_the_oracle(misa, k_dtype, q_dtype, H, kc, k):
     seed = 9900 + kc
@@ -105,10 +109,11 @@ def test_many_query_rerank_against_the_oracle(misa, k_dtype, q_dtype, H, kc, k):
     assert torch.equal(val, val2)
 
 
-def test_many_query_rerank_on_the_fp8_matrix_instruction(misa):
+@pytest.mark.parametrize("kc,k", [(900, 128), (2900, 700)])     # two kernels, one
+def test_many_query_rerank_on_the_fp8_matrix_instruction(misa, kc, k):
     if not misa.HAS_FP8_MFMA:
         pytest.skip("library built without the fp8 matrix path")
-    seed, L, kc, k = 9931, 3000, 900, 128
+    seed, L = 9931, 3000
     rng = np.random.default_rng(seed)
     wl, inp = _problem(seed, "e4m3", "e4m3", 64, L)
     dv = misa.to_device(inp)
@@ -177,11 +182,12 @@ def test_longest_list_the_kernel_takes(misa):
         _check_rows_against_oracle(inp, cand, idx.cpu().numpy(), val.cpu().numpy(), k, sample, f"rerank k'={kc}")
 
 
+@pytest.mark.parametrize("kc", [1500, 2200])
 @pytest.mark.parametrize("paged", [False, True])
-def test_many_query_rerank_over_several_ragged_sequences(misa, paged):
-    # 3 sequences x 400 queries (1200 rows: the one-kernel path), ragged lengths, optionally a page
+def test_many_query_rerank_over_several_ragged_sequences(misa, paged, kc):
+    # 3 sequences x 400 queries (1200 rows: with 2200 candidates the one-kernel path), ragged lengths, optionally a page
     # pool; every sequence alone (400 rows: dense scores + row top-k) must give the same bits
-    seed, L, kc, k, n_seq, n_q = 9990, 2500, 1500, 300, 3, 400
+    seed, L, k, n_seq, n_q = 9990, 2500, 300, 3, 400
     rng = np.random.default_rng(seed)
     wl = WL.scaled(WL.WORKLOADS["c2"], n_seq=n_seq, L=L, n_q=n_q, H=64, h=1, B=64, k=1, k_cand=0,
                    k_dtype="e4m3", q_dtype="bf16", needles=6, name="rrf_multi")
@@ -222,10 +228,11 @@ def test_many_query_rerank_over_several_ragged_sequences(misa, paged):
             assert_scores_close(vh[s, t, :ke], dense[got[:ke]], f"multi values {s},{t}")
 
 
-def test_many_query_rerank_writes_only_its_outputs(misa):
+@pytest.mark.parametrize("kc", [777, 2049])                     # two kernels, one
+def test_many_query_rerank_writes_only_its_outputs(misa, kc):
     # idx / val are windows of larger buffers filled with a sentinel: nothing outside them changes,
     # and the candidate list (which the kernel overwrites in LDS, not in memory) stays as it was
-    seed, L, kc, k = 9995, 2000, 777, 129
+    seed, L, k = 9995, 2000, 129
     rng = np.random.default_rng(seed)
     wl, inp = _problem(seed, "e4m3", "bf16", 64, L)
     dv = misa.to_device(inp)
@@ -247,8 +254,8 @@ def test_many_query_rerank_writes_only_its_outputs(misa):
 
 
 @pytest.mark.parametrize("kc,k,H,k_dtype", [
-    (2047, 512, 64, "bf16"),      # the longest list that is not sampled
-    (2048, 512, 64, "e4m3"),      # the shortest that is, exactly eight scores per thread
+    (2047, 512, 64, "bf16"),      # the longest of the short lists that take two kernels
+    (2048, 512, 64, "e4m3"),      # the shortest that the one kernel takes, exactly eight scores per thread
     (2049, 2040, 32, "bf16"),     # one score in the last walk; more wanted than the sample can bracket
     (2303, 1, 64, "e4m3"),        # no upper end
     (5000, 1250, 64, "bf16"),
@@ -308,7 +315,7 @@ def test_many_query_rerank_nan_beside_exactly_k_infinite_scores(misa):
 
 
 @pytest.mark.parametrize("rows", [703, 704, 1023])
-@pytest.mark.parametrize("k_dtype,q_dtype,H,kc,k", [("bf16", "bf16", 64, 2048, 512), ("e4m3", "e4m3", 32, 2100, 700), ("e4m3", "bf16", 20, 600, 64)])
+@pytest.mark.parametrize("k_dtype,q_dtype,H,kc,k", [("bf16", "bf16", 64, 2048, 512), ("e4m3", "e4m3", 32, 2100, 700), ("e4m3", "bf16", 20, 600, 64), ("e4m3", "bf16", 20, 2300, 64)])
 def test_rerank_around_the_one_kernel_threshold(misa, rows, k_dtype, q_dtype, H, kc, k):
     seed, L = 9700 + rows + kc, 4000
     rng = np.random.default_rng(seed)
@@ -323,6 +330,29 @@ def test_rerank_around_the_one_kernel_threshold(misa, rows, k_dtype, q_dtype, H,
     idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=300)
     assert torch.equal(idx, idx2)
     assert torch.equal(val, val2)
+
+
+@pytest.mark.parametrize("rows,kc", [(2, 129), (3, 16384), (7, 8191), (33, 11218), (96, 4738), (384, 655), (640, 130)])
+@pytest.mark.parametrize("k_dtype,q_dtype,H", [("bf16", "bf16", 64), ("e4m3", "bf16", 20), ("e4m3", "e4m3_matrix", 32)])
+def test_rerank_in_pieces_of_any_number(misa, rows, kc, k_dtype, q_dtype, H):
+    """Few rows: the pieces that a list is cut into follow from the number of rows, the scores do not."""
+    seed, L, k = 9700 + rows, 17000, kc // 3
+    matrix = q_dtype == "e4m3_matrix"
+    wl = WL.scaled(WL.WORKLOADS["c2"], n_seq=1, L=L, n_q=rows, H=H, h=1, B=64, k=1, k_cand=0, k_dtype=k_dtype,
+                   q_dtype="e4m3" if matrix else q_dtype, needles=6, name=f"rrp{seed}")
+    inp = WL.make_inputs(wl, seed=seed)
+    dv = misa.to_device(inp)
+    p = replace(dv["problem"], q_dtype=misa.FP8_E4M3_MATRIX) if matrix else dv["problem"]
+    rng = np.random.default_rng(seed)
+    cand = _candidates(rng, rows, L, kc, full=True)
+    cand[0, rows // 2, rng.integers(0, kc, kc // 9)] = -1
+    dcand = torch.from_numpy(cand).cuda()
+    idx, val = _rerank(misa, p, dv, dcand, kc, k)
+    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=max(1, rows // 3))
+    assert torch.equal(idx, idx2)
+    assert torch.equal(val, val2)
+    _check_rows_against_oracle(inp, cand, idx.cpu().numpy(), val.cpu().numpy(), k, sorted({0, rows // 2, rows - 1}),
+                               f"rerank {rows} x {kc}", abs_frac=ABS_FRAC_FP8_MATRIX if matrix else ABS_FRAC)
 
 
 @pytest.mark.parametrize("rows,kc,one_kernel", [

@@ -1,5 +1,5 @@
-"""Seeded random many-query re-rank problems (Eq. misa_final_topk): list lengths up to the
-8192 the one-kernel path takes and beyond, any k, head counts, storage types, ragged lists."""
+"""Seeded random many-query re-rank problems (Eq. misa_final_topk): list lengths below, inside and beyond the
+2048 to 8192 that the one-kernel path takes, any k, head counts, storage types, ragged lists."""
 import numpy as np
 import pytest
 import torch
@@ -36,7 +36,7 @@ def test_many_query_rerank_random(misa, seed):
     cand = _candidates(rng, rows, L, kc, full=bool(seed % 3 == 0))
     dcand = torch.from_numpy(cand).cuda()
     idx, val = _rerank(misa, p, dv, dcand, kc, k)
-    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=700)
+    idx2, val2 = _rerank_in_pieces(misa, p, dv, dcand, kc, k, piece=300)      # (well below the one-kernel threshold)
     assert torch.equal(idx, idx2), (rows, H, L, kc, k)
     assert torch.equal(val, val2), (rows, H, L, kc, k)
     sample = [0, rows - 1] + rng.choice(rows, size=6, replace=False).tolist()
